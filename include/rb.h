@@ -121,16 +121,16 @@ typedef enum { RB_DRIFT_LEAPFROG = 0, RB_DRIFT_EPICYCLE = 1 } rb_drift;
  *                   only the moments are recomputed bottom-up; otherwise the
  *                   tree is rebuilt.  Same results either way; rb_stats
  *                   counts the reused steps.  0: rebuild every step.
- *  walk64_schedule  FP64 walk: 0 chooses (3 when the accumulators allow it,
- *                   else 2 or 1 by size), 1 every lane walks for its
- *                   own particle, 2 a wave walks once for its 64 particles
- *                   (each lane keeping its own decisions), 3 as 2 with one
- *                   wave per subtree two levels below the root (64x the
- *                   work units for systems of few particles; the subtrees'
- *                   sums are added in octant order afterwards, so only
- *                   their rounding differs; a context whose accumulators
- *                   for this would exceed 2 GiB runs 2).  All visit, per
- *                   particle, the same nodes; only the speed differs.
+ *  walk64_schedule  FP64 walk: 0 (the fastest) rounds over a stack of opened
+ *                   nodes, several waves sharing 64 particles, 1 every lane
+ *                   walks for its own particle, 2 a wave walks once for its
+ *                   64 particles (each lane keeping its own decisions), 3 as
+ *                   2 with one wave per subtree one or two levels below the
+ *                   root (the subtrees' sums are added in octant order
+ *                   afterwards; a context whose accumulators for this would
+ *                   exceed 2 GiB runs 2).  All visit, per particle, the same
+ *                   nodes; the order of the sums, and so their rounding, and
+ *                   the speed differ.
  */
 typedef struct {
   double G;

@@ -2,27 +2,30 @@
 //
 // The result is the plain per-particle Barnes-Hut sum: every particle makes
 // its own opening decisions, w^2 < theta^2 R^2 with R measured from its own
-// position to the cell's centre of mass, and visits the nodes it needs in
-// depth-first octant order.  The opening test, the image shifts and the
-// term arithmetic round exactly as a plain sequential FP64 walk does, so the
-// decisions are reproducible bit for bit.
+// position to the cell's centre of mass, and adds the terms of exactly the
+// nodes that its own stackless walk (child link when opening, skip link
+// otherwise) would visit.  The opening test, the image shifts and the term
+// arithmetic round exactly as a plain sequential FP64 walk does, so the
+// decisions are reproducible bit for bit; only the order of the sums differs
+// between the schedules.
 //
-// Two schedules give the same sums.  k_walk64 (systems with many work
-// units): one wave takes 64 Morton-consecutive particles (one per lane)
-// and walks the tree once for all of them.  The node in hand is the same
-// for the whole wave, so its record is read with scalar loads; each lane
-// tests it against its own particle.  A lane takes part in a node only if
-// it opened every ancestor of that node; each lane keeps the deepest level
-// down to which it did so along the current path, and a node of level l is
-// its when that level is at least l.  Lanes that accept a cell add its
-// monopole (and quadrupole) term; the wave descends to the children when
-// any lane opened it and moves on to the next node after the subtree
-// otherwise.  Every lane
-// thus sees exactly the nodes, in exactly the order, that its own
-// stackless walk (child link when opening, skip link otherwise) would.
-// k_walk64_lane (few work units, where the wave's single chain of dependent
-// node loads would leave the chip waiting): every lane follows that
-// stackless walk on its own, with its own loads.
+// k_walk64, the walk unless another schedule is asked for: rounds over a
+// stack of opened nodes, one to sixteen waves per 64 Morton-consecutive
+// particles (described there).
+//
+// k_walk64_parts (schedules 2 and 3): one wave takes 64 Morton-consecutive
+// particles (one per lane) and walks the tree once for all of them.  The
+// node in hand is the same for the whole wave, so its record is read with
+// scalar loads; each lane tests it against its own particle.  A lane takes
+// part in a node only if it opened every ancestor of that node; each lane
+// keeps the deepest level down to which it did so along the current path,
+// and a node of level l is its when that level is at least l.  Lanes that
+// accept a cell add its monopole (and quadrupole) term; the wave descends to
+// the children when any lane opened it and moves on to the next node after
+// the subtree otherwise.
+//
+// k_walk64_lane (schedule 1): every lane follows its stackless walk on its
+// own, with its own loads.
 #include "rb_internal.h"
 
 // 1 / sqrt(x): hardware estimate y (relative error ~2^-23) refined by one
@@ -141,7 +144,7 @@ __device__ __forceinline__ uint32_t w64_uniform(uint32_t v) {
 // waves cover more of the node loads' latency (measured 10% faster on the
 // 256-patch ensemble).
 template <bool QUAD, bool STATS, int PD, bool OFF32>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk64(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk64_parts(
     const WalkItem *__restrict__ items, uint32_t n_items, int img_split, int n_img, int parts,
     int ngx, int ngy, int boundary, const PatchInfo *__restrict__ patch,
     const uint32_t *__restrict__ nlive, const uint32_t *__restrict__ root,
@@ -408,6 +411,430 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
   }
 }
 
+// ---------------------------------------------------------------------------
+// The walk of 64 Morton-consecutive particles (one per lane) as rounds over a
+// stack of opened nodes, NW waves per item.
+//
+// An entry of the stack names the children of an opened node, the ghost
+// image, and the lanes (a 64-bit mask) that opened the node and all its
+// ancestors: the particles that work on the children.  A round takes up to
+// eight entries per wave, one child per lane, and sorts the children by the
+// opening test over the item's whole bounding box:
+//   accepted by every lane   -- the cell's terms are added for the lanes of
+//                               the mask, without a test per lane;
+//   opened by every lane     -- the children are pushed with the same mask;
+//   neither                  -- every lane tests the cell on its own: those
+//                               that accept it add its terms, the others are
+//                               the mask its children are pushed with.
+// The box tests decide exactly as the lanes' own tests would.  A lane's test
+// compares fl(theta^2 R^2) with R^2 = fma(dz, dz, fma(dy, dy, dx dx)) and
+// d = fl(c - fl(x - o)); rounding is monotone, so the same expression over
+// the smallest (largest) |d| per axis that fl(c - y) takes on the box's
+// corners y bounds every lane's value from below (above), rounding included.
+// So every particle sees exactly the nodes its own stackless walk sees.
+//
+// Bound by FP64 issue: VALU busy 96% of the time, half of its lanes at work
+// (the lanes of a mask; 64 particles of a thin sheet need 1.9 times the nodes
+// that one needs).  A cell costs 36 FP64 operations and one FP32 reciprocal
+// root, its record arriving by scalar loads.  Against the node-by-node walk
+// of k_walk64_parts, opened nodes cost one lane of a round instead of a visit
+// of the whole wave, accepted cells need no test, and the 88 scalar
+// instructions of a visit fall to 11 per cell.  Whole calls, parts -> rounds:
+// 1,024-particle sphere 155 -> 143 us; four steps of the 50,000-particle
+// sheet 2.57 -> 2.15 ms (64 accumulator sets per particle become one); a step
+// of 64 patches (2.1e6 particles) 13.4 -> 11.1 ms; 1,048,583-particle sphere
+// 13.6 -> 10.6 ms (of these, FP32's start of the cells' reciprocal roots:
+// 88 instead of 95 ns per cell and SIMD).
+//
+// NW: sixteen waves share an item below RB_WALK64_WAVES16 items, eight below
+// RB_WALK64_WAVES8, four above (FP64 steps, us, at NW = 4 / 8 / 16: sheets of
+// 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
+// 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
+// 11.6 against 11.4 ms on 64 patches: four waves read a common part of the
+// tree).
+#define W64G_ENTRY 16  // bytes per stack entry
+// entries that depth-first descent may need on top of a full stack: one
+// entry popped and at most eight pushed per level
+#define W64G_RESERVE (7 * RB_DEPTH + 8)
+
+// stack entries per item: the rounds' full width while it holds less than
+// CAP - RESERVE - 56 NW; with NW = 1, 5 KB, so that LDS holds 32 waves a CU
+template <int NW>
+constexpr int w64g_cap() {
+  return NW == 1 ? 288 : 512 + 64 * NW;
+}
+
+__device__ __forceinline__ double w64_readlane_d(double v, int j) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, j);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), j);
+  return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+__device__ __forceinline__ uint64_t w64_readlane_u64(uint32_t lo, uint32_t hi, int j) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)hi, j) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)lo, j);
+}
+
+__device__ __forceinline__ double w64_wave_min(double v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) v = fmin(v, __shfl_xor(v, d, 64));
+  return w64_readlane_d(v, 0);
+}
+
+__device__ __forceinline__ double w64_wave_max(double v) {
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) v = fmax(v, __shfl_xor(v, d, 64));
+  return w64_readlane_d(v, 0);
+}
+
+// 1 / sqrt(x) as rb_rsqrt64, from FP32's estimate of the rounded x (as good a
+// start, about 2^-23 with the rounding of x, in less than half the time of
+// the FP64 instruction); for x whose FP32 value is normal and finite.
+__device__ __forceinline__ double w64_rsqrt_f32(double x) {
+  const double y = (double)__builtin_amdgcn_rsqf((float)x);
+  const double e = __builtin_fma(-(x * y), y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+
+// A node as the rounds' evaluation reads it, in scalar registers: centre of
+// mass, mass, quadrupole (not read for point masses).
+struct W64Node {
+  double cx, cy, cz, m, q0, q1, q2, q3, q4, q5;
+};
+
+template <bool Q, bool OFF32>
+__device__ __forceinline__ void w64g_load(w64_dbl_p mcom, w64_dbl_p Qarr, uint32_t v, W64Node &r) {
+  const w64_dbl_p mp = (w64_dbl_p)w64_at<OFF32>((const void *)mcom, v, 32u);
+  r.cx = mp[0]; r.cy = mp[1]; r.cz = mp[2]; r.m = mp[3];
+  if (Q) {
+    const w64_dbl_p qp = (w64_dbl_p)w64_at<OFF32>((const void *)Qarr, v, 48u);
+    r.q0 = qp[0]; r.q1 = qp[1]; r.q2 = qp[2]; r.q3 = qp[3]; r.q4 = qp[4]; r.q5 = qp[5];
+  }
+}
+
+// The terms of a cell (per unit G) for the lanes that call it.
+template <bool QUAD, bool RS32>
+__device__ __forceinline__ void w64g_cell(const W64Node &n, double d0, double d1, double d2,
+                                          double rho2, double &ax, double &ay, double &az) {
+  const double ri = RS32 ? w64_rsqrt_f32(rho2) : rb_rsqrt64(rho2);
+  const double u = ri * ri, g = ri * u;  // rho^-2, rho^-3
+  if (QUAD) {
+    const double e0 = __builtin_fma(n.q0, d0, __builtin_fma(n.q1, d1, n.q2 * d2));
+    const double e1 = __builtin_fma(n.q1, d0, __builtin_fma(n.q3, d1, n.q4 * d2));
+    const double e2 = __builtin_fma(n.q2, d0, __builtin_fma(n.q4, d1, n.q5 * d2));
+    const double dqd = __builtin_fma(d0, e0, __builtin_fma(d1, e1, d2 * e2));
+    const double gs = g * __builtin_fma(2.5 * dqd, u * u, n.m);
+    const double gu = g * u;
+    ax = __builtin_fma(-gu, e0, __builtin_fma(gs, d0, ax));
+    ay = __builtin_fma(-gu, e1, __builtin_fma(gs, d1, ay));
+    az = __builtin_fma(-gu, e2, __builtin_fma(gs, d2, az));
+  } else {
+    const double f = g * n.m;
+    ax = __builtin_fma(f, d0, ax);
+    ay = __builtin_fma(f, d1, ay);
+    az = __builtin_fma(f, d2, az);
+  }
+}
+
+template <int NW>
+__device__ __forceinline__ void w64g_sync() {
+  if (NW > 1) {
+    __syncthreads();
+  } else {  // one wave: order its LDS writes before its later reads
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+template <bool QUAD, bool STATS, int NW, bool RS32, bool OFF32>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk64(
+    const WalkItem *__restrict__ items, uint32_t n_units, int img_split, int n_img, int ngx,
+    int ngy, int boundary, const PatchInfo *__restrict__ patch,
+    const uint32_t *__restrict__ nlive, const uint32_t *__restrict__ root,
+    const NodeLink *__restrict__ link, const double4 *__restrict__ mcom_g,
+    const double *__restrict__ Q_g, const double *__restrict__ sx_g,
+    const double *__restrict__ sy_g, const double *__restrict__ sz_g,
+    const double *__restrict__ msrc_g, const double *__restrict__ sched,
+    const uint32_t *__restrict__ ctr, uint32_t P, double G, double b2, double theta2,
+    double *__restrict__ acc, uint64_t cap, unsigned long long *__restrict__ stats,
+    const uint32_t *__restrict__ lev_off, uint32_t *__restrict__ err, int slot) {
+  constexpr int CAP = w64g_cap<NW>();
+  // the stack's memory also takes the waves' partial sums at the end
+  static_assert(NW == 1 || CAP * W64G_ENTRY >= NW * 3 * 64 * 8, "reduction space");
+  static_assert(sizeof(uint4) == W64G_ENTRY, "stack entry");
+  __shared__ uint4 stk[CAP];
+  __shared__ uint32_t s_push[NW];
+  __shared__ double2 img[RB_MAX_IMAGES];
+  const w64_dbl_p mcom = (w64_dbl_p)mcom_g;
+  const w64_dbl_p Qarr = (w64_dbl_p)Q_g;
+  const w64_dbl_p msrc = (w64_dbl_p)msrc_g;
+  const w64_dbl_p sxc = (w64_dbl_p)sx_g, syc = (w64_dbl_p)sy_g, szc = (w64_dbl_p)sz_g;
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t w = NW > 1 ? w64_uniform(threadIdx.x >> 6) : 0u;
+  // workgroups are dealt to the eight XCDs in turn; workgroup b takes its
+  // unit from the (b mod 8)-th eighth, so that each XCD's L2 holds the nodes
+  // of one contiguous eighth of them
+  const uint32_t nb = gridDim.x, xq = nb >> 3, xr = nb & 7u, xcd = blockIdx.x & 7u;
+  const uint32_t unit = xcd * xq + (xcd < xr ? xcd : xr) + (blockIdx.x >> 3);
+  if (unit >= n_units) return;  // whole workgroups
+  const uint32_t n_nodes = lev_off[RB_NLEV];
+  const uint32_t item = img_split ? unit / (uint32_t)n_img : unit;
+  const int im0 = img_split ? (int)(unit % (uint32_t)n_img) : 0;
+  const int nim = img_split ? 1 : n_img;
+  const WalkItem it = items[item];
+  const uint32_t p = it.patch;
+  const double W = patch[p].W;
+  // (W 2^-l)^2 = fl(W W) 2^-2l exactly: scaling by a power of two is exact
+  const double W2 = W * W;
+  const int nvirt = (int)patch[p].nvirt;
+  const uint32_t st = patch[p].start, nl = nlive[p];
+  const uint32_t s = it.start + lane;
+  const bool valid = s < it.end && (s - st) < nl;
+  double px = 0.0, py = 0.0, pz = 0.0;
+  if (valid) { px = sx_g[s]; py = sy_g[s]; pz = sz_g[s]; }
+  const uint64_t live = __ballot(valid);
+  const uint32_t r0 = live ? w64_uniform(root[p]) : RB_NONE;
+  // the item's box
+  const double lx = w64_wave_min(valid ? px : INFINITY), hx = w64_wave_max(valid ? px : -INFINITY);
+  const double ly = w64_wave_min(valid ? py : INFINITY), hy = w64_wave_max(valid ? py : -INFINITY);
+  const double lz = w64_wave_min(valid ? pz : INFINITY), hz = w64_wave_max(valid ? pz : -INFINITY);
+  if (threadIdx.x < (uint32_t)n_img) {
+    double ox, oy;
+    bool self;
+    rb_image((int)threadIdx.x, ngx, ngy, boundary, patch[p].L[0], patch[p].L[1],
+             sched[(size_t)ctr[slot] * 2 * P + p], ox, oy, self);
+    img[threadIdx.x] = make_double2(ox, oy);
+  }
+  int sp = 0;
+  if (r0 != RB_NONE) {
+    if (r0 < n_nodes) {
+      sp = nim;
+      if (threadIdx.x < (uint32_t)nim)
+        stk[threadIdx.x] = make_uint4(r0, 1u | ((uint32_t)(im0 + (int)threadIdx.x) << 8),
+                                      (uint32_t)live, (uint32_t)(live >> 32));
+    } else if (threadIdx.x == 0) {
+      atomicOr(err, RB_ERR_TREE);
+    }
+  }
+  const uint32_t self_img = (uint32_t)(n_img / 2);  // the ghost rings' centre
+  uint32_t n_open = 0, n_cell = 0, n_pp = 0;
+  double ax = 0.0, ay = 0.0, az = 0.0;
+  // the image in hand and the particle as it sees it
+  uint32_t cur_img = RB_NONE;
+  double y0 = 0.0, y1 = 0.0;
+  auto to_image = [&](uint32_t im) {
+    if (im != cur_img) {  // uniform
+      cur_img = im;
+      const double2 o = img[im];
+      y0 = px - o.x;
+      y1 = py - o.y;
+    }
+  };
+  w64g_sync<NW>();
+  for (;;) {
+    // entries of this round: eight per wave, dealt to the waves in turn
+    int k = sp < 8 * NW ? sp : 8 * NW;
+    if (sp + 7 * k > CAP - W64G_RESERVE) {
+      k = (CAP - W64G_RESERVE - sp) / 7;
+      if (k < 1) k = sp > 0 ? 1 : 0;
+    }
+    if (k == 0) break;  // the same in every wave
+    const int pi = (int)(lane >> 3) * NW + (int)w;
+    uint4 en = make_uint4(0u, 0u, 0u, 0u);
+    if (pi < k) en = stk[sp - 1 - pi];
+    const uint32_t c8 = lane & 7u, node = en.x + c8, im = en.y >> 8;
+    const bool has = c8 < (en.y & 255u);
+    NodeLink lk = {0u, 0u, 0u, 0u};
+    double4 mc = make_double4(0.0, 0.0, 0.0, 0.0);
+    if (has) {
+      lk = link[node];
+      mc = mcom_g[node];
+    }
+    const double2 io = img[has ? im : 0u];
+    const int l = (int)(lk.lvl & 255u);
+    const bool leaf = (lk.lvl & 256u) != 0;
+    const uint32_t nch = lk.lvl >> 9;
+    const bool alive = has && mc.w != 0.0;
+    const bool single = alive && leaf && lk.count == 1u;
+    uint32_t mlo = en.z, mhi = en.w;
+    // smallest and largest distance per axis, as the lanes' tests round them
+    const double xa = mc.x - (lx - io.x), xb = mc.x - (hx - io.x);
+    const double ya = mc.y - (ly - io.y), yb = mc.y - (hy - io.y);
+    const double za = mc.z - lz, zb = mc.z - hz;
+    const double nx = fmax(fmax(xb, -xa), 0.0), fx = fmax(fabs(xa), fabs(xb));
+    const double ny = fmax(fmax(yb, -ya), 0.0), fy = fmax(fabs(ya), fabs(yb));
+    const double nz = fmax(fmax(zb, -za), 0.0), fz = fmax(fabs(za), fabs(zb));
+    const double near2 = __builtin_fma(nz, nz, __builtin_fma(ny, ny, nx * nx));
+    const double far2 = __builtin_fma(fz, fz, __builtin_fma(fy, fy, fx * fx));
+    const double w2 = ldexp(W2, -2 * l);
+    const bool cell = alive && !single;
+    // cells above the root boxes are always opened; a centre that is no
+    // number is opened, as by the lanes (their comparison fails)
+    const bool below = l >= nvirt;
+    const bool ordered = mc.x == mc.x && mc.y == mc.y && mc.z == mc.z;
+    const bool all_in = cell && below && ordered && w2 < theta2 * near2;
+    const bool all_out = cell && !(below && ordered && w2 < theta2 * far2);
+    const bool mixed = cell && !all_in && !all_out;
+    if (single && im == self_img) {
+      // every lane but the particle itself
+      const uint32_t own = lk.child_or_first - it.start;
+      if (own < 32u) mlo &= ~(1u << own);
+      else if (own < 64u) mhi &= ~(1u << (own - 32u));
+    }
+    if (STATS) {
+      const uint32_t cnt = (uint32_t)(__popc(mlo) + __popc(mhi));
+      if (cell && below) n_open += cnt;
+      if (all_in) n_cell += cnt;
+      if (single) n_pp += cnt;
+    }
+    // The children of one entry share its image, its mask and their level, and
+    // are numbered consecutively: everything but the child's number is read
+    // from lane 8 q once per entry.
+    const uint64_t b_mixed = __ballot(mixed);
+    const int n_mine = k > (int)w ? (k - (int)w + NW - 1) / NW : 0;
+    // the lanes that open the cell: all of the mask, or as they find
+    uint32_t plo = all_out ? mlo : 0u, phi = all_out ? mhi : 0u;
+    for (int q8 = 0; q8 < 8 * n_mine; q8 += 8) {
+      uint32_t m = (uint32_t)(b_mixed >> q8) & 255u;
+      if (m == 0u) continue;
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)node, q8);
+      const uint64_t mask = w64_readlane_u64(en.z, en.w, q8);
+      const double w2q = w64_readlane_d(w2, q8 + __builtin_ctz(m));
+      to_image((uint32_t)__builtin_amdgcn_readlane((int)im, q8));
+      do {
+        const uint32_t c = (uint32_t)__builtin_ctz(m);
+        m &= m - 1u;
+        W64Node nd;
+        w64g_load<QUAD, OFF32>(mcom, Qarr, first + c, nd);
+        const double d0 = nd.cx - y0, d1 = nd.cy - y1, d2 = nd.cz - pz;
+        const double R2 = __builtin_fma(d2, d2, __builtin_fma(d1, d1, d0 * d0));
+        const bool take = __builtin_amdgcn_inverse_ballot_w64(mask) && w2q < theta2 * R2;
+        const uint64_t opened = mask & ~__ballot(take);
+        if (take) {
+          w64g_cell<QUAD, RS32>(nd, d0, d1, d2, R2 + b2, ax, ay, az);
+          if (STATS) ++n_cell;
+        }
+        if (lane == (uint32_t)q8 + c) { plo = (uint32_t)opened; phi = (uint32_t)(opened >> 32); }
+      } while (m);
+    }
+    // opened nodes onto the stack (children are numbered after their parent,
+    // so the descent ends), opened bucket leaves to be summed below
+    const bool opens = (plo | phi) != 0u;
+    bool push = opens && !leaf;
+    if (push && !(lk.child_or_first > node && nch >= 1u && nch <= 8u && lk.child_or_first < n_nodes &&
+                  nch <= n_nodes - lk.child_or_first)) {
+      atomicOr(err, RB_ERR_TREE);
+      push = false;
+    }
+    const uint64_t pm = __ballot(push);
+    int at = sp - k, all = (int)__popcll(pm);
+    if (NW > 1) {
+      if (lane == 0) s_push[w] = (uint32_t)all;
+      __syncthreads();  // every wave has read its entries; counts known
+      all = 0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        const int t = (int)s_push[q];
+        if (q < (int)w) at += t;
+        all += t;
+      }
+    }
+    sp = sp - k + all;
+    if (sp > CAP) {  // cannot happen with the reserve above
+      if (threadIdx.x == 0) atomicOr(err, RB_ERR_STACK);
+      sp = 0;
+    } else if (push) {
+      stk[at + (int)rb_mbcnt(pm)] = make_uint4(lk.child_or_first, nch | (im << 8), plo, phi);
+    }
+    // accepted cells, then single-particle leaves
+    const uint64_t b_in = __ballot(all_in), b_single = __ballot(single);
+    for (int q8 = 0; q8 < 8 * n_mine; q8 += 8) {
+      uint32_t m = (uint32_t)(b_in >> q8) & 255u;
+      uint32_t ms = (uint32_t)(b_single >> q8) & 255u;
+      if ((m | ms) == 0u) continue;
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)node, q8);
+      const uint64_t mask = w64_readlane_u64(en.z, en.w, q8);
+      const uint32_t imq = (uint32_t)__builtin_amdgcn_readlane((int)im, q8);
+      to_image(imq);
+      if (m && __builtin_amdgcn_inverse_ballot_w64(mask)) {
+        do {
+          W64Node nd;
+          w64g_load<QUAD, OFF32>(mcom, Qarr, first + (uint32_t)__builtin_ctz(m), nd);
+          m &= m - 1u;
+          const double d0 = nd.cx - y0, d1 = nd.cy - y1, d2 = nd.cz - pz;
+          w64g_cell<QUAD, RS32>(nd, d0, d1, d2, w64_r2(d0, d1, d2, b2), ax, ay, az);
+        } while (m);
+      }
+      while (ms) {
+        const uint32_t c = (uint32_t)__builtin_ctz(ms);
+        ms &= ms - 1u;
+        W64Node nd;
+        w64g_load<false, OFF32>(mcom, Qarr, first + c, nd);
+        // the mask without the particle itself
+        const uint64_t others = imq == self_img ? w64_readlane_u64(mlo, mhi, q8 + (int)c) : mask;
+        if (__builtin_amdgcn_inverse_ballot_w64(others)) {
+          const double d0 = nd.cx - y0, d1 = nd.cy - y1, d2 = nd.cz - pz;
+          w64_mono(nd.m, d0, d1, d2, w64_r2(d0, d1, d2, b2), ax, ay, az);
+        }
+      }
+    }
+    // opened bucket leaves: their members one by one
+    for (uint64_t m = __ballot(opens && leaf); m; m &= m - 1) {
+      const int j = __ffsll((long long)m) - 1;
+      const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lk.child_or_first, j);
+      const uint32_t e = a + (uint32_t)__builtin_amdgcn_readlane((int)lk.count, j);
+      const uint64_t mine = w64_readlane_u64(plo, phi, j);
+      const uint32_t imj = (uint32_t)__builtin_amdgcn_readlane((int)im, j);
+      to_image(imj);
+      if (e < a || e > cap) {
+        if (lane == 0) atomicOr(err, RB_ERR_TREE);
+        continue;
+      }
+      for (uint32_t q = a; q < e; ++q) {
+        const double mj = msrc[q];
+        if (mj == 0.0) continue;
+        if (__builtin_amdgcn_inverse_ballot_w64(mine) && !(imj == self_img && q == s)) {
+          const double f0 = sxc[q] - y0, f1 = syc[q] - y1, f2 = szc[q] - pz;
+          w64_mono(mj, f0, f1, f2, w64_r2(f0, f1, f2, b2), ax, ay, az);
+          if (STATS) ++n_pp;
+        }
+      }
+    }
+    w64g_sync<NW>();  // entries written before the next round reads them
+  }
+  double *a = acc + (size_t)(img_split ? im0 : 0) * 3 * cap;
+  if (NW > 1) {
+    // the waves' sums, added in wave order
+    double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(&stk[0]);
+    red[w][0][lane] = ax; red[w][1][lane] = ay; red[w][2][lane] = az;
+    __syncthreads();
+    ax = ay = az = 0.0;
+    if (w == 0) {
+#pragma unroll
+      for (int q = 0; q < NW; ++q) {
+        ax += red[q][0][lane]; ay += red[q][1][lane]; az += red[q][2][lane];
+      }
+    }
+  }
+  if (w == 0 && s < it.end) {
+    a[s] = G * ax; a[cap + s] = G * ay; a[2 * cap + s] = G * az;
+  }
+  if (STATS) {
+    unsigned long long o = n_open, c = n_cell, q2 = n_pp;
+    for (int d = 32; d >= 1; d >>= 1) {
+      o += __shfl_xor(o, d, 64);
+      c += __shfl_xor(c, d, 64);
+      q2 += __shfl_xor(q2, d, 64);
+    }
+    if (lane == 0) {
+      atomicAdd(&stats[0], o);
+      atomicAdd(&stats[1], c);
+      atomicAdd(&stats[2], q2);
+    }
+  }
+}
+
 template <bool QUAD, bool STATS>
 __global__ __launch_bounds__(64) void k_walk64_lane(
     const WalkItem *__restrict__ items, int img_split, int n_img, int ngx, int ngy,
@@ -608,6 +1035,21 @@ __global__ __launch_bounds__(1024) void k_w64_list(uint32_t *__restrict__ ord,
   }
 }
 
+// Whether every accepted cell's rho^2 is a normal, finite FP32 value, so that
+// its reciprocal root may start from FP32's estimate: an accepted cell has
+// R^2 > (W 2^-21)^2 / theta^2, and no distance in the box or to an image is
+// above 8 times its longest side.  (Particle pairs may be closer than any
+// such bound; they always start from the FP64 instruction.)
+static bool w64_fp32_seed(const rb_ctx *c, double theta2, double b2) {
+  const double lo = 0x1p-120, hi = 0x1p+120;
+  if (!(b2 < hi)) return false;
+  for (const PatchInfo &p : c->h_patch) {
+    const double L = fmax(fmax(p.L[0], p.L[1]), p.L[2]);
+    if (!(p.W * p.W * 0x1p-42 > lo * theta2) || !(64.0 * L * L < hi)) return false;
+  }
+  return true;
+}
+
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot) {
   const uint32_t n_items = (uint32_t)c->h_items64.size();
@@ -617,6 +1059,37 @@ hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const do
   const double b2 = c->p.softening * c->p.softening;
   const double th2 = c->p.theta * c->p.theta;
   const bool quad = c->p.quadrupole != 0, stats = (c->p.profile & 2) != 0;
+  if (c->walk64_mode == 0) {
+    const dim3 g(units);
+    const bool rs32 = w64_fp32_seed(c, th2, b2);
+#define RB_W64G_ARGS                                                                        \
+  c->d_items64, units, split, c->n_img, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,     \
+      c->d_patch, c->d_nlive, c->d_root, c->d_link, c->d_mcom, c->d_Q, sx, sy, sz, c->d_msrc, \
+      c->d_sched, c->d_ctr, c->P, c->p.G, b2, th2, c->d_acc, c->cap, c->d_stats,             \
+      c->d_lev_off, c->d_err, slot
+#define RB_W64G_NW(Q, S, R, O)                                                               \
+  do {                                                                                       \
+    if (nw == 4) hipLaunchKernelGGL((k_walk64<Q, S, 4, R, O>), g, dim3(256), 0, c->stream, RB_W64G_ARGS); \
+    else if (nw == 8) hipLaunchKernelGGL((k_walk64<Q, S, 8, R, O>), g, dim3(512), 0, c->stream, RB_W64G_ARGS); \
+    else hipLaunchKernelGGL((k_walk64<Q, S, 16, R, O>), g, dim3(1024), 0, c->stream, RB_W64G_ARGS); \
+  } while (0)
+#define RB_W64G_S(Q, S)                             \
+  do {                                              \
+    if (rs32 && off32) RB_W64G_NW(Q, S, true, true); \
+    else if (rs32) RB_W64G_NW(Q, S, true, false);    \
+    else RB_W64G_NW(Q, S, false, false);             \
+  } while (0)
+    const int nw = c->walk64_waves;
+    const bool off32 = c->node_cap * 48ull < (1ull << 32);
+    if (quad && stats) RB_W64G_S(true, true);
+    else if (quad) RB_W64G_S(true, false);
+    else if (stats) RB_W64G_S(false, true);
+    else RB_W64G_S(false, false);
+#undef RB_W64G_S
+#undef RB_W64G_NW
+#undef RB_W64G_ARGS
+    return hipGetLastError();
+  }
   if (c->walk64_mode != 1) {
     const int parts = c->walk_parts;
     unsigned grid = units * (uint32_t)parts;  // one unit per wave and workgroup
@@ -642,12 +1115,12 @@ hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const do
     const bool off32 = c->node_cap * 48ull < (1ull << 32);
 #define RB_W64_LAUNCH(PD)                                                                          \
   do {                                                                                             \
-    if (quad && stats) hipLaunchKernelGGL((k_walk64<true, true, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
-    else if (quad && off32) hipLaunchKernelGGL((k_walk64<true, false, PD, true>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
-    else if (quad) hipLaunchKernelGGL((k_walk64<true, false, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
-    else if (stats) hipLaunchKernelGGL((k_walk64<false, true, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
-    else if (off32) hipLaunchKernelGGL((k_walk64<false, false, PD, true>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
-    else hipLaunchKernelGGL((k_walk64<false, false, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    if (quad && stats) hipLaunchKernelGGL((k_walk64_parts<true, true, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    else if (quad && off32) hipLaunchKernelGGL((k_walk64_parts<true, false, PD, true>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    else if (quad) hipLaunchKernelGGL((k_walk64_parts<true, false, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    else if (stats) hipLaunchKernelGGL((k_walk64_parts<false, true, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    else if (off32) hipLaunchKernelGGL((k_walk64_parts<false, false, PD, true>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
+    else hipLaunchKernelGGL((k_walk64_parts<false, false, PD, false>), g, bl, 0, c->stream, RB_WALK64_ARGS); \
   } while (0)
     if (parts == 64) RB_W64_LAUNCH(2);
     else if (parts == 8) RB_W64_LAUNCH(1);

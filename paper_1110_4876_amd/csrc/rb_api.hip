@@ -141,27 +141,22 @@ double shear_offset(const rb_params &p, double Lx, double Ly, double t) {
 }
 
 // One walk work item per (group, image) pair, or per group with all its
-// images, and the FP64 walk's schedule.  The FP64 walk is split by the
-// subtrees below the root (schedule 3) whenever the accumulators allow it,
-// taking all images per item: measured faster than one wave per 64
-// particles (schedule 2) from 10^3 to 10^7 particles (2.6x at 50,000, 11%
-// at 10^6, 1-2% above 4·10^6).  Otherwise schedule 2, or per-lane walks
-// (schedule 1, with a split by image) when the 64-particle items would
-// leave the chip idle.  The grouped FP32 walk already draws from a device
-// queue and splits only on request.
+// images, and the FP64 walk's schedule: rounds over a stack of opened nodes
+// (all images per item unless split on request) unless the parameters ask
+// for another.  Of those, the split by the subtrees below the root (schedule
+// 3) needs an accumulator set per part and falls back to schedule 2 where
+// they were not allocated; schedules 1 and 2 take an item per image below
+// 16384 items.  The grouped FP32 walk draws from a device queue and splits
+// only on request.
 void set_split(rb_ctx *c) {
   const uint32_t n_items = (uint32_t)c->h_items64.size();
   const bool fp64 = c->p.precision == RB_FP64;
   int mode = c->p.walk64_schedule;
-  if (mode == 0) {
-    const uint32_t units = n_items * (uint32_t)c->n_img;
-    if (c->acc_sets >= RB_WALK64_PARTS) mode = 3;
-    else mode = units >= RB_WALK64_SHARED_MIN ? 2 : 1;
-  }
+  c->walk64_waves = n_items < RB_WALK64_WAVES16 ? 16 : n_items < RB_WALK64_WAVES8 ? 8 : 4;
   const int sp = c->p.split_images;
   if (c->n_img <= 1 || sp == 0) c->img_split = 0;
   else if (sp == 1) c->img_split = 1;
-  else c->img_split = (fp64 && mode != 3 && n_items < 16384) ? 1 : 0;
+  else c->img_split = (fp64 && (mode == 1 || mode == 2) && n_items < 16384) ? 1 : 0;
   // parts need an accumulator set each (d_acc is sized at creation)
   const int per = c->img_split ? c->n_img : 1;
   int parts = (n_items < RB_WALK64_PARTS2_MAX_ITEMS) ? RB_WALK64_PARTS2 : RB_WALK64_PARTS;

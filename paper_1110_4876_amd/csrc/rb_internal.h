@@ -56,9 +56,11 @@ struct rb_ctx {
   uint64_t node_cap = 0;
   int n_img = 1;             // ghost images
   int img_split = 0;         // items per image (1) or all images per item (0)
-  // FP64 walk: 1 (per-lane walks), 2 (wave-shared) or 3 (wave-shared, one
-  // unit per child subtree of the root); walk_parts = 8 with 3, else 1
-  int walk64_mode = 1;
+  // FP64 walk: 0 (rounds over a stack, walk64_waves waves per item), 1
+  // (per-lane walks), 2 (wave-shared) or 3 (wave-shared, one unit per
+  // subtree one or two levels below the root; walk_parts = 8 or 64, else 1)
+  int walk64_mode = 0;
+  int walk64_waves = 4;
   int walk_parts = 1;
   int acc_sets = 1;          // sets of 3 * cap doubles that d_acc holds
 
@@ -292,8 +294,10 @@ hipError_t launch_rowscan_levels(rb_ctx *c, const uint32_t *reuse = nullptr);
 #define RB_W64_HEAVY_OFF (RB_W64_TAG_OFF + RB_WALK64_ORDER_CAP)
 #define RB_W64_ORD_WORDS (RB_W64_HEAVY_OFF + RB_WALK64_HEAVY_MAX)
 inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c->walk_parts; }
-// work units from which the wave-shared FP64 walk beats per-lane walks
-#define RB_WALK64_SHARED_MIN 12288u
+// 64-particle items below which sixteen (eight) waves share an item's rounds
+// in the FP64 walk; four above
+#define RB_WALK64_WAVES16 1024u
+#define RB_WALK64_WAVES8 8192u
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot);
 hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const double *sz,

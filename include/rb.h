@@ -334,7 +334,7 @@ int rb_batch_gravity(rb_ctx *ctx, const rb_particles *p, double t, double *ax,
  * (capacity >= 2^28, or node capacity >= 2^27), RB_ECAPACITY (more than 8
  * pairs per particle), and the deferred errors of the tree build.  Phase
  * times: "coll_search" is the search kernel, "collide" the rest (R_max, cell
- * records, work items, resolution rounds).
+ * records, work items, resolution).
  */
 int rb_collide(rb_ctx *ctx, rb_particles *p, const double *radius, int64_t n, double t,
                double epsilon, uint64_t seed, int64_t *n_pairs, int64_t *n_resolved,
@@ -395,7 +395,7 @@ enum { RB_SWEEP_X = 0, RB_SWEEP_PHI = 1 };
  * than 8 pairs per particle), RB_EOUTSIDE (a particle outside a periodic or
  * shear axis).  The context's tree is not kept (the sort reuses its
  * buffers).  Phase times: "coll_search" is the sweep, "collide" the
- * resolution rounds.
+ * resolution.
  */
 int rb_sweep(rb_ctx *ctx, rb_particles *p, const double *radius, int64_t n, double t,
              double dt, int32_t axis, double epsilon, uint64_t seed, int64_t *n_pairs,

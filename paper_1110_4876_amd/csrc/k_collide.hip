@@ -16,13 +16,14 @@
 // queued once, from its lower caller index i, as the code i 2^35 + j 2^7 + k.
 //
 // Order and resolution: the queue's order is ascending h = splitmix64(seed +
-// code) (a bijection, so the order is total).  Resolving collisions one after
-// the other in that order is reproduced in rounds: a collision is resolved
-// in the first round in which it has the smallest h among the unresolved
-// collisions of both its particles (collisions without a common particle
-// commute).  Resolution applies v_n' = -eps v_n, v_t' = v_t with momentum
-// conservation when the pair approaches (d . u < 0, u = v_j + w_k - v_i with
-// w_k the image's shear velocity).
+// code) (a bijection, so the order is total).  Resolving the collisions one
+// after the other in that order gives each of them the velocities left by the
+// earlier collisions of its own two particles, and collisions without a
+// common particle commute: so a collision may be resolved as soon as its
+// predecessors, the last earlier one of each particle, have been (k_coll_run).
+// Resolution applies v_n' = -eps v_n, v_t' = v_t with momentum conservation
+// when the pair approaches (d . u < 0, u = v_j + w_k - v_i with w_k the
+// image's shear velocity).
 //
 // Compiled without FP contraction so that the pair tests and the velocity
 // updates round exactly as a plain evaluation of the same expressions.
@@ -43,10 +44,12 @@ __global__ __launch_bounds__(256) void k_coll_rmax(const double *__restrict__ R,
                                                    const uint32_t *__restrict__ starts,
                                                    const uint32_t *__restrict__ nlive,
                                                    uint32_t P, uint32_t n,
-                                                   unsigned long long *__restrict__ rmax) {
+                                                   unsigned long long *__restrict__ rmax,
+                                                   uint32_t *__restrict__ head) {
   __shared__ double part[4];
   double r = 0.0;
   for (uint32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
+    head[s] = RB_NONE;  // the particles' lists of pairs start empty
     const uint32_t p = (P == 1) ? 0u : rb_patch_of(starts, P, s);
     if (s - starts[p] < nlive[p]) {
       const double v = R[orig[s]];
@@ -157,8 +160,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const PatchInfo *__restrict__ patch, const uint32_t *__restrict__ starts,
     const uint32_t *__restrict__ nlive, const uint32_t *__restrict__ root,
     const CollNode *__restrict__ cells, int ngx, int ngy, int boundary, double omega, double t,
-    const unsigned long long *__restrict__ rmax_bits, uint64_t *__restrict__ queue,
-    uint32_t qcap, uint32_t *__restrict__ qcnt, uint32_t *__restrict__ err,
+    const unsigned long long *__restrict__ rmax_bits, CollQueue Q, uint32_t *__restrict__ err,
     const uint16_t *__restrict__ wrap, const unsigned long long *__restrict__ disp_bits,
     const double *__restrict__ sched, const uint32_t *__restrict__ ctr, int slot,
     uint32_t P) {
@@ -304,7 +306,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
                 const double sum = Ri + cr_[q];
                 if (d0 * d0 + d1 * d1 + d2 * d2 < sum * sum)
                   rb_coll_keep(((uint64_t)oi << 35) | ((uint64_t)oj << 7) | (uint64_t)kc,
-                               mine, nm, queue, qcap, qcnt, err);
+                               mine, nm, Q);
               }
             }
             coll_wave_sync();
@@ -358,56 +360,42 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
       nl += __popcll(lm);
       coll_wave_sync();
     }
-    // the rest: one atomic per wave
-    const uint32_t incl = rb_wave_incl_scan(nm);
-    const uint32_t tot = __shfl(incl, 63, 64);
-    uint32_t qbase = 0;
-    if (lane == 63 && tot) qbase = atomicAdd(qcnt, tot);
-    qbase = __shfl(qbase, 63, 64);
-    const uint32_t at = qbase + incl - nm;
-    for (uint32_t q = 0; q < nm; ++q)
-      if (at + q < qcap) queue[at + q] = mine[q];
-    if (nm && at + nm > qcap) atomicOr(err, RB_ERR_COLL);
+    rb_coll_rest(mine, nm, Q);
   }
 }
 
-// The rounds run on a fixed grid that strides over the list, whose length
-// each kernel reads on the device (at most the queue's capacity), so the host
-// launches them without knowing it.
-#define CR_GRID 256
-
-// round, step 1: every particle learns the smallest h among its unresolved
-// collisions; the next list's count is cleared (that list was the previous
-// round's input), and the first round saves the number of detected pairs
-__global__ __launch_bounds__(256) void k_coll_min(const uint64_t *__restrict__ list,
-                                                  const uint32_t *__restrict__ cnt,
-                                                  uint32_t *__restrict__ next_cnt,
-                                                  uint32_t *__restrict__ save, uint32_t qcap,
-                                                  uint64_t seed,
-                                                  unsigned long long *__restrict__ best) {
-  const uint32_t n = min(cnt[0], qcap);
-  const uint32_t q0 = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q0 == 0) {
-    next_cnt[0] = 0;
-    if (save) save[0] = cnt[0];
-  }
-  for (uint32_t q = q0; q < n; q += gridDim.x * blockDim.x) {
-    const uint64_t c = list[q];
-    const unsigned long long h = rb_splitmix64(seed + c);
-    atomicMin(&best[c >> 35], h);
-    atomicMin(&best[(c >> 7) & ((1ull << 28) - 1ull)], h);
-  }
+// Words that another thread of the same launch may just have written, or may
+// read next, are loaded and exchanged at the device's coherent point.  An
+// exchange that has returned has been performed there: coll_performed waits
+// for the returned words, so whatever this thread sends out afterwards is
+// seen only after them.
+__device__ __forceinline__ double coll_ld(const double *p) {
+  return __longlong_as_double((long long)__hip_atomic_load(
+      reinterpret_cast<unsigned long long *>(const_cast<double *>(p)), __ATOMIC_RELAXED,
+      __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ uint32_t coll_xchg(double *p, double v) {
+  return (uint32_t)__hip_atomic_exchange(reinterpret_cast<unsigned long long *>(p),
+                                         (unsigned long long)__double_as_longlong(v),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t coll_xchg(uint32_t *p, uint32_t v) {
+  return __hip_atomic_exchange(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void coll_performed(uint32_t returned) {
+  asm volatile("" ::"v"(returned) : "memory");
 }
 
 // Resolve the collision of code c if its particles approach (d . u < 0);
-// returns whether it did.  Each particle takes part in at most one
-// collision resolved in a round, so the updates of a round do not race.
+// returns whether it did.  Its predecessors are done and its successors wait
+// for it, so no other thread uses the two velocities meanwhile.
 // The arrays are in caller order, or (inv given: collisions inside a step)
 // in the step's sorted order, inv mapping caller indices to slots; the
 // shear offset is taken from the step's schedule row when s_end is given.
 __device__ __forceinline__ bool rb_coll_apply(
-    uint64_t c, double *__restrict__ x, double *__restrict__ y, double *__restrict__ z,
-    double *__restrict__ vx, double *__restrict__ vy, double *__restrict__ vz,
+    uint64_t c, const double *__restrict__ x, const double *__restrict__ y,
+    const double *__restrict__ z, double *__restrict__ vx, double *__restrict__ vy,
+    double *__restrict__ vz,
     const double *__restrict__ m, const PatchInfo *__restrict__ patch,
     const uint32_t *__restrict__ starts, uint32_t P, int ngx, int ngy, int boundary,
     double omega, double t, double eps, const uint32_t *__restrict__ inv = nullptr,
@@ -422,12 +410,14 @@ __device__ __forceinline__ bool rb_coll_apply(
                     : s_end ? s_end[p] : remainder(1.5 * omega * W * t, W);
   double ox, oy, wy;
   rb_coll_image(k, ngx, ngy, boundary, W, sh, omega, ox, oy, wy);
+  const double vi0 = coll_ld(vx + i), vi1 = coll_ld(vy + i), vi2 = coll_ld(vz + i);
+  const double vj0 = coll_ld(vx + j), vj1 = coll_ld(vy + j), vj2 = coll_ld(vz + j);
   const double d0 = (x[j] + ox) - x[i];
   const double d1 = (y[j] + oy) - y[i];
   const double d2 = (z[j] + 0.0) - z[i];
-  const double u0 = vx[j] - vx[i];
-  const double u1 = (vy[j] + wy) - vy[i];
-  const double u2 = vz[j] - vz[i];
+  const double u0 = vj0 - vi0;
+  const double u1 = (vj1 + wy) - vi1;
+  const double u2 = vj2 - vi2;
   const double M = m[i] + m[j];
   if (!(d0 * u0 + d1 * u1 + d2 * u2 < 0.0 && M > 0.0)) return false;
   const double dist = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
@@ -435,165 +425,127 @@ __device__ __forceinline__ bool rb_coll_apply(
   const double vn = n0 * u0 + n1 * u1 + n2 * u2;
   const double f = (1.0 + eps) * vn;
   const double fi = (m[j] / M) * f, fj = (m[i] / M) * f;
-  vx[i] = vx[i] + fi * n0; vy[i] = vy[i] + fi * n1; vz[i] = vz[i] + fi * n2;
-  vx[j] = vx[j] - fj * n0; vy[j] = vy[j] - fj * n1; vz[j] = vz[j] - fj * n2;
+  coll_performed(coll_xchg(vx + i, vi0 + fi * n0) ^ coll_xchg(vy + i, vi1 + fi * n1) ^
+                 coll_xchg(vz + i, vi2 + fi * n2) ^ coll_xchg(vx + j, vj0 - fj * n0) ^
+                 coll_xchg(vy + j, vj1 - fj * n1) ^ coll_xchg(vz + j, vj2 - fj * n2));
   return true;
 }
 
-// round, step 2: collisions first in line for both particles are resolved;
-// the others go to the next round's list
-__global__ __launch_bounds__(256) void k_coll_resolve(
-    const uint64_t *__restrict__ list, const uint32_t *__restrict__ cnt, uint32_t qcap,
-    uint64_t *__restrict__ next, uint32_t *__restrict__ next_cnt, uint64_t seed,
-    const unsigned long long *__restrict__ best, double *__restrict__ x,
-    double *__restrict__ y, double *__restrict__ z, double *__restrict__ vx,
+// Arrivals at a pair: three start it.  The owner thread brings one for
+// itself and one for each side without a predecessor, once the pair's
+// successors are written; every predecessor brings one.  The arrival that
+// completes them runs the pair (nobody waits for anybody).  An arrival is
+// sent only once the velocities and successors before it have been performed
+// (coll_performed), so the thread that completes the pair loads them as they
+// were left.  (Release and acquire fences instead write back and invalidate
+// an XCD's whole L2 each time: 220,617 pairs took 2.10 ms per call with them,
+// 1.03 ms this way.)
+__device__ __forceinline__ uint32_t coll_arrive(uint32_t *arr, uint32_t q, uint32_t v) {
+  return __hip_atomic_fetch_add(&arr[q], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + v;
+}
+
+// the queue's launch: one pair per thread up to 65,536 pairs
+#define CR_BLOCKS 256
+#define CR_THREADS 256u
+
+// The whole queue in one launch, in the order of the keys h at every
+// particle.  Thread by thread over the pairs: the pair's place among its
+// particles' other pairs (the smallest later key of each side is its
+// successor, an earlier key means it has a predecessor), then its arrival; a
+// thread whose arrival completes a pair resolves it and follows its
+// successors from there.
+//
+// Inside a step (inv given) the arrays are in the step's sorted order, inv
+// maps caller indices to slots, the seed is the step's (seedp[0] + the step
+// index), the shear offset the step's end-time offset, and the pairs and
+// resolutions are added to the running totals in cum.  Being the last kernel
+// before the host reads the counts, it copies the error word next to them
+// (cnt[3]).
+//
+// Bound by latency: the links of the longest chain of dependent collisions,
+// each a round trip for the pair's words, one for the velocities and one for
+// the exchanges and arrivals.  A round at a time in one workgroup (three
+// barriers and three passes over the list each), or, between calls, in three
+// launches and the counts read back by the host every four rounds, against
+// one launch: 50,000-particle settled sheet inside a step 282 -> 34 us; as a
+// call 80 -> 41 us (9,938 pairs); ring with 27,939 pairs 234 -> 82 us.  With
+// no pair at all the launch costs 1 us more than the one workgroup did.
+__global__ __launch_bounds__(CR_THREADS) void k_coll_run(
+    CollQueue Q, uint32_t *__restrict__ succ, uint64_t seed, const double *__restrict__ x,
+    const double *__restrict__ y, const double *__restrict__ z, double *__restrict__ vx,
     double *__restrict__ vy, double *__restrict__ vz, const double *__restrict__ m,
     const PatchInfo *__restrict__ patch, const uint32_t *__restrict__ starts, uint32_t P,
     int ngx, int ngy, int boundary, double omega, double t, double eps,
-    unsigned long long *__restrict__ n_res) {
-  const uint32_t n = min(cnt[0], qcap);
-  // wave-uniform trip count: a wave covers 64 consecutive entries per pass
-  const uint32_t wbase = blockIdx.x * blockDim.x + (threadIdx.x & ~63u);
-  for (uint32_t q0 = wbase; q0 < n; q0 += gridDim.x * blockDim.x) {
-    const uint32_t q = q0 + rb_lane();
-    const bool in = q < n;
-    uint64_t c = 0;
-    bool ready = false;
-    if (in) {
-      c = list[q];
-      const unsigned long long h = rb_splitmix64(seed + c);
-      ready = best[c >> 35] == h && best[(c >> 7) & ((1ull << 28) - 1ull)] == h;
-    }
-    const bool resolved = ready && rb_coll_apply(c, x, y, z, vx, vy, vz, m, patch, starts, P,
-                                                 ngx, ngy, boundary, omega, t, eps);
-    const uint64_t rm = __ballot(resolved);
-    if (rb_lane() == 0 && rm) atomicAdd(n_res, (unsigned long long)__popcll(rm));
-    // survivors to the next list, one atomic per wave
-    const bool keep = in && !ready;
-    const uint64_t km = __ballot(keep);
-    uint32_t base = 0;
-    if (rb_lane() == 0 && km) base = atomicAdd(next_cnt, (uint32_t)__popcll(km));
-    base = __shfl(base, 0, 64);
-    if (keep) next[base + rb_mbcnt(km)] = c;
-  }
-}
-
-// round, step 3: the particles of this round's collisions forget their
-// minimum (ready for the next round)
-__global__ __launch_bounds__(256) void k_coll_reset(const uint64_t *__restrict__ list,
-                                                    const uint32_t *__restrict__ cnt,
-                                                    uint32_t qcap,
-                                                    unsigned long long *__restrict__ best) {
-  const uint32_t n = min(cnt[0], qcap);
-  for (uint32_t q = blockIdx.x * blockDim.x + threadIdx.x; q < n;
-       q += gridDim.x * blockDim.x) {
-    const uint64_t c = list[q];
-    best[c >> 35] = ~0ull;
-    best[(c >> 7) & ((1ull << 28) - 1ull)] = ~0ull;
-  }
-}
-
-// All remaining rounds in one workgroup, for short lists (at most CR_SMALL
-// entries; a longer list is left as it is, for the multi-workgroup rounds).
-// The lists ping-pong between l[a] and l[1 - a]; on completion both counts
-// are zero.  Being the last kernel before the host reads the counts, it
-// copies the error word next to them (cnt[3]).  best[] is read and cleared with device-scope atomics (its
-// minima are formed by atomics, which the L1 cache does not see); the
-// velocities are plain loads and stores ordered by the workgroup barriers.
-#define CR_SMALL 4096
-//
-// Inside a step (inv given) every queue is resolved here, however long; the
-// seed is the step's (seedp[0] + the step index), the shear offset the
-// step's end-time offset, and the pairs and resolutions are added to the
-// running totals in cum.
-__global__ __launch_bounds__(1024) void k_coll_rounds1(
-    uint64_t *__restrict__ l0, uint64_t *__restrict__ l1, uint32_t *__restrict__ cnt, int a,
-    uint32_t *__restrict__ save, uint32_t qcap, uint64_t seed,
-    unsigned long long *__restrict__ best, double *__restrict__ x, double *__restrict__ y,
-    double *__restrict__ z, double *__restrict__ vx, double *__restrict__ vy,
-    double *__restrict__ vz, const double *__restrict__ m,
-    const PatchInfo *__restrict__ patch, const uint32_t *__restrict__ starts, uint32_t P,
-    int ngx, int ngy, int boundary, double omega, double t, double eps,
-    unsigned long long *__restrict__ n_res, const uint32_t *__restrict__ err,
-    const uint32_t *__restrict__ inv, const uint64_t *__restrict__ seedp,
-    const double *__restrict__ sched, const uint32_t *__restrict__ ctr, int slot,
-    unsigned long long *__restrict__ cum) {
-  __shared__ uint32_t s_n, s_next;
-  __shared__ unsigned long long s_res;
-  const uint32_t tid = threadIdx.x;
-  const uint32_t n0 = min(cnt[a], qcap);
-  if (tid == 0 && save) save[0] = cnt[a];
+    unsigned long long *__restrict__ n_res, const uint32_t *__restrict__ inv,
+    const uint64_t *__restrict__ seedp, const double *__restrict__ sched,
+    const uint32_t *__restrict__ ctr, int slot, unsigned long long *__restrict__ cum) {
+  const uint32_t n = min(Q.cnt[0], Q.cap);
   const double *s_end = inv ? sched + (size_t)ctr[slot] * 2 * P + P : nullptr;
   if (inv) seed = seedp[0] + ctr[slot];
-  if (!inv && n0 > CR_SMALL) {  // uniform
-    if (tid == 0) cnt[3] = err[0];
-    return;
-  }
-  if (tid == 0) {
-    s_n = n0;
-    s_res = 0;
-  }
-  uint64_t *cur = a ? l1 : l0, *nxt = a ? l0 : l1;
-  __syncthreads();
-  for (;;) {
-    const uint32_t n = s_n;
-    if (n == 0) break;  // uniform
-    if (tid == 0) s_next = 0;
-    for (uint32_t q = tid; q < n; q += blockDim.x) {
-      const uint64_t c = cur[q];
-      const unsigned long long h = rb_splitmix64(seed + c);
-      atomicMin(&best[c >> 35], h);
-      atomicMin(&best[(c >> 7) & ((1ull << 28) - 1ull)], h);
-    }
-    __syncthreads();
-    for (uint32_t q0 = tid & ~63u; q0 < n; q0 += blockDim.x) {
-      const uint32_t q = q0 + rb_lane();
-      const bool in = q < n;
-      uint64_t c = 0;
-      bool ready = false;
-      if (in) {
-        c = cur[q];
-        const unsigned long long h = rb_splitmix64(seed + c);
-        ready = __hip_atomic_load(&best[c >> 35], __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT) == h &&
-                __hip_atomic_load(&best[(c >> 7) & ((1ull << 28) - 1ull)], __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT) == h;
+  uint32_t done = 0;
+  for (uint32_t own = blockIdx.x * CR_THREADS + threadIdx.x; own < n;
+       own += gridDim.x * CR_THREADS) {
+    const uint64_t code = Q.code[own];
+    const uint64_t h = rb_splitmix64(seed + code);
+    uint32_t node[2] = {Q.head[rb_coll_i(code)], Q.head[rb_coll_j(code)]};
+    uint64_t best[2] = {~0ull, ~0ull};
+    uint32_t next[2] = {RB_NONE, RB_NONE};
+    bool pred[2] = {false, false};
+    while ((node[0] & node[1]) != RB_NONE) {  // both lists side by side
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        if (node[e] == RB_NONE) continue;
+        const uint32_t q = node[e] >> 1;
+        const uint64_t hq = rb_splitmix64(seed + Q.code[q]);
+        node[e] = Q.link[node[e]];
+        if (hq < h) pred[e] = true;
+        if (hq > h && hq < best[e]) {
+          best[e] = hq;
+          next[e] = q;
+        }
       }
-      const bool resolved = ready && rb_coll_apply(c, x, y, z, vx, vy, vz, m, patch, starts,
-                                                   P, ngx, ngy, boundary, omega, t, eps, inv,
-                                                   s_end);
-      const uint64_t rm = __ballot(resolved);
-      if (rb_lane() == 0 && rm) atomicAdd(&s_res, (unsigned long long)__popcll(rm));
-      const bool keep = in && !ready;
-      const uint64_t km = __ballot(keep);
-      uint32_t base = 0;
-      if (rb_lane() == 0 && km) base = atomicAdd(&s_next, (uint32_t)__popcll(km));
-      base = __shfl(base, 0, 64);
-      if (keep) nxt[base + rb_mbcnt(km)] = c;
     }
-    __syncthreads();
-    for (uint32_t q = tid; q < n; q += blockDim.x) {
-      const uint64_t c = cur[q];
-      __hip_atomic_store(&best[c >> 35], ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&best[(c >> 7) & ((1ull << 28) - 1ull)], ~0ull, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    coll_performed(coll_xchg(&succ[2 * (size_t)own], next[0]) ^
+                   coll_xchg(&succ[2 * (size_t)own + 1], next[1]));
+    // the pair to run, and a list of pairs ready to run after it (linked
+    // through their arrival words, which nobody adds to any more)
+    uint32_t run = RB_NONE, more = RB_NONE;
+    if (coll_arrive(Q.arr, own, 3u - (pred[0] ? 1u : 0u) - (pred[1] ? 1u : 0u)) == 3u) run = own;
+    while (run != RB_NONE) {
+      asm volatile("" ::: "memory");  // no load of the pair's words before its last arrival
+      const uint32_t s0 = __hip_atomic_load(&succ[2 * (size_t)run], __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t s1 = __hip_atomic_load(&succ[2 * (size_t)run + 1], __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+      if (rb_coll_apply(Q.code[run], x, y, z, vx, vy, vz, m, patch, starts, P, ngx, ngy, boundary,
+                        omega, t, eps, inv, s_end))
+        ++done;
+      run = RB_NONE;
+      const uint32_t a0 = s0 != RB_NONE ? coll_arrive(Q.arr, s0, 1u) : 0u;
+      const uint32_t a1 = s1 != RB_NONE ? coll_arrive(Q.arr, s1, 1u) : 0u;
+      if (a0 == 3u) run = s0;
+      if (a1 == 3u) {
+        if (run == RB_NONE) {
+          run = s1;
+        } else {
+          Q.arr[s1] = more;
+          more = s1;
+        }
+      }
+      if (run == RB_NONE && more != RB_NONE) {
+        run = more;
+        more = Q.arr[run];
+      }
     }
-    uint64_t *tmp = cur;
-    cur = nxt;
-    nxt = tmp;
-    __syncthreads();
-    if (tid == 0) s_n = s_next;
-    __syncthreads();
   }
-  if (tid == 0) {
-    cnt[0] = 0;
-    cnt[1] = 0;
-    cnt[3] = err[0];
-    if (s_res) atomicAdd(n_res, s_res);
-    if (cum) {
-      cum[0] += (unsigned long long)n0;
-      cum[1] += s_res;
-    }
+  for (int d = 32; d >= 1; d >>= 1) done += (uint32_t)__shfl_xor((int)done, d, 64);
+  if (rb_lane() == 0 && done) {
+    atomicAdd(n_res, (unsigned long long)done);
+    if (cum) atomicAdd(&cum[1], (unsigned long long)done);
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    Q.cnt[3] = Q.err[0];
+    if (cum) cum[0] += (unsigned long long)n;
   }
 }
 
@@ -603,7 +555,7 @@ hipError_t launch_coll_prep(rb_ctx *c, const double *radius) {
   if (n == 0) return hipSuccess;
   const unsigned grid = std::min(rb_div_up(n, 1024), 128u);
   hipLaunchKernelGGL(k_coll_rmax, dim3(grid), dim3(256), 0, c->stream, radius, c->d_orig[0],
-                     c->d_starts, c->d_nlive, c->P, n, c->d_cmax);
+                     c->d_starts, c->d_nlive, c->P, n, c->d_cmax, c->d_chead);
   CollNode *cells = reinterpret_cast<CollNode *>(c->d_cgeo);
   hipLaunchKernelGGL(k_coll_geom, dim3(rb_div_up(c->node_cap, 256)), dim3(256), 0, c->stream,
                      c->d_px[0][0], c->d_px[0][1], c->d_px[0][2], c->d_patch, c->d_starts, c->P,
@@ -624,36 +576,19 @@ hipError_t launch_coll_detect(rb_ctx *c, const double *radius, double t) {
                      c->d_witems_mid, c->d_gctr, c->cap, c->d_px[0][0], c->d_px[0][1],
                      c->d_px[0][2], c->d_orig[0], radius, c->d_patch, c->d_starts, c->d_nlive,
                      c->d_root, cells, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,
-                     c->p.omega, t, c->d_cmax, c->d_cq[0], (uint32_t)c->cq_cap, c->d_ccnt,
-                     c->d_err, nullptr, nullptr, nullptr, nullptr, 0, c->P);
+                     c->p.omega, t, c->d_cmax, rb_coll_queue(c), c->d_err,
+                     nullptr, nullptr, nullptr, nullptr, 0, c->P);
   return hipGetLastError();
 }
 
-// One round over list `a` (count d_ccnt[a]) into list 1 - a.
-hipError_t launch_coll_rounds1(rb_ctx *c, int a, const rb_particles *pp, double t, double eps,
-                               uint64_t seed, uint32_t *save) {
-  hipLaunchKernelGGL(k_coll_rounds1, dim3(1), dim3(1024), 0, c->stream, c->d_cq[0],
-                     c->d_cq[1], c->d_ccnt, a, save, (uint32_t)c->cq_cap, seed, c->d_cbest,
-                     pp->x, pp->y, pp->z, pp->vx, pp->vy, pp->vz, pp->m, c->d_patch,
-                     c->d_starts, c->P, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,
-                     c->p.omega, t, eps, c->d_cres, c->d_err, nullptr, nullptr, nullptr,
+// the queue that the search left, on the caller's arrays
+hipError_t launch_coll_run(rb_ctx *c, const rb_particles *pp, double t, double eps,
+                           uint64_t seed) {
+  hipLaunchKernelGGL(k_coll_run, dim3(CR_BLOCKS), dim3(CR_THREADS), 0, c->stream, rb_coll_queue(c),
+                     c->d_csucc, seed, pp->x, pp->y, pp->z, pp->vx, pp->vy, pp->vz, pp->m,
+                     c->d_patch, c->d_starts, c->P, c->p.n_ghost[0], c->p.n_ghost[1],
+                     c->p.boundary, c->p.omega, t, eps, c->d_cres, nullptr, nullptr, nullptr,
                      nullptr, 0, nullptr);
-  return hipGetLastError();
-}
-
-hipError_t launch_coll_round(rb_ctx *c, int a, const rb_particles *pp, double t, double eps,
-                             uint64_t seed, uint32_t *save) {
-  uint32_t *cnt = c->d_ccnt + a, *next_cnt = c->d_ccnt + (1 - a);
-  const uint32_t qcap = (uint32_t)c->cq_cap;
-  hipLaunchKernelGGL(k_coll_min, dim3(CR_GRID), dim3(256), 0, c->stream, c->d_cq[a], cnt,
-                     next_cnt, save, qcap, seed, c->d_cbest);
-  hipLaunchKernelGGL(k_coll_resolve, dim3(CR_GRID), dim3(256), 0, c->stream, c->d_cq[a], cnt,
-                     qcap, c->d_cq[1 - a], next_cnt, seed, c->d_cbest, pp->x, pp->y, pp->z,
-                     pp->vx, pp->vy, pp->vz, pp->m, c->d_patch, c->d_starts, c->P,
-                     c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary, c->p.omega, t, eps,
-                     c->d_cres);
-  hipLaunchKernelGGL(k_coll_reset, dim3(CR_GRID), dim3(256), 0, c->stream, c->d_cq[a], cnt,
-                     qcap, c->d_cbest);
   return hipGetLastError();
 }
 
@@ -685,21 +620,20 @@ hipError_t launch_coll_step_search(rb_ctx *c, int buf, int slot) {
                      c->d_witems_mid, c->d_gctr, c->cap, c->d_px[buf][0], c->d_px[buf][1],
                      c->d_px[buf][2], c->d_orig[buf], c->coll_R, c->d_patch, c->d_starts,
                      c->d_nlive, c->d_root, cells, c->p.n_ghost[0], c->p.n_ghost[1],
-                     c->p.boundary, c->p.omega, 0.0, c->d_cmax, c->d_cq[0],
-                     (uint32_t)c->cq_cap, c->d_ccnt, c->d_err, c->d_cwrap,
+                     c->p.boundary, c->p.omega, 0.0, c->d_cmax, rb_coll_queue(c), c->d_err,
+                     c->d_cwrap,
                      reinterpret_cast<const unsigned long long *>(c->d_ccnt + 8), c->d_sched,
                      c->d_ctr, slot, c->P);
   return hipGetLastError();
 }
 
-// then every round of the queue, on the sorted state
-hipError_t launch_coll_step_rounds(rb_ctx *c, int buf, int slot) {
+// then the queue, on the sorted state
+hipError_t launch_coll_step_run(rb_ctx *c, int buf, int slot) {
   double *const *b = c->d_px[buf];
-  hipLaunchKernelGGL(k_coll_rounds1, dim3(1), dim3(1024), 0, c->stream, c->d_cq[0],
-                     c->d_cq[1], c->d_ccnt, 0, c->d_ccnt + 2, (uint32_t)c->cq_cap, 0ull,
-                     c->d_cbest, b[0], b[1], b[2], b[3], b[4], b[5], b[6], c->d_patch,
+  hipLaunchKernelGGL(k_coll_run, dim3(CR_BLOCKS), dim3(CR_THREADS), 0, c->stream, rb_coll_queue(c),
+                     c->d_csucc, 0ull, b[0], b[1], b[2], b[3], b[4], b[5], b[6], c->d_patch,
                      c->d_starts, c->P, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,
-                     c->p.omega, 0.0, c->coll_eps, c->d_cres, c->d_err, c->d_cinv,
+                     c->p.omega, 0.0, c->coll_eps, c->d_cres, c->d_cinv,
                      reinterpret_cast<const uint64_t *>(c->d_ctr + 4), c->d_sched, c->d_ctr,
                      slot, reinterpret_cast<unsigned long long *>(c->d_ccnt + 10));
   return hipGetLastError();

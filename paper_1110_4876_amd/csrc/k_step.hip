@@ -149,7 +149,7 @@ __global__ __launch_bounds__(256) void k_post(
     uint32_t *__restrict__ bctl, uint16_t *__restrict__ wrap,
     unsigned long long *__restrict__ disp, const uint32_t *__restrict__ orig,
     const double *__restrict__ radius, uint32_t *__restrict__ inv,
-    unsigned long long *__restrict__ rmax) {
+    unsigned long long *__restrict__ rmax, uint32_t *__restrict__ head) {
   const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t k = ctr[slot], nsteps = ctr[2];
   // the next step reads its index from the other slot; its keep-the-tree
@@ -164,9 +164,11 @@ __global__ __launch_bounds__(256) void k_post(
   const bool has_next = k + 1 < nsteps && mode != 1;
   PState q{bx[s], by[s], bz[s], bvx[s], bvy[s], bvz[s]};
   const bool live = (s - pi.start) < nlive[p];
-  if (mode == 1) {  // for the search and the rounds: caller index -> slot, R_max
+  if (mode == 1) {  // for the search and the queue: caller index -> slot, R_max,
+                    // empty lists of pairs
     const uint32_t o = orig[s];
     inv[o] = s;
+    head[s] = RB_NONE;
     if (live) {
       const double v = radius[o];
       rad = v > 0.0 ? v : 0.0;  // (a NaN radius is never larger)
@@ -260,7 +262,7 @@ hipError_t launch_post(rb_ctx *c, int buf, int slot, int mode) {
       c->d_key[0], c->d_idx[0], c->d_err, c->sort_small ? c->d_bcnt : nullptr, c->d_bctl,  \
       c->d_cwrap,                                                                          \
       c->d_ccnt ? reinterpret_cast<unsigned long long *>(c->d_ccnt + 8) : nullptr,         \
-      c->d_orig[buf], c->coll_R, c->d_cinv, c->d_cmax
+      c->d_orig[buf], c->coll_R, c->d_cinv, c->d_cmax, c->d_chead
   const dim3 g(rb_div_up(n, 256)), bl(256);
   if (mode == 1) hipLaunchKernelGGL(k_post<1>, g, bl, 0, c->stream, RB_POST_ARGS);
   else if (mode == 2) hipLaunchKernelGGL(k_post<2>, g, bl, 0, c->stream, RB_POST_ARGS);

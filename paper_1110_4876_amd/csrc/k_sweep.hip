@@ -106,10 +106,12 @@ __global__ __launch_bounds__(256) void k_sw_keys(
     const double *__restrict__ R, const PatchInfo *__restrict__ patch, uint32_t n,
     int open_xy, int phi, double dt, SweepGrid g, uint64_t *__restrict__ key,
     uint32_t *__restrict__ idx, uint32_t *__restrict__ err, uint32_t *__restrict__ bcnt,
-    uint32_t *__restrict__ bctl, unsigned long long *__restrict__ lmax) {
+    uint32_t *__restrict__ bctl, unsigned long long *__restrict__ lmax,
+    uint32_t *__restrict__ head) {
   const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
   double len = 0.0;
   if (s < n) {
+    head[s] = RB_NONE;  // the particle's list of pairs
     const PatchInfo pi = patch[0];
     const double xs = x[s], ys = y[s], zs = z[s];
     uint32_t q;
@@ -226,9 +228,7 @@ __device__ __forceinline__ void rb_sw_test(const SwRec &E, const SwRec &F, int c
                                            int ngy, int boundary, double W, double sh,
                                            double omega, double dt,
                                            uint64_t (&mine)[RB_COLL_LOCAL], uint32_t &nm,
-                                           uint64_t *__restrict__ queue, uint32_t qcap,
-                                           uint32_t *__restrict__ qcnt,
-                                           uint32_t *__restrict__ err) {
+                                           const CollQueue &Q) {
   const bool e_is_i = E.p < F.p;
   const SwRec &I = e_is_i ? E : F;
   const SwRec &J = e_is_i ? F : E;
@@ -254,8 +254,7 @@ __device__ __forceinline__ void rb_sw_test(const SwRec &E, const SwRec &F, int c
     const double u2 = J.vz - I.vz;
     if (rb_sw_meets(d0, d1, d2, u0, u1, u2, sum, dt)) {
       const int k = (boundary == RB_OPEN) ? 0 : (ix + ngx) * (2 * ngy + 1) + (iy + ngy);
-      rb_coll_keep(((uint64_t)I.p << 35) | ((uint64_t)J.p << 7) | (uint64_t)k, mine, nm,
-                   queue, qcap, qcnt, err);
+      rb_coll_keep(((uint64_t)I.p << 35) | ((uint64_t)J.p << 7) | (uint64_t)k, mine, nm, Q);
     }
   }
 }
@@ -277,8 +276,7 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
     const double *__restrict__ sR, const double *__restrict__ shi,
     const uint32_t *__restrict__ nlive, const PatchInfo *__restrict__ patch, int ngx, int ngy,
     int boundary, double omega, double t, double dt, SweepGrid g,
-    const unsigned long long *__restrict__ lmax_bits, uint64_t *__restrict__ queue,
-    uint32_t qcap, uint32_t *__restrict__ qcnt, uint32_t *__restrict__ err) {
+    const unsigned long long *__restrict__ lmax_bits, CollQueue Q) {
   __shared__ uint64_t c_key[64];
   __shared__ double c_x[64], c_y[64], c_z[64], c_vx[64], c_vy[64], c_vz[64], c_R[64];
   __shared__ uint32_t c_p[64];
@@ -328,8 +326,7 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
           F.vx = c_vx[q]; F.vy = c_vy[q]; F.vz = c_vz[q];
           F.R = c_R[q]; F.p = c_p[q];
           if (F.p != E.p)
-            rb_sw_test(E, F, 0, ngx, ngy, boundary, W, sh, omega, dt, mine, nm, queue, qcap,
-                       qcnt, err);
+            rb_sw_test(E, F, 0, ngx, ngy, boundary, W, sh, omega, dt, mine, nm, Q);
         }
       }
       // (every lane reaches this barrier: the loop bounds are uniform)
@@ -355,21 +352,11 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
         F.x = sx[f]; F.y = sy[f]; F.z = sz[f];
         F.vx = svx[f]; F.vy = svy[f]; F.vz = svz[f];
         F.R = sR[f]; F.p = pf;
-        rb_sw_test(E, F, c, ngx, ngy, boundary, W, sh, omega, dt, mine, nm, queue, qcap,
-                   qcnt, err);
+        rb_sw_test(E, F, c, ngx, ngy, boundary, W, sh, omega, dt, mine, nm, Q);
       }
     }
   }
-  // the rest: one atomic per wave
-  const uint32_t incl = rb_wave_incl_scan(nm);
-  const uint32_t tot = __shfl(incl, 63, 64);
-  uint32_t qbase = 0;
-  if (rb_lane() == 63 && tot) qbase = atomicAdd(qcnt, tot);
-  qbase = __shfl(qbase, 63, 64);
-  const uint32_t at = qbase + incl - nm;
-  for (uint32_t q = 0; q < nm; ++q)
-    if (at + q < qcap) queue[at + q] = mine[q];
-  if (nm && at + nm > qcap) atomicOr(err, RB_ERR_COLL);
+  rb_coll_rest(mine, nm, Q);
 }
 
 // The azimuthal sweep: one wave per SW_EPB consecutive sorted intervals,
@@ -387,8 +374,7 @@ __global__ __launch_bounds__(64) void k_sw_pairs_phi(
     const double *__restrict__ svy, const double *__restrict__ svz,
     const double *__restrict__ sR, const uint32_t *__restrict__ nlive,
     const PatchInfo *__restrict__ patch, double dt, SweepGrid g,
-    const unsigned long long *__restrict__ lmax_bits, uint64_t *__restrict__ queue,
-    uint32_t qcap, uint32_t *__restrict__ qcnt, uint32_t *__restrict__ err) {
+    const unsigned long long *__restrict__ lmax_bits, CollQueue Q) {
   const uint32_t lane = threadIdx.x;
   const uint32_t sub = lane % SW_SUB;
   const uint32_t r = blockIdx.x * SW_EPB + lane / SW_SUB;
@@ -424,20 +410,11 @@ __global__ __launch_bounds__(64) void k_sw_pairs_phi(
         F.x = sx[f]; F.y = sy[f]; F.z = sz[f];
         F.vx = svx[f]; F.vy = svy[f]; F.vz = svz[f];
         F.R = sR[f]; F.p = pf;
-        rb_sw_test(E, F, 0, 0, 0, RB_OPEN, W, 0.0, 0.0, dt, mine, nm, queue, qcap, qcnt, err);
+        rb_sw_test(E, F, 0, 0, 0, RB_OPEN, W, 0.0, 0.0, dt, mine, nm, Q);
       }
     }
   }
-  // the rest: one atomic per wave
-  const uint32_t incl = rb_wave_incl_scan(nm);
-  const uint32_t tot = __shfl(incl, 63, 64);
-  uint32_t qbase = 0;
-  if (rb_lane() == 63 && tot) qbase = atomicAdd(qcnt, tot);
-  qbase = __shfl(qbase, 63, 64);
-  const uint32_t at = qbase + incl - nm;
-  for (uint32_t q = 0; q < nm; ++q)
-    if (at + q < qcap) queue[at + q] = mine[q];
-  if (nm && at + nm > qcap) atomicOr(err, RB_ERR_COLL);
+  rb_coll_rest(mine, nm, Q);
 }
 
 static SweepGrid sweep_grid(const rb_ctx *c, int phi) {
@@ -459,7 +436,7 @@ hipError_t launch_sweep_keys(rb_ctx *c, const rb_particles *pp, const double *ra
                      pp->y, pp->z, pp->vx, pp->vy, radius, c->d_patch, n,
                      c->p.boundary == RB_OPEN ? 1 : 0, phi, dt, sweep_grid(c, phi), c->d_key[0],
                      c->d_idx[0], c->d_err, c->sort_small ? c->d_bcnt : nullptr, c->d_bctl,
-                     c->d_cmax);
+                     c->d_cmax, c->d_chead);
   return hipGetLastError();
 }
 
@@ -476,13 +453,12 @@ hipError_t launch_sweep_pairs(rb_ctx *c, const rb_particles *pp, const double *r
     hipLaunchKernelGGL(k_sw_pairs_phi, dim3(rb_div_up(n, SW_EPB)), dim3(64), 0, c->stream,
                        c->d_key[0], c->d_orig[0], s[0], s[1], s[2], s[3], s[4], s[5],
                        c->d_swR, c->d_nlive, c->d_patch, dt, sweep_grid(c, 1), c->d_cmax,
-                       c->d_cq[0], (uint32_t)c->cq_cap, c->d_ccnt, c->d_err);
+                       rb_coll_queue(c));
     return hipGetLastError();
   }
   hipLaunchKernelGGL(k_sw_pairs, dim3(rb_div_up(n, SW_EPB)), dim3(64), 0, c->stream,
                      c->d_key[0], c->d_orig[0], s[0], s[1], s[2], s[3], s[4], s[5], c->d_swR,
                      c->d_swhi, c->d_nlive, c->d_patch, c->p.n_ghost[0], c->p.n_ghost[1],
-                     c->p.boundary, c->p.omega, t, dt, sweep_grid(c, 0), c->d_cmax, c->d_cq[0],
-                     (uint32_t)c->cq_cap, c->d_ccnt, c->d_err);
+                     c->p.boundary, c->p.omega, t, dt, sweep_grid(c, 0), c->d_cmax, rb_coll_queue(c));
   return hipGetLastError();
 }

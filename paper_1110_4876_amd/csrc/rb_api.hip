@@ -671,7 +671,7 @@ int step_kernels(rb_ctx *c, int src) {
     // next step's first drift
     RB_PHASE(PH_POST, launch_post(c, dst, src, 1));
     RB_PHASE(PH_CSEARCH, launch_coll_step_search(c, dst, src));
-    RB_PHASE(PH_COLLIDE, launch_coll_step_rounds(c, dst, src));
+    RB_PHASE(PH_COLLIDE, launch_coll_step_run(c, dst, src));
     RB_PHASE(PH_POST, launch_post(c, dst, src, 2));
   } else {
     RB_PHASE(PH_POST, launch_post(c, dst, src));
@@ -1012,17 +1012,20 @@ int rb_batch_step(rb_ctx *c, rb_particles *p, double t, double dt, int32_t nstep
 // collision buffers, allocated by the first collision call of a context
 static int coll_alloc(rb_ctx *c) {
   if (c->cap >= (1ull << 28)) return fail(RB_EUNSUPPORTED, "pair codes need n < 2^28");
-  if (c->d_cq[0]) return RB_OK;
-  c->cq_cap = 8 * c->cap + 1024;
-  RB_TRY(dalloc(c, &c->d_cq[0], c->cq_cap));
-  RB_TRY(dalloc(c, &c->d_cq[1], c->cq_cap));
+  if (c->h_cpin) return RB_OK;
+  // (list nodes are numbered 2 q and 2 q + 1 in 32 bits)
+  c->cq_cap = std::min<uint64_t>(8 * c->cap + 1024, 0x7FFFFFFEull);
+  // one block, freed as one: [codes | links | successors | arrivals | heads]
+  RB_TRY(dalloc(c, &c->d_cq, c->cq_cap + (5 * c->cq_cap + c->cap + 1) / 2));
+  c->d_clink = reinterpret_cast<uint32_t *>(c->d_cq + c->cq_cap);
+  c->d_csucc = c->d_clink + 2 * c->cq_cap;
+  c->d_carr = c->d_csucc + 2 * c->cq_cap;
+  c->d_chead = c->d_carr + c->cq_cap;
   RB_TRY(dalloc(c, &c->d_ccnt, 16));
   c->d_cmax = reinterpret_cast<unsigned long long *>(c->d_ccnt + 4);
   c->d_cres = reinterpret_cast<unsigned long long *>(c->d_ccnt + 6);
-  RB_HIP(hipHostMalloc((void **)&c->h_cpin, 64, hipHostMallocDefault));
   RB_HIP(hipMemsetAsync(c->d_ccnt, 0, 64, c->stream));
-  RB_TRY(dalloc(c, &c->d_cbest, c->cap));
-  RB_HIP(hipMemsetAsync(c->d_cbest, 0xFF, 8 * c->cap, c->stream));
+  RB_HIP(hipHostMalloc((void **)&c->h_cpin, 64, hipHostMallocDefault));
   return RB_OK;
 }
 
@@ -1039,43 +1042,27 @@ static int coll_check_args(rb_ctx *c, rb_particles *p, const double *radius, dou
   return RB_OK;
 }
 
-// The queue the search left in list 0: optional copy of the codes, then the
-// resolution rounds, each resolving at least the collision first in the
-// whole queue.  A short queue is resolved entirely by one workgroup; a long
-// one first goes through batches of multi-workgroup rounds (whose kernels
-// read the list's length on the device) until it is short.  The first launch
-// saves the number of detected pairs in the third count.
+// The queue the search left: optional copy of the codes, then every collision
+// in one launch; the counts and the error word come back in one copy.
 static int coll_resolve(rb_ctx *c, rb_particles *p, double t, double epsilon, uint64_t seed,
                         uint64_t *codes, int64_t codes_cap, int64_t *n_pairs,
                         int64_t *n_resolved) {
-  if (codes_cap > 0) {  // the detected pairs, before the rounds reuse their list
+  if (codes_cap > 0) {
     uint32_t cnt = 0;
     RB_HIP(hipMemcpyAsync(&cnt, c->d_ccnt, 4, hipMemcpyDeviceToHost, c->stream));
     RB_HIP(hipStreamSynchronize(c->stream));
     RB_TRY(report_device_errors(c));
     if (cnt > 0)
-      RB_HIP(hipMemcpy(codes, c->d_cq[0], 8 * (size_t)std::min<int64_t>(cnt, codes_cap),
+      RB_HIP(hipMemcpy(codes, c->d_cq, 8 * (size_t)std::min<int64_t>(cnt, codes_cap),
                        hipMemcpyDeviceToHost));
   }
-  int a = 0;
-  uint64_t rounds = 0;
   const uint32_t *h_cnt = c->h_cpin;
-  RB_PHASE(PH_COLLIDE, launch_coll_rounds1(c, a, p, t, epsilon, seed, c->d_ccnt + 2));
-  for (;;) {
-    RB_HIP(hipMemcpyAsync(c->h_cpin, c->d_ccnt, 32, hipMemcpyDeviceToHost, c->stream));
-    RB_HIP(hipStreamSynchronize(c->stream));
-    if (h_cnt[3]) return report_device_errors(c);  // (a full queue ends the call here)
-    if (h_cnt[a] == 0) break;
-    if (rounds > h_cnt[2])
-      return fail(RB_EHIP, "collision rounds did not finish (internal error)");
-    for (int r = 0; r < 4; ++r, ++rounds) {
-      RB_PHASE(PH_COLLIDE, launch_coll_round(c, a, p, t, epsilon, seed, nullptr));
-      a = 1 - a;
-    }
-    RB_PHASE(PH_COLLIDE, launch_coll_rounds1(c, a, p, t, epsilon, seed, nullptr));
-  }
+  RB_PHASE(PH_COLLIDE, launch_coll_run(c, p, t, epsilon, seed));
+  RB_HIP(hipMemcpyAsync(c->h_cpin, c->d_ccnt, 32, hipMemcpyDeviceToHost, c->stream));
+  RB_HIP(hipStreamSynchronize(c->stream));
+  if (h_cnt[3]) return report_device_errors(c);  // (a full queue ends the call here)
   RB_TRY(mark(c, PH_TOTAL, false));
-  if (n_pairs) *n_pairs = (int64_t)h_cnt[2];
+  if (n_pairs) *n_pairs = (int64_t)h_cnt[0];
   if (n_resolved) {
     unsigned long long res;
     memcpy(&res, h_cnt + 6, 8);

@@ -138,19 +138,20 @@ struct rb_ctx {
   uint32_t *d_large = nullptr;      // nodes with more than G particles, by level
   uint32_t *d_bottom = nullptr;     // those without such a child (not in d_large)
   uint32_t *d_large_cnt = nullptr;  // per-level counts, then the bottom count
-  // collisions (allocated by the first rb_collide): two code lists (the
-  // detected pairs, then the survivors of each resolution round), their
-  // counts, each particle's smallest pending queue key, R_max, resolved
+  // collisions (allocated by the first rb_collide): the queue of pair codes,
+  // each pair's place in its two particles' lists, its arrivals and its
+  // successors (rb_coll_queue), the particles' list heads, R_max, resolved
   // collisions, the cells' centres and links
-  uint64_t *d_cq[2] = {nullptr, nullptr};
+  uint64_t *d_cq = nullptr;
   uint64_t cq_cap = 0;
-  // one 64-byte block [list counts 0, 1 | detected pairs | copy of the
+  uint32_t *d_clink = nullptr, *d_carr = nullptr, *d_csucc = nullptr;
+  uint32_t *d_chead = nullptr;
+  // one 64-byte block [detected pairs | - | - | copy of the
   // error word | R_max bits (2 words) | resolved (2 words) | largest
   // displacement bits (2 words) | collisions of rb_step since they were
   // last read: pairs (2 words), resolved (2 words) | -], its first 40 bytes
   // cleared once per call or step and read back in one copy
   uint32_t *d_ccnt = nullptr;
-  unsigned long long *d_cbest = nullptr;
   unsigned long long *d_cmax = nullptr;  // = d_ccnt + 4
   unsigned long long *d_cres = nullptr;  // = d_ccnt + 6
   uint32_t *h_cpin = nullptr;            // pinned host copy of the block (16 words)
@@ -228,19 +229,59 @@ __device__ __forceinline__ void rb_coll_image(int k, int ngx, int ngy, int bound
   rb_coll_image_xy(k / ny - ngx, k % ny - ngy, boundary, W, sh, omega, ox, oy, wy);
 }
 
+// The collision queue: detected pairs in any order, and every particle's list
+// of its pairs.  Pair q is node 2 q of its lower particle's list and node
+// 2 q + 1 of its higher one's; link[node] is the next node of the same list,
+// head[particle] its first (RB_NONE at the end).
+struct CollQueue {
+  uint64_t *code;
+  uint32_t *cnt, *link, *head, *arr, *err;
+  uint32_t cap;
+};
+
+__device__ __forceinline__ uint32_t rb_coll_i(uint64_t code) { return (uint32_t)(code >> 35); }
+__device__ __forceinline__ uint32_t rb_coll_j(uint64_t code) {
+  return (uint32_t)((code >> 7) & ((1ull << 28) - 1ull));
+}
+
+// place `at` of the queue takes a pair, which joins its particles' lists
+__device__ __forceinline__ void rb_coll_put(const CollQueue &Q, uint32_t at, uint64_t code) {
+  if (at >= Q.cap) return;
+  Q.code[at] = code;
+  Q.arr[at] = 0u;
+  const uint32_t a = atomicExch(&Q.head[rb_coll_i(code)], 2u * at);
+  const uint32_t b = atomicExch(&Q.head[rb_coll_j(code)], 2u * at + 1u);
+  Q.link[2 * (size_t)at] = a;
+  Q.link[2 * (size_t)at + 1] = b;
+}
+
 // queue a pair from the lane's local list, writing the list out when full
 __device__ __forceinline__ void rb_coll_keep(uint64_t code, uint64_t (&mine)[RB_COLL_LOCAL],
-                                             uint32_t &nm, uint64_t *__restrict__ queue,
-                                             uint32_t qcap, uint32_t *__restrict__ qcnt,
-                                             uint32_t *__restrict__ err) {
+                                             uint32_t &nm, const CollQueue &Q) {
   if (nm == RB_COLL_LOCAL) {
-    const uint32_t at = atomicAdd(qcnt, (uint32_t)nm);
-    for (uint32_t q = 0; q < nm; ++q)
-      if (at + q < qcap) queue[at + q] = mine[q];
-    if (at + nm > qcap) atomicOr(err, RB_ERR_COLL);
+    const uint32_t at = atomicAdd(Q.cnt, (uint32_t)nm);
+    for (uint32_t q = 0; q < nm; ++q) rb_coll_put(Q, at + q, mine[q]);
+    if (at + nm > Q.cap) atomicOr(Q.err, RB_ERR_COLL);
     nm = 0;
   }
   mine[nm++] = code;
+}
+
+// the lanes' remaining pairs, with one atomic per wave
+__device__ __forceinline__ void rb_coll_rest(const uint64_t (&mine)[RB_COLL_LOCAL], uint32_t nm,
+                                             const CollQueue &Q) {
+  const uint32_t incl = rb_wave_incl_scan(nm);
+  const uint32_t tot = __shfl(incl, 63, 64);
+  uint32_t qbase = 0;
+  if (rb_lane() == 63 && tot) qbase = atomicAdd(Q.cnt, tot);
+  qbase = __shfl(qbase, 63, 64);
+  const uint32_t at = qbase + incl - nm;
+  for (uint32_t q = 0; q < nm; ++q) rb_coll_put(Q, at + q, mine[q]);
+  if (nm && at + nm > Q.cap) atomicOr(Q.err, RB_ERR_COLL);
+}
+
+inline CollQueue rb_coll_queue(rb_ctx *c) {
+  return {c->d_cq, c->d_ccnt, c->d_clink, c->d_chead, c->d_carr, c->d_err, (uint32_t)c->cq_cap};
 }
 
 // ---- launchers (each returns hipSuccess or the launch error) ----
@@ -255,12 +296,10 @@ hipError_t launch_sweep_pairs(rb_ctx *c, const rb_particles *pp, const double *r
 hipError_t launch_coll_prep(rb_ctx *c, const double *radius);
 hipError_t launch_coll_step_prep(rb_ctx *c, int buf);
 hipError_t launch_coll_step_search(rb_ctx *c, int buf, int slot);
-hipError_t launch_coll_step_rounds(rb_ctx *c, int buf, int slot);
+hipError_t launch_coll_step_run(rb_ctx *c, int buf, int slot);
 hipError_t launch_coll_detect(rb_ctx *c, const double *radius, double t);
-hipError_t launch_coll_rounds1(rb_ctx *c, int a, const rb_particles *pp, double t, double eps,
-                               uint64_t seed, uint32_t *save);
-hipError_t launch_coll_round(rb_ctx *c, int a, const rb_particles *pp, double t, double eps,
-                             uint64_t seed, uint32_t *save);
+hipError_t launch_coll_run(rb_ctx *c, const rb_particles *pp, double t, double eps,
+                           uint64_t seed);
 hipError_t launch_bsort(rb_ctx *c);
 hipError_t launch_permute_state(rb_ctx *c, int src, int dst);
 hipError_t launch_permute_gravity(rb_ctx *c, const double *x, const double *y,

@@ -182,3 +182,26 @@ def test_c1_full_size_after_steps(orc, steps):
     np.testing.assert_array_equal(np.sort(codes[:npair]), np.sort(oc))
     for k in ("vx", "vy", "vz"):
         assert np.abs(got[k] - ost[k]).max() <= 1e-13 * np.abs(ost[k]).max(), k
+
+
+@pytest.mark.parametrize("n,pile", [(3000, 150), (20000, 380), (70, 33)])
+def test_pile_up_long_chains(orc, n, pile):
+    # `pile` particles all overlapping each other (chains of that many
+    # dependent collisions at every one of them; 11,175, 72,010 and 528 pairs:
+    # fewer than the queue's launch has threads, and more) among particles
+    # that touch nothing.  The collisions are the oracle's, in its order and
+    # with its arithmetic, so the usual bound applies.
+    rng = np.random.default_rng(n)
+    W = 64.0
+    x = rng.uniform(-W / 2, W / 2, (n, 3))
+    x[:pile] = 7.0 + rng.uniform(0.0, 0.01, (pile, 3))
+    x[pile:][np.linalg.norm(x[pile:] - 7.0, axis=1) < 1.0] += 2.0
+    order = rng.permutation(n)
+    x = x[order]
+    v = rng.normal(size=(n, 3))
+    params = inputs.base_params(G=1.0, b=0.0, W=W, x0=(-W / 2,) * 3)
+    pr = inputs.Problem(*(np.ascontiguousarray(a) for a in (*x.T, *v.T)),
+                        rng.uniform(0.5, 2.0, n), params, n, 0.1)
+    R = np.where(order < pile, 0.02, 1e-6)
+    npair, nres = _compare(orc, pr, R, 0.0, 0.7, 21)
+    assert npair == pile * (pile - 1) // 2 and nres > pile // 2

@@ -297,6 +297,7 @@ int init_ctx(rb_ctx *c, const rb_params *p, uint32_t P, const int64_t *off, cons
   if (c->node_cap > 0xFFFFFFF0ull) return fail(RB_ECAPACITY, "node capacity beyond 32-bit indices");
   const uint64_t max_tiles = cap / RB_TILE_MIN + P + 1;
   const uint64_t max_items = cap / 16 + 2 * (uint64_t)P + 8;
+  const uint64_t cap_pad = (cap + 31) / 32 * 32;  // (each array starts on a 256-byte line)
   RB_TRY(dalloc(c, &c->d_patch, P));
   RB_TRY(dalloc(c, &c->d_starts, P + 1));
   RB_TRY(dalloc(c, &c->d_nlive, P));
@@ -308,7 +309,10 @@ int init_ctx(rb_ctx *c, const rb_params *p, uint32_t P, const int64_t *off, cons
   for (int b = 0; b < 2; ++b) {
     RB_TRY(dalloc(c, &c->d_key[b], cap));
     RB_TRY(dalloc(c, &c->d_idx[b], cap));
-    for (int f = 0; f < 7; ++f) RB_TRY(dalloc(c, &c->d_px[b][f], cap));
+    // eight doubles per slot in one block: seven arrays, or one 64-byte record
+    // per particle (StateRec)
+    RB_TRY(dalloc(c, &c->d_px[b][0], 8 * cap_pad));
+    for (int f = 1; f < 7; ++f) c->d_px[b][f] = c->d_px[b][0] + f * cap_pad;
     RB_TRY(dalloc(c, &c->d_orig[b], cap));
   }
   // sort tiles: at least 256 slots each, at most one partial tile per patch

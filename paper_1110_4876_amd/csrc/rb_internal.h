@@ -32,6 +32,13 @@ __device__ __forceinline__ WalkItem rb_walk_item(const WalkItem *__restrict__ it
   return items[(uint32_t)cap - 1u - (gi - n_big - n_mid)];
 }
 
+// A particle's whole state in one 64-byte line, in the caller's order: between
+// the caller's arrays and Morton order the rows move once in this form, so
+// that a random access costs one line and not one per array.
+struct __align__(64) StateRec {
+  double2 xy, zvx, vyz, m0;  // x y | z vx | vy vz | m -
+};
+
 // Control block of the 64-part FP64 walk's dispatch order.  Before each
 // walk the listing kernel lists the units whose last cost reached the
 // threshold, under the launch number `epoch`, and histograms the costs (by
@@ -99,8 +106,9 @@ struct rb_ctx {
   uint2 *d_bseg = nullptr;      // segments (first slot, patch)
   uint32_t *d_bctl = nullptr;   // [segments, segments taken]
 
-  // particles in sorted order (ping-pong for rb_step)
-  double *d_px[2][7] = {};          // x y z vx vy vz m
+  // particles in sorted order (ping-pong for rb_step): x y z vx vy vz m, or
+  // records in the caller's order (StateRec) on the way in and out
+  double *d_px[2][7] = {};
   uint32_t *d_orig[2] = {nullptr, nullptr};
   double *d_msrc = nullptr;         // source mass of sorted slots
   int cur = 0;                      // buffer holding the sorted state

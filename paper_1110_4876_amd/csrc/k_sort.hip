@@ -1,39 +1,33 @@
 // k_sort.hip -- stable LSD radix sort of (Morton key, slot) pairs inside every
 // patch, for large systems: 8 passes of 8-bit digits over the 64-bit keys,
-// one launch per pass.  (Small systems use the bucket sort of k_bsort.hip.)
+// three launches per pass.  (Small systems use the bucket sort of k_bsort.hip.)
 //
-// Digit totals of all eight passes come from one counting launch
-// (k_sort_hist), per patch.  Each pass (k_sort_pass) then works tile by tile
-// (256 threads, 256 * R consecutive slots of one patch) in a single launch:
-//   rank   -- every wave ranks its R rows of 64 keys in order: the lanes
-//             holding the same digit find each other with 8 ballots, a
-//             lane's rank is the count of equal-digit lanes below it plus
-//             the digit's running count of the wave (LDS), so equal keys keep
-//             their order;
-//   prefix -- per digit, the tile publishes its count and looks back over
-//             the preceding tiles of its patch for their published sums
-//             (decoupled look-back: tiles take their index from a device
-//             counter, so every tile waited on is already running);
-//   scatter -- slot = patch start + keys of smaller digits in the patch +
-//             keys of this digit in earlier tiles + earlier waves + rank.
-// Look-back words carry a tag (sort number and pass), so stale words from
-// earlier passes or sorts never match and nothing needs clearing between
-// passes.  A wait that does not end within a bounded number of polls sets an
-// error bit and gives up, so every wave exits.
+// Each pass works on tiles of 256 * R consecutive slots of one patch, by
+// workgroups of 256 threads:
+//   k_sort_count -- every tile's count of every digit;
+//   k_sort_scan  -- per patch and digit, the keys of the digit in earlier
+//                   tiles, and in the patch;
+//   k_sort_pass  -- every wave ranks its R rows of 64 keys in order: the lanes
+//                   holding the same digit find each other with 8 ballots, a
+//                   lane's rank is the count of equal-digit lanes below it
+//                   plus the digit's running count of the wave (LDS), so
+//                   equal keys keep their order.  The tile is put in digit
+//                   order in LDS and written out in runs, after the patch's
+//                   keys of smaller digits and of this digit in earlier tiles.
 // Sentinel keys of removed particles (all ones) sort last.
+//
+// Bound by the launches and their round trips at 10^6 keys, by HBM above: a
+// pass takes 22 us (count 5.4, scan 4.6, ranks and writes 12.4) at 1,000,003
+// keys and 87 us (20, 7, 60; 1.9 times its 24 bytes a key at the copy rate) at
+// 2^23.  One launch per pass with a decoupled look-back -- each tile waiting
+// for its predecessors' published counts and adding them up, 32 words a round
+// trip over 500 to 4,000 tiles -- took 56 and 184 us, and a counting launch
+// for all passes 22 and 119 us.
 #include "rb_internal.h"
 
 #define SORT_BITS 8
 #define SORT_BINS 256
 #define SORT_PASSES 8
-#define LB_AGG 1ull
-#define LB_PREFIX 2ull
-#define LB_POLLS (1u << 22)
-#define LB_WIN 32  // predecessors read per look-back step
-
-__device__ __forceinline__ uint64_t lb_pack(uint32_t tag, uint64_t flag, uint32_t count) {
-  return ((uint64_t)tag << 34) | (flag << 32) | (uint64_t)count;
-}
 
 // lanes of the wave holding the same 8-bit digit
 __device__ __forceinline__ uint64_t wave_match8(uint32_t d, bool valid) {
@@ -47,73 +41,80 @@ __device__ __forceinline__ uint64_t wave_match8(uint32_t d, bool valid) {
   return peers;
 }
 
-// Digit totals of every pass, per patch: block b counts the sort tiles
-// [b T, (b + 1) T) in LDS and adds its non-zero bins to the patch's totals.
-// Each thread loads 8 keys at a time (loads in flight together); a digit
-// that the whole wave shares is added with one LDS atomic.
-// Block 0 also resets the first pass's tile counter.
-__global__ __launch_bounds__(256) void k_sort_hist(
-    const uint64_t *__restrict__ key, const uint32_t *__restrict__ tile_start,
-    const uint32_t *__restrict__ tile_end, const uint32_t *__restrict__ tile_patch,
-    uint32_t n_tiles, uint32_t tiles_per_block, uint32_t P, uint32_t *__restrict__ stot,
-    uint32_t *__restrict__ sctl) {
-  __shared__ uint32_t h[SORT_PASSES * SORT_BINS];
-  const uint32_t tid = threadIdx.x;
-  const uint32_t epoch = sctl[0];
-  uint32_t *tot = stot + (size_t)(epoch & 1u) * P * (SORT_PASSES * SORT_BINS);
-  if (blockIdx.x == 0 && tid == 0) sctl[1] = 0;
-  const uint32_t t0 = blockIdx.x * tiles_per_block;
-  const uint32_t t1 = min(t0 + tiles_per_block, n_tiles);
-  for (uint32_t i = tid; i < SORT_PASSES * SORT_BINS; i += 256) h[i] = 0;
+// Every tile's count of every digit of this pass, digit-major (the scan below
+// reads a digit's counts in a row).
+template <int R>
+__global__ __launch_bounds__(256) void k_sort_count(int pass, const uint64_t *__restrict__ kin,
+                                                    const uint32_t *__restrict__ tile_start,
+                                                    const uint32_t *__restrict__ tile_end,
+                                                    uint32_t n_tiles,
+                                                    uint32_t *__restrict__ cnt) {
+  __shared__ uint32_t h[4][SORT_BINS];
+  const uint32_t tid = threadIdx.x, w = tid >> 6, t = blockIdx.x;
+  const uint32_t s0 = tile_start[t], s1 = tile_end[t];
+  const int shift = SORT_BITS * pass;
+  uint64_t kk[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t s = s0 + r * 256 + tid;
+    kk[r] = s < s1 ? kin[s] : 0ull;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) h[q][tid] = 0;
   __syncthreads();
-  uint32_t cur = (t0 < t1) ? tile_patch[t0] : 0u;
-  auto flush = [&](uint32_t p) {
-    for (uint32_t i = tid; i < SORT_PASSES * SORT_BINS; i += 256) {
-      const uint32_t v = h[i];
-      if (v) atomicAdd(&tot[(size_t)p * (SORT_PASSES * SORT_BINS) + i], v);
-      h[i] = 0;
-    }
-  };
-  for (uint32_t t = t0; t < t1; ++t) {
-    const uint32_t p = tile_patch[t];
-    if (p != cur) {  // uniform: every thread reads the same tile entry
-      __syncthreads();
-      flush(cur);
-      __syncthreads();
-      cur = p;
-    }
-    const uint32_t sa = tile_start[t], s1 = tile_end[t];
-    for (uint32_t sb = sa; sb < s1; sb += 8 * 256) {
-      uint64_t k8[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const uint32_t s = sb + u * 256 + tid;
-        k8[u] = (s < s1) ? key[s] : 0ull;
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const bool valid = sb + u * 256 + tid < s1;
-        const uint64_t vm = __ballot(valid);
-        if (vm == 0) continue;  // uniform over the wave
-        const int first = __ffsll((long long)vm) - 1;
-#pragma unroll
-        for (int q = 0; q < SORT_PASSES; ++q) {
-          const uint32_t d = (uint32_t)(k8[u] >> (SORT_BITS * q)) & (SORT_BINS - 1);
-          // a digit shared by the whole wave (the high digits of nearby
-          // keys): one atomic for all lanes
-          const uint32_t d0 = (uint32_t)__shfl((int)d, first, 64);
-          if (__ballot(valid && d == d0) == vm) {
-            if (rb_lane() == (uint32_t)first)
-              atomicAdd(&h[q * SORT_BINS + d0], (uint32_t)__popcll(vm));
-          } else if (valid) {
-            atomicAdd(&h[q * SORT_BINS + d], 1u);
-          }
-        }
-      }
+  for (int r = 0; r < R; ++r) {
+    const bool valid = s0 + r * 256 + tid < s1;
+    const uint64_t vm = __ballot(valid);
+    if (vm == 0) break;  // uniform over the wave
+    const uint32_t d = (uint32_t)(kk[r] >> shift) & (SORT_BINS - 1);
+    // a digit that the whole wave shares: one LDS atomic
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+    if (__ballot(valid && d == d0) == vm) {
+      if (rb_lane() == 0) atomicAdd(&h[w][d0], (uint32_t)__popcll(vm));
+    } else if (valid) {
+      atomicAdd(&h[w][d], 1u);
     }
   }
   __syncthreads();
-  if (t0 < t1) flush(cur);
+  cnt[(size_t)tid * n_tiles + t] = h[0][tid] + h[1][tid] + h[2][tid] + h[3][tid];
+}
+
+// Block (d, p): the counts of digit d in patch p's tiles become the counts in
+// the tiles before each; their sum goes to tot.
+__global__ __launch_bounds__(256) void k_sort_scan(uint32_t *__restrict__ cnt,
+                                                   const uint32_t *__restrict__ patch_tile0,
+                                                   uint32_t P, uint32_t n_tiles,
+                                                   uint32_t *__restrict__ tot) {
+  __shared__ uint32_t wsum[4];
+  const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const uint32_t d = blockIdx.x;
+  for (uint32_t p = blockIdx.y; p < P; p += gridDim.y) {
+    uint32_t carry = 0;
+    const uint32_t t0 = patch_tile0[p], t1 = patch_tile0[p + 1];
+    uint32_t *row = cnt + (size_t)d * n_tiles;
+    // 1024 tiles per round, four consecutive ones per thread
+    for (uint32_t off = t0; off < t1; off += 1024) {
+      const uint32_t i0 = off + 4 * tid;
+      uint32_t v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = (i0 + k < t1) ? row[i0 + k] : 0u;
+      const uint32_t sum = v[0] + v[1] + v[2] + v[3];
+      const uint32_t incl = rb_wave_incl_scan(sum);
+      if (lane == 63) wsum[w] = incl;
+      __syncthreads();
+      uint32_t ex = carry + incl - sum;
+      for (uint32_t q = 0; q < w; ++q) ex += wsum[q];
+      carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+      __syncthreads();  // (wsum is rewritten)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (i0 + k < t1) row[i0 + k] = ex;
+        ex += v[k];
+      }
+    }
+    if (tid == 0) tot[(size_t)p * SORT_BINS + d] = carry;
+  }
 }
 
 template <int R>
@@ -121,43 +122,22 @@ __global__ __launch_bounds__(256) void k_sort_pass(
     int pass, const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout,
     const uint32_t *__restrict__ tile_start, const uint32_t *__restrict__ tile_end,
-    const uint32_t *__restrict__ tile_patch, const uint32_t *__restrict__ patch_tile0,
-    const uint32_t *__restrict__ starts, uint32_t P, uint32_t n_tiles,
-    uint32_t *__restrict__ stot, uint64_t *__restrict__ desc, uint32_t *__restrict__ sctl,
-    uint32_t *__restrict__ err) {
-  __shared__ uint32_t cnt[4][SORT_BINS];  // per-wave digit counts, then offsets
-  __shared__ uint32_t base[SORT_BINS];
-  __shared__ uint32_t wsum[4];
-  __shared__ uint32_t s_tile;
+    const uint32_t *__restrict__ tile_patch, const uint32_t *__restrict__ starts,
+    uint32_t n_tiles, const uint32_t *__restrict__ earlier, const uint32_t *__restrict__ tot) {
+  __shared__ uint32_t cnt[4][SORT_BINS];  // per-wave digit counts, then places in the tile
+  __shared__ uint32_t base[SORT_BINS];    // first slot of a digit less its place in the tile
+  __shared__ uint32_t wsum[4], psum[4];
+  __shared__ uint64_t sk[256 * R];
+  __shared__ uint32_t sv[256 * R];
   const uint32_t tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   const int shift = SORT_BITS * pass;
-  if (tid == 0) {
-    const uint32_t t = atomicAdd(&sctl[1 + (pass & 1)], 1u);
-    // the next pass's counter is idle until this launch ends
-    if (t == 0) sctl[1 + ((pass + 1) & 1)] = 0;
-    s_tile = t;
-  }
+  const uint32_t t = blockIdx.x;
+  const uint32_t s0 = tile_start[t], s1 = tile_end[t];
+  const uint32_t p = tile_patch[t];
+  const uint32_t before = earlier[(size_t)tid * n_tiles + t];
+  const uint32_t in_patch = tot[(size_t)p * SORT_BINS + tid];
 #pragma unroll
   for (int q = 0; q < 4; ++q) cnt[q][tid] = 0;
-  __syncthreads();
-  const uint32_t t = s_tile;
-  if (t >= n_tiles) {  // a counter that was not reset: report, touch nothing
-    if (tid == 0) atomicOr(err, RB_ERR_SORT);
-    return;  // uniform over the block
-  }
-  const uint32_t p = tile_patch[t], s0 = tile_start[t], s1 = tile_end[t];
-  const bool first = (t == patch_tile0[p]);
-  const uint32_t epoch = sctl[0];
-  const uint32_t tag = (epoch * SORT_PASSES + (uint32_t)pass) & 0x3FFFFFFFu;
-  uint32_t *tot_cur = stot + (size_t)(epoch & 1u) * P * (SORT_PASSES * SORT_BINS);
-  // the other totals buffer is counted into by the next sort: clear this
-  // patch's part (once per patch, in the first pass)
-  if (pass == 0 && first) {
-    uint32_t *tot_next = stot + (size_t)((epoch + 1u) & 1u) * P * (SORT_PASSES * SORT_BINS) +
-                         (size_t)p * (SORT_PASSES * SORT_BINS);
-    for (uint32_t i = tid; i < SORT_PASSES * SORT_BINS; i += 256) tot_next[i] = 0;
-  }
-
   // rank: wave w owns rows [w R, (w + 1) R) of the tile
   uint64_t kk[R];
   uint32_t vv[R], lr[R];
@@ -168,6 +148,7 @@ __global__ __launch_bounds__(256) void k_sort_pass(
     kk[r] = valid ? kin[s] : 0ull;
     vv[r] = valid ? vin[s] : 0u;
   }
+  __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const uint32_t s = s0 + (w * R + r) * 64 + lane;
@@ -183,82 +164,46 @@ __global__ __launch_bounds__(256) void k_sort_pass(
     if (valid && rank == 0) cnt[w][d] = b0 + (uint32_t)__popcll(peers);
   }
   __syncthreads();
-
-  // per digit (thread tid): counts of the tile and offsets of the waves
+  // per digit (thread tid): its place in the tile, and each wave's in it
   const uint32_t c0 = cnt[0][tid], c1 = cnt[1][tid], c2 = cnt[2][tid], c3 = cnt[3][tid];
-  const uint32_t tile_cnt = c0 + c1 + c2 + c3;
-  cnt[0][tid] = 0;
-  cnt[1][tid] = c0;
-  cnt[2][tid] = c0 + c1;
-  cnt[3][tid] = c0 + c1 + c2;
-  uint64_t *my = desc + (size_t)t * SORT_BINS + tid;
-  uint32_t excl = 0;
-  if (first) {
-    __hip_atomic_store(my, lb_pack(tag, LB_PREFIX, tile_cnt), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    __hip_atomic_store(my, lb_pack(tag, LB_AGG, tile_cnt), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    // read the predecessors LB_WIN at a time (loads in flight together),
-    // then take them in order up to the first published prefix
-    const uint32_t t_first = patch_tile0[p];
-    uint32_t j = t;  // tiles [t_first, j) are still to be read
-    uint32_t polls = 0;
-    bool done = false;
-    while (!done) {
-      const uint32_t nwin = min((uint32_t)LB_WIN, j - t_first);
-      if (nwin == 0) {  // no prefix before the patch's first tile: report, stop
-        atomicOr(err, RB_ERR_SORT);
-        break;
-      }
-      uint64_t x[LB_WIN];
-#pragma unroll
-      for (int q = 0; q < LB_WIN; ++q)
-        if ((uint32_t)q < nwin)
-          x[q] = __hip_atomic_load(desc + (size_t)(j - 1 - q) * SORT_BINS + tid,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int q = 0; q < LB_WIN; ++q) {
-        if (done || (uint32_t)q >= nwin) continue;
-        uint64_t v = x[q];
-        // wait for this predecessor to publish (bounded)
-        while (!((uint32_t)(v >> 34) == tag && ((v >> 32) & 3ull) != 0)) {
-          if (++polls > LB_POLLS) {
-            atomicOr(err, RB_ERR_SORT);
-            v = lb_pack(tag, LB_PREFIX, 0u);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-          v = __hip_atomic_load(desc + (size_t)(j - 1 - q) * SORT_BINS + tid, __ATOMIC_RELAXED,
-                                __HIP_MEMORY_SCOPE_AGENT);
-        }
-        excl += (uint32_t)v;
-        if (((v >> 32) & 3ull) == LB_PREFIX) done = true;
-      }
-      j -= nwin;  // the patch's first tile publishes a prefix: j never passes it
-    }
-    __hip_atomic_store(my, lb_pack(tag, LB_PREFIX, excl + tile_cnt), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t all = c0 + c1 + c2 + c3;
+  const uint32_t incl = rb_wave_incl_scan(all), pincl = rb_wave_incl_scan(in_patch);
+  if (lane == 63) {
+    wsum[w] = incl;
+    psum[w] = pincl;
   }
-  // keys of smaller digits in the patch: exclusive scan of the totals
-  const uint32_t dt = tot_cur[(size_t)p * (SORT_PASSES * SORT_BINS) + pass * SORT_BINS + tid];
-  const uint32_t incl = rb_wave_incl_scan(dt);
-  if (lane == 63) wsum[w] = incl;
   __syncthreads();
-  uint32_t add = 0;
-  for (uint32_t q = 0; q < w; ++q) add += wsum[q];
-  base[tid] = starts[p] + add + incl - dt + excl;
+  uint32_t at = incl - all, slot0 = starts[p] + pincl - in_patch + before;
+  for (uint32_t q = 0; q < w; ++q) {
+    at += wsum[q];
+    slot0 += psum[q];
+  }
+  cnt[0][tid] = at;
+  cnt[1][tid] = at + c0;
+  cnt[2][tid] = at + c0 + c1;
+  cnt[3][tid] = at + c0 + c1 + c2;
+  base[tid] = slot0 - at;
   __syncthreads();
-
-  // scatter
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const uint32_t s = s0 + (w * R + r) * 64 + lane;
     if (s < s1) {
       const uint32_t d = (uint32_t)(kk[r] >> shift) & (SORT_BINS - 1);
-      const uint32_t pos = base[d] + cnt[w][d] + lr[r];
-      kout[pos] = kk[r];
-      vout[pos] = vv[r];
+      const uint32_t q = cnt[w][d] + lr[r];
+      sk[q] = kk[r];
+      sv[q] = vv[r];
+    }
+  }
+  __syncthreads();
+  // out in digit order: neighbouring threads write neighbouring slots
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const uint32_t q = r * 256 + tid;
+    if (s0 + q < s1) {
+      const uint64_t k = sk[q];
+      const uint32_t pos = base[(uint32_t)(k >> shift) & (SORT_BINS - 1)] + q;
+      kout[pos] = k;
+      vout[pos] = sv[q];
     }
   }
 }
@@ -266,24 +211,24 @@ __global__ __launch_bounds__(256) void k_sort_pass(
 hipError_t launch_sort(rb_ctx *c) {
   if (c->sort_small) return launch_bsort(c);
   if (c->n_stiles == 0) return hipSuccess;
-  const uint32_t tpb = c->sort_hist_tiles;
-  hipLaunchKernelGGL(k_sort_hist, dim3(rb_div_up(c->n_stiles, tpb)), dim3(256), 0, c->stream,
-                     c->d_key[0], c->d_stile_start, c->d_stile_end, c->d_stile_patch,
-                     c->n_stiles, tpb, c->P, c->d_stot, c->d_sctl);
+  const dim3 grid(c->n_stiles), block(256);
+  const dim3 sgrid(SORT_BINS, std::min<uint32_t>(c->P, 64u));
   int src = 0;
   for (int pass = 0; pass < SORT_PASSES; ++pass) {
-#define RB_SORT_ARGS                                                                       \
-  pass, c->d_key[src], c->d_idx[src], c->d_key[1 - src], c->d_idx[1 - src], c->d_stile_start, \
-      c->d_stile_end, c->d_stile_patch, c->d_spatch_tile0, c->d_starts, c->P, c->n_stiles,    \
-      c->d_stot, c->d_sdesc, c->d_sctl, c->d_err
-    const dim3 grid(c->n_stiles), block(256);
-    switch (c->sort_rows) {
-      case 1: hipLaunchKernelGGL(k_sort_pass<1>, grid, block, 0, c->stream, RB_SORT_ARGS); break;
-      case 2: hipLaunchKernelGGL(k_sort_pass<2>, grid, block, 0, c->stream, RB_SORT_ARGS); break;
-      case 4: hipLaunchKernelGGL(k_sort_pass<4>, grid, block, 0, c->stream, RB_SORT_ARGS); break;
-      default: hipLaunchKernelGGL(k_sort_pass<8>, grid, block, 0, c->stream, RB_SORT_ARGS); break;
-    }
-#undef RB_SORT_ARGS
+#define RB_SORT_R(R)                                                                         \
+  do {                                                                                       \
+    hipLaunchKernelGGL(k_sort_count<R>, grid, block, 0, c->stream, pass, c->d_key[src],       \
+                       c->d_stile_start, c->d_stile_end, c->n_stiles, c->d_scnt);             \
+    hipLaunchKernelGGL(k_sort_scan, sgrid, block, 0, c->stream, c->d_scnt, c->d_spatch_tile0, \
+                       c->P, c->n_stiles, c->d_stot);                                         \
+    hipLaunchKernelGGL(k_sort_pass<R>, grid, block, 0, c->stream, pass, c->d_key[src],        \
+                       c->d_idx[src], c->d_key[1 - src], c->d_idx[1 - src], c->d_stile_start, \
+                       c->d_stile_end, c->d_stile_patch, c->d_starts, c->n_stiles, c->d_scnt, \
+                       c->d_stot);                                                            \
+  } while (0)
+    if (c->sort_rows == 4) RB_SORT_R(4);
+    else RB_SORT_R(8);
+#undef RB_SORT_R
     src = 1 - src;
   }
   return hipGetLastError();  // an even number of passes: the result is in buffer 0

@@ -109,12 +109,9 @@ __global__ __launch_bounds__(64) void k_topo_write(
     uint32_t *__restrict__ nlastchild, uint32_t *__restrict__ nskip,
     uint8_t *__restrict__ nlevel, uint8_t *__restrict__ nleaf, uint32_t *__restrict__ root,
     uint32_t *__restrict__ err, uint32_t *__restrict__ gctr, uint32_t *__restrict__ large_cnt,
-    uint32_t *__restrict__ sort_number, uint32_t *__restrict__ csr,
-    uint32_t *__restrict__ start_ids, const uint32_t *__restrict__ reuse,
+    uint32_t *__restrict__ csr, uint32_t *__restrict__ start_ids, const uint32_t *__restrict__ reuse,
     unsigned long long *__restrict__ stats) {
   const uint32_t b = blockIdx.x, lane = threadIdx.x;
-  // the sort that produced these keys is complete: number the next one
-  if (b == 0 && lane == 0) sort_number[0] += 1u;
   if (reuse && *reuse == 0u) {
     // the step keeps the last tree: its nodes, lists and work items stand;
     // only the grouped walk's queue restarts
@@ -252,7 +249,7 @@ hipError_t launch_topology(rb_ctx *c, const uint32_t *reuse) {
                      c->P, L, nv, c->n_tiles, c->d_cnt, c->d_lev_tot, (uint32_t)c->node_cap,
                      c->d_lev_off, c->d_nfirst, c->d_nlast, c->d_nchild, c->d_nlastchild,
                      c->d_nskip, c->d_nlevel, c->d_nleaf, c->d_root, c->d_err, c->d_gctr,
-                     c->d_large_cnt, c->d_sctl, c->d_csr, c->d_start_ids, reuse, c->d_stats);
+                     c->d_large_cnt, c->d_csr, c->d_start_ids, reuse, c->d_stats);
   return hipGetLastError();
 }
 

@@ -197,16 +197,17 @@ int build_layout(rb_ctx *c) {
   c->h_patch_tile0[P] = (uint32_t)c->h_tile_start.size();
   c->n_tiles = (uint32_t)c->h_tile_start.size();
   // systems (or batches) whose patches all hold at most 2^18 slots use the
-  // bucket sort; larger ones the look-back radix sort, tiles of 256 x R
-  // slots per 256-thread block, R growing with the system so that large
-  // sorts use fewer, fuller tiles
+  // bucket sort; larger ones the radix sort, tiles of 256 x R slots per
+  // 256-thread block (one step of a sheet at theta 1.2, R = 2 / 4 / 8:
+  // 400,000 particles 552 / 536 / 539 us, 700,000 852 / 822 / 818, 8.4e6 7.58
+  // / 7.16 / 6.93 ms)
   {
     const uint64_t n = c->h_starts[P];
     uint64_t largest = 0;
     for (uint32_t p = 0; p < P; ++p)
       largest = std::max<uint64_t>(largest, c->h_starts[p + 1] - c->h_starts[p]);
     c->sort_small = largest <= c->small_sort_max;
-    c->sort_rows = n < (1u << 18) ? 1 : n < (1u << 19) ? 2 : n < (1u << 20) ? 4 : 8;
+    c->sort_rows = n < (1u << 19) ? 4 : 8;
     const uint32_t st = c->sort_small ? 256u : 256u * (uint32_t)c->sort_rows;
     c->stile = st;
     c->h_stile_start.clear(); c->h_stile_end.clear(); c->h_stile_patch.clear();
@@ -222,11 +223,6 @@ int build_layout(rb_ctx *c) {
     }
     c->h_spatch_tile0[P] = (uint32_t)c->h_stile_start.size();
     c->n_stiles = (uint32_t)c->h_stile_start.size();
-    // histogram blocks: about 256 of them, at least 2048 keys each
-    {
-      const uint64_t per = std::max<uint64_t>(2048, (n + 255) / 256);
-      c->sort_hist_tiles = (uint32_t)std::max<uint64_t>(1, per / st);
-    }
     const size_t ns = c->n_stiles;
     RB_TRY(upload_sync(c, c->d_stile_start, c->h_stile_start.data(), ns * 4));
     RB_TRY(upload_sync(c, c->d_stile_end, c->h_stile_end.data(), ns * 4));
@@ -321,14 +317,8 @@ int init_ctx(rb_ctx *c, const rb_params *p, uint32_t P, const int64_t *off, cons
   RB_TRY(dalloc(c, &c->d_stile_end, max_stiles));
   RB_TRY(dalloc(c, &c->d_stile_patch, max_stiles));
   RB_TRY(dalloc(c, &c->d_spatch_tile0, P + 1));
-  RB_TRY(dalloc(c, &c->d_stot, 2 * 2048 * (uint64_t)P));
-  RB_TRY(dalloc(c, &c->d_sdesc, 256 * max_stiles));
-  RB_TRY(dalloc(c, &c->d_sctl, 4));
-  // totals start at zero (each sort clears the buffer the next one counts
-  // into); look-back words start with no valid flag
-  RB_HIP(hipMemsetAsync(c->d_stot, 0, 4 * 2 * 2048 * (size_t)P, c->stream));
-  RB_HIP(hipMemsetAsync(c->d_sdesc, 0, 8 * 256 * max_stiles, c->stream));
-  RB_HIP(hipMemsetAsync(c->d_sctl, 0, 16, c->stream));
+  RB_TRY(dalloc(c, &c->d_stot, 256 * (uint64_t)P));
+  RB_TRY(dalloc(c, &c->d_scnt, 256 * max_stiles));
   // bucket sort: patches of up to 2^18 slots (segments: at most one per
   // slot, plus one per patch)
   c->small_sort_max = std::min<uint64_t>(cap, 1u << 18);
@@ -640,7 +630,6 @@ int report_device_errors(rb_ctx *c) {
                   (unsigned long long)c->node_cap);
     if (err & RB_ERR_STACK) return fail(RB_ECAPACITY, "FP32 walk traversal stack overflow");
     if (err & RB_ERR_TREE) return fail(RB_ECAPACITY, "inconsistent tree links (internal error)");
-    if (err & RB_ERR_SORT) return fail(RB_EHIP, "radix sort look-back timed out (internal error)");
     if (err & RB_ERR_COLL) return fail(RB_ECAPACITY, "collision queue capacity exceeded");
     if (err & RB_ERR_INDEX) return fail(RB_EINVAL, "a target index lies outside [0, n)");
     if (err & RB_ERR_OUTSIDE)

@@ -92,12 +92,10 @@ struct rb_ctx {
   uint32_t *d_stile_start = nullptr, *d_stile_end = nullptr, *d_stile_patch = nullptr;
   uint32_t *d_spatch_tile0 = nullptr;  // P + 1
   uint32_t n_stiles = 0;
-  int sort_rows = 1;                   // rows of 64 keys per wave (1, 2, 4, 8)
+  int sort_rows = 4;                   // rows of 64 keys per wave (4 or 8)
   uint32_t stile = 256;                // slots per sort tile
-  uint32_t sort_hist_tiles = 1;        // sort tiles counted per histogram block
-  uint32_t *d_stot = nullptr;          // 2 x P x 8 passes x 256 digit totals
-  uint64_t *d_sdesc = nullptr;         // look-back words, 256 per sort tile
-  uint32_t *d_sctl = nullptr;          // [sort number, tile counter A, B, pad]
+  uint32_t *d_stot = nullptr;          // P x 256: a pass's keys of every digit
+  uint32_t *d_scnt = nullptr;          // 256 x sort tiles: digit counts, then those before
   // small systems: bucket sort (k_bsort.hip)
   bool sort_small = false;
   uint64_t small_sort_max = 0;  // largest patch the bucket sort takes

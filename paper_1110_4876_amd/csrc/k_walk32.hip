@@ -7,16 +7,15 @@
 // spatially compact and the items partition the particles.  One wave serves
 // one work item (an item with all its images, or one (item, image) pair),
 // pulled from a device queue by a persistent grid of workgroups of four
-// independent waves; floor(64 / n) lanes share each of the item's n
-// particles.  The image offsets of the item are tabulated in LDS once.  The
+// independent waves.  The image offsets of the item are tabulated in LDS once.  The
 // wave walks the tree once for the whole group (the item's particles): a
 // node is accepted for every member at once when w^2 < theta^2 R_min^2,
 // R_min being the distance from the node's image-shifted centre of mass to
 // the group's bounding box -- no member is closer, so every member would
 // accept the node on its own.  Accepted cells
 // and the particles of single-particle or opened leaves go to LDS
-// interaction lists (ballot / mbcnt compaction), evaluated by all lanes
-// reading the same entry (LDS broadcast).
+// interaction lists (ballot / mbcnt compaction); all 64 lanes evaluate them,
+// whatever the item's size (W32Share).
 //
 // Precision: traversal, opening test, image offsets and group-relative
 // positions are FP64.  List entries hold FP32 positions relative to the
@@ -26,13 +25,8 @@
 #include "rb_internal.h"
 
 #define W32_SCAP 1024  // traversal stack entries per wave (node << 5 | image)
-#define W32_CL 96      // cell list capacity (flushed at >= 32 entries)
-#define W32_CFLUSH 32
-#define W32_PL 128     // particle list capacity (flushed at >= 64 entries)
+#define W32_LIST 128   // cell and particle list capacities (64 taken at 64 entries)
 #define W32_RESERVE (7 * RB_DEPTH + 8)
-#ifndef W32_CELL_PAIRS
-#define W32_CELL_PAIRS 1  // cells two at a time: more registers, better issue
-#endif
 
 __device__ __forceinline__ int w32_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 // a value equal in every lane, moved to scalar registers
@@ -112,49 +106,151 @@ __device__ __forceinline__ void w32_part(const float4 a, float px, float py, flo
   f.x = fmaf(h, dx, f.x); f.y = fmaf(h, dy, f.y); f.z = fmaf(h, dz, f.z);
 }
 
-__device__ __forceinline__ void w32_eval_cells(const W32Cell *__restrict__ cel, int cnt, int sub,
-                                               int lpp, float px, float py, float pz, float b2,
-                                               bool quad, double &ax, double &ay, double &az) {
-  F3 f = {0.f, 0.f, 0.f};
-  int e = sub;
-#if W32_CELL_PAIRS
-  for (; e + lpp < cnt; e += 2 * lpp) {
-    const float4 a0 = cel[e].pos, a1 = cel[e + lpp].pos;
-    float4 q00 = {}, q01 = {}, q10 = {}, q11 = {};
-    if (quad) {
-      q00 = cel[e].q0; q01 = cel[e + lpp].q0;
-      q10 = cel[e].q1; q11 = cel[e + lpp].q1;
-    }
-    w32_cell(a0, q00, make_float2(q10.x, q10.y), px, py, pz, b2, quad, f);
-    w32_cell(a1, q01, make_float2(q11.x, q11.y), px, py, pz, b2, quad, f);
-  }
-#endif
-  for (; e < cnt; e += lpp) {
-    float4 q0 = {}, q1 = {};
-    if (quad) { q0 = cel[e].q0; q1 = cel[e].q1; }
-    w32_cell(cel[e].pos, q0, make_float2(q1.x, q1.y), px, py, pz, b2, quad, f);
-  }
-  ax += (double)f.x; ay += (double)f.y; az += (double)f.z;
+// How the wave's lanes share a list among an item's n members.  The members
+// form B = ceil(n / 4) blocks of four; a list of 16 S entries has 16 units
+// (entries v, v + 16, ...), and block b takes units 16 b .. 16 b + 15 of the
+// 16 B units of all blocks.  Lane group g (four lanes, one per member of a
+// block) does the B units from B g on: units of one block, and from the 16th
+// unit of that block on (after `turn` units) of the next.  So all 64 lanes
+// work whatever n is, a pass costs B / 16 of the list, and a lane serves the
+// same two members for every S.  Sixteen entries read at once lie in different
+// LDS banks.  The walk is bound by the issue of these terms.  Against
+// floor(64 / n) lanes per member (33 to 63 members leave 1 - n / 64 of the
+// lanes idle) and two terms at a time: a step of 1,048,576 ring particles
+// 1890 -> 1810 us, of 64 patches of 50,000 4190 -> 3950 us.  Four terms at a
+// time need 147 registers, three waves per SIMD; two at a time with four or
+// five waves, or the next terms' reads in flight ahead, were 1 to 3 % slower.
+struct W32Share {
+  int B, unit, turn;    // blocks, first unit of the lane's first block, units before the next
+  uint32_t turns;       // bit k: some lane goes on to its next block after k units
+  float ax, ay, az;     // the member of the first block, and of the next
+  float bx, by, bz;
+};
+
+struct D3 {
+  double x, y, z;
+};
+
+__device__ __forceinline__ void w32_add(D3 &a, const F3 &f) {
+  a.x += (double)f.x; a.y += (double)f.y; a.z += (double)f.z;
 }
 
-__device__ __forceinline__ void w32_eval_parts(const float4 *__restrict__ ppos, int cnt, int sub,
-                                               int lpp, float px, float py, float pz, float b2,
-                                               double &ax, double &ay, double &az) {
-  F3 f = {0.f, 0.f, 0.f};
-  int e = sub;
-  for (; e + 3 * lpp < cnt; e += 4 * lpp) {
-    const float4 a0 = ppos[e], a1 = ppos[e + lpp], a2 = ppos[e + 2 * lpp], a3 = ppos[e + 3 * lpp];
-    w32_part(a0, px, py, pz, b2, f);
-    w32_part(a1, px, py, pz, b2, f);
-    w32_part(a2, px, py, pz, b2, f);
-    w32_part(a3, px, py, pz, b2, f);
+__device__ __forceinline__ W32Share w32_share(int n, int lane) {
+  W32Share h;
+  h.B = (n + 3) >> 2;
+  const int u = h.B * (lane >> 2);
+  h.unit = u & 15;
+  const bool turns = h.unit + h.B > 16;
+  h.turn = turns ? 16 - h.unit : 32;
+  uint32_t t = 0u;
+#pragma unroll
+  for (int g = 1; g < 16; ++g) {
+    const int ug = (h.B * g) & 15;
+    if (ug + h.B > 16) t |= 1u << (16 - ug);
   }
-  for (; e < cnt; e += lpp) w32_part(ppos[e], px, py, pz, b2, f);
-  ax += (double)f.x; ay += (double)f.y; az += (double)f.z;
+  h.turns = t;
+  return h;
+}
+
+// the lane's member in its first block, or in the next; at least n: none
+__device__ __forceinline__ int w32_member(const W32Share &h, int lane, int next) {
+  return 4 * (((h.B * (lane >> 2)) >> 4) + next) + (lane & 3);
+}
+
+// The terms of 16 S entries, summed in FP32 (at most 4 B terms per sum) and
+// added to the members' FP64 sums; S entries at a time, so that their chains
+// of dependent terms overlap.
+template <int S, bool QUAD>
+__device__ __forceinline__ void w32_eval_cells(const W32Cell *__restrict__ cel,
+                                               const W32Share &h, float b2, D3 &A, D3 &Bs) {
+  F3 f = {0.f, 0.f, 0.f};
+  float px = h.ax, py = h.ay, pz = h.az;
+  const W32Cell *e = cel + h.unit;
+  for (int k = 0; k < h.B; ++k, ++e) {
+    if ((h.turns >> k) & 1u) {  // uniform
+      if (k == h.turn) {
+        w32_add(A, f);
+        f = {0.f, 0.f, 0.f};
+        px = h.bx; py = h.by; pz = h.bz;
+        e = cel;
+      }
+    }
+    float4 a[S], q0[S] = {};
+    float2 q1[S] = {};
+#pragma unroll
+    for (int i = 0; i < S; ++i) {
+      a[i] = e[16 * i].pos;
+      if (QUAD) {
+        q0[i] = e[16 * i].q0;
+        q1[i] = make_float2(e[16 * i].q1.x, e[16 * i].q1.y);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < S; ++i) w32_cell(a[i], q0[i], q1[i], px, py, pz, b2, QUAD, f);
+  }
+  if (h.turn < h.B) w32_add(Bs, f);
+  else w32_add(A, f);
+}
+
+template <int S>
+__device__ __forceinline__ void w32_eval_parts(const float4 *__restrict__ ppos,
+                                               const W32Share &h, float b2, D3 &A, D3 &Bs) {
+  F3 f = {0.f, 0.f, 0.f};
+  float px = h.ax, py = h.ay, pz = h.az;
+  const float4 *e = ppos + h.unit;
+  for (int k = 0; k < h.B; ++k, ++e) {
+    if ((h.turns >> k) & 1u) {  // uniform
+      if (k == h.turn) {
+        w32_add(A, f);
+        f = {0.f, 0.f, 0.f};
+        px = h.bx; py = h.by; pz = h.bz;
+        e = ppos;
+      }
+    }
+    float4 a[S];
+#pragma unroll
+    for (int i = 0; i < S; ++i) a[i] = e[16 * i];
+#pragma unroll
+    for (int i = 0; i < S; ++i) w32_part(a[i], px, py, pz, b2, f);
+  }
+  if (h.turn < h.B) w32_add(Bs, f);
+  else w32_add(A, f);
+}
+
+// entries that add nothing, up to a whole number of 16 (away from the
+// members: the terms stay finite)
+__device__ __forceinline__ void w32_pad_cells(W32Cell *cel, int n, int lane, bool quad) {
+  const int at = n + lane;
+  if (at < ((n + 15) & ~15)) {
+    cel[at].pos = make_float4(4.f, 4.f, 4.f, 0.f);
+    if (quad) {
+      cel[at].q0 = make_float4(0.f, 0.f, 0.f, 0.f);
+      cel[at].q1 = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+  }
+}
+__device__ __forceinline__ void w32_pad_parts(float4 *ppos, int n, int lane) {
+  const int at = n + lane;
+  if (at < ((n + 15) & ~15)) ppos[at] = make_float4(4.f, 4.f, 4.f, 0.f);
+}
+
+// A member's sum over the lanes that served it, lane groups in order (red:
+// the lanes' sums for their first and next members).
+__device__ __forceinline__ D3 w32_total(const double (*__restrict__ red)[3][64],
+                                        const W32Share &h, int m) {
+  D3 t = {0.0, 0.0, 0.0};
+  const int u0 = 16 * (m >> 2), u1 = u0 + 16;  // the block's units
+  // from the group that reaches u0 (its next block) or starts there
+  for (int g = u0 / h.B; g < 16 && h.B * g < u1; ++g) {
+    const int u = h.B * g, l = 4 * g + (m & 3);
+    const double(*r)[64] = red[u < u0 ? 1 : 0];
+    t.x += r[0][l]; t.y += r[1][l]; t.z += r[2][l];
+  }
+  return t;
 }
 
 template <bool QUAD, bool STATS>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_walk32(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void k_walk32(
     const WalkItem *__restrict__ groups, const WalkItem *__restrict__ groups_mid,
     uint32_t *__restrict__ gctr, int img_split, int n_img,
     int ngx, int ngy, int boundary, const PatchInfo *__restrict__ patch,
@@ -167,11 +263,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
   // four independent waves per workgroup (fewer workgroups to dispatch),
   // each with its own stack, lists and image table
   __shared__ uint32_t stk_all[4][W32_SCAP];
-  __shared__ W32Cell cel_all[4][W32_CL];
-  __shared__ float4 ppos_all[4][W32_PL];
+  __shared__ W32Cell cel_all[4][W32_LIST];
+  __shared__ float4 ppos_all[4][W32_LIST];
   __shared__ double2 img_all[4][RB_MAX_IMAGES];
 
-  static_assert(sizeof(cel_all[0]) >= 3 * 64 * sizeof(double), "reduction space");
+  static_assert(sizeof(cel_all[0]) >= 2 * 3 * 64 * sizeof(double), "reduction space");
   // the wave index is uniform: keep it (and the LDS bases) in scalar registers
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t *stk = stk_all[wv];
@@ -211,12 +307,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       if (lane == 0) atomicOr(err, RB_ERR_TREE);
       continue;
     }
-    // lpp = floor(64 / cnt) lanes per member, lane = member + cnt * sub;
-    // the lanes past lpp * cnt repeat members and are left out of the sums
-    const int lpp = 64 / cnt;
-    const int pidx = lane % cnt, sub = lane / cnt;
-    const bool valid = sub < lpp;
-    const uint32_t s = grp.start + (uint32_t)pidx;
+    const bool valid = lane < cnt;
+    const uint32_t s = grp.start + (uint32_t)(valid ? lane : 0);
 
     double x = sx[s], y = sy[s], z = sz[s];
     double lx = valid ? x : INFINITY, ly = valid ? y : INFINITY, lz = valid ? z : INFINITY;
@@ -237,9 +329,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
     const float b2 = (float)((soft * invW) * (soft * invW)) + W32_R2_FLOOR;
     const float px = (float)((x - gx) * invW), py = (float)((y - gy) * invW),
                 pz = (float)((z - gz) * invW);
+    W32Share h = w32_share(cnt, lane);
+    {
+      // (a lane without a member takes the first: its sums are not used)
+      const int ma = w32_member(h, lane, 0), mb = w32_member(h, lane, 1);
+      const int la = ma < cnt ? ma : 0, lb = mb < cnt ? mb : 0;
+      h.ax = __shfl(px, la, 64); h.ay = __shfl(py, la, 64); h.az = __shfl(pz, la, 64);
+      h.bx = __shfl(px, lb, 64); h.by = __shfl(py, lb, 64); h.bz = __shfl(pz, lb, 64);
+    }
     const double shear = sched[(size_t)step * 2 * P + p];
     const uint32_t r0 = root[p];
-    double ax = 0.0, ay = 0.0, az = 0.0;
+    D3 A = {0.0, 0.0, 0.0}, Bs = {0.0, 0.0, 0.0};
     if (lane < n_img) {
       double ox, oy;
       w32_image(lane, ngx, ngy, boundary, patch[p].L[0], patch[p].L[1], shear, ox, oy);
@@ -332,6 +432,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
           }
         }
         cl += __popcll(m);
+        if (STATS) n_cell += (unsigned long long)__popcll(m) * (unsigned long long)cnt;
       }
       // single-particle leaves
       {
@@ -342,6 +443,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                                   (float)((cz - gz) * invW), (float)(mc.w * gm_scale));
         }
         pl += __popcll(m);
+        if (STATS) n_pp += (unsigned long long)__popcll(m) * (unsigned long long)cnt;
       }
       // opened bucket leaves: the wave expands them one after another
       uint64_t bm = __ballot(open_leaf);
@@ -352,10 +454,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         const uint32_t count = __shfl(lk.count, src, 64);
         const double bx = __shfl(ox, src, 64), by = __shfl(oy, src, 64);
         for (uint32_t c0 = 0; c0 < count; c0 += 64) {
-          if (pl + 64 > W32_PL) {
-            w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
-            if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
-            pl = 0;
+          if (pl >= 64) {
+            w32_eval_parts<4>(ppos + (pl - 64), h, b2, A, Bs);
+            pl -= 64;
           }
           const uint32_t j = first + c0 + (uint32_t)lane;
           const bool inb = c0 + (uint32_t)lane < count;
@@ -369,43 +470,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
                                     (float)((sz[j] - gz) * invW), (float)(mj * gm_scale));
           }
           pl += __popcll(m);
+          if (STATS) n_pp += (unsigned long long)__popcll(m) * (unsigned long long)cnt;
         }
       }
       // next batch in flight while the lists are evaluated
       pop(k, e, lk, mc, q0, q1);
-      if (cl >= W32_CFLUSH) {
-        w32_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
-        if (STATS) n_cell += (unsigned long long)cl * (unsigned long long)cnt;
-        cl = 0;
+      if (cl >= 64) {
+        cl -= 64;
+        w32_eval_cells<4, QUAD>(cel + cl, h, b2, A, Bs);
       }
       if (pl >= 64) {
-        w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
-        if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
-        pl = 0;
+        pl -= 64;
+        w32_eval_parts<4>(ppos + pl, h, b2, A, Bs);
       }
     }
     if (overflow && lane == 0) atomicOr(err, RB_ERR_STACK);
-    if (cl > 0) {
-      w32_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
-      if (STATS) n_cell += (unsigned long long)cl * (unsigned long long)cnt;
+    // the rest of the lists, padded to a whole number of 16 entries (at most
+    // 63 cells; an expanded leaf leaves up to 64 particles or more)
+    w32_pad_cells(cel, cl, lane, QUAD);
+    if (pl >= 64) {
+      pl -= 64;
+      w32_eval_parts<4>(ppos + pl, h, b2, A, Bs);
     }
-    if (pl > 0) {
-      w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
-      if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
-    }
-    // lanes m, m + cnt, ... hold partial sums of member m: added in that
-    // order through the wave's cell list, which is no longer needed
-    double(*red)[64] = reinterpret_cast<double(*)[64]>(cel);
+    w32_pad_parts(ppos, pl, lane);
     w32_wave_sync();
-    red[0][lane] = ax; red[1][lane] = ay; red[2][lane] = az;
+    if (cl > 48) w32_eval_cells<4, QUAD>(cel, h, b2, A, Bs);
+    else if (cl > 32) w32_eval_cells<3, QUAD>(cel, h, b2, A, Bs);
+    else if (cl > 16) w32_eval_cells<2, QUAD>(cel, h, b2, A, Bs);
+    else if (cl > 0) w32_eval_cells<1, QUAD>(cel, h, b2, A, Bs);
+    if (pl > 48) w32_eval_parts<4>(ppos, h, b2, A, Bs);
+    else if (pl > 32) w32_eval_parts<3>(ppos, h, b2, A, Bs);
+    else if (pl > 16) w32_eval_parts<2>(ppos, h, b2, A, Bs);
+    else if (pl > 0) w32_eval_parts<1>(ppos, h, b2, A, Bs);
+    // the lanes' sums, through the wave's cell list (no longer needed)
+    double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(cel);
     w32_wave_sync();
-    if (lane < cnt) {
-      double tx = red[0][lane], ty = red[1][lane], tz = red[2][lane];
-      for (int k = 1; k < lpp; ++k) {
-        tx += red[0][lane + k * cnt]; ty += red[1][lane + k * cnt]; tz += red[2][lane + k * cnt];
-      }
+    red[0][0][lane] = A.x; red[0][1][lane] = A.y; red[0][2][lane] = A.z;
+    red[1][0][lane] = Bs.x; red[1][1][lane] = Bs.y; red[1][2][lane] = Bs.z;
+    w32_wave_sync();
+    if (valid) {
+      const D3 t = w32_total(red, h, lane);
       double *a = acc + (size_t)(img_split ? im0 : 0) * 3 * cap;
-      a[s] = tx; a[cap + s] = ty; a[2 * cap + s] = tz;
+      a[s] = t.x; a[cap + s] = t.y; a[2 * cap + s] = t.z;
     }
     w32_wave_sync();  // the list is rewritten by the next item
   }
@@ -423,7 +529,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // every run.  Each wave keeps its own interaction lists and evaluates them
 // for all of the group's particles; the waves' partial forces are added in
 // wave order at the end.  Two barriers per round; a group's chain of
-// dependent rounds is up to NW times shorter.
+// dependent rounds is up to NW times shorter.  A round's entries are dealt
+// evenly: with 64 to each wave in turn the first wave evaluated a small
+// round's list while the others waited (a step of 3,000 particles 121 -> 117
+// us with eight waves, of 50,000 212 -> 206 with four).
 // list capacities of the multi-wave walk: a list is evaluated at the start
 // of a round once it holds W32M_CFLUSH cells (W32M_PFLUSH particles), while
 // that round's node records are in flight; a round adds at most 64 entries
@@ -440,6 +549,49 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 #endif
 static_assert(W32M_CL >= W32M_CFLUSH - 1 + 64 && W32M_PL >= W32M_PFLUSH - 1 + 64,
               "a round's appends must fit after a partial list");
+
+// floor(64 / n) lanes (lpp) share each member here: the lists of a round are
+// short (up to 64 entries per wave), and the sharing of the one-wave walk
+// costs more to set up and to sum than the idle lanes it saves (a step of
+// 50,000 ring particles 210 us this way, 250 that way).
+__device__ __forceinline__ void w32m_eval_cells(const W32Cell *__restrict__ cel, int cnt, int sub,
+                                               int lpp, float px, float py, float pz, float b2,
+                                               bool quad, double &ax, double &ay, double &az) {
+  F3 f = {0.f, 0.f, 0.f};
+  int e = sub;
+  for (; e + lpp < cnt; e += 2 * lpp) {
+    const float4 a0 = cel[e].pos, a1 = cel[e + lpp].pos;
+    float4 q00 = {}, q01 = {}, q10 = {}, q11 = {};
+    if (quad) {
+      q00 = cel[e].q0; q01 = cel[e + lpp].q0;
+      q10 = cel[e].q1; q11 = cel[e + lpp].q1;
+    }
+    w32_cell(a0, q00, make_float2(q10.x, q10.y), px, py, pz, b2, quad, f);
+    w32_cell(a1, q01, make_float2(q11.x, q11.y), px, py, pz, b2, quad, f);
+  }
+  for (; e < cnt; e += lpp) {
+    float4 q0 = {}, q1 = {};
+    if (quad) { q0 = cel[e].q0; q1 = cel[e].q1; }
+    w32_cell(cel[e].pos, q0, make_float2(q1.x, q1.y), px, py, pz, b2, quad, f);
+  }
+  ax += (double)f.x; ay += (double)f.y; az += (double)f.z;
+}
+
+__device__ __forceinline__ void w32m_eval_parts(const float4 *__restrict__ ppos, int cnt, int sub,
+                                               int lpp, float px, float py, float pz, float b2,
+                                               double &ax, double &ay, double &az) {
+  F3 f = {0.f, 0.f, 0.f};
+  int e = sub;
+  for (; e + 3 * lpp < cnt; e += 4 * lpp) {
+    const float4 a0 = ppos[e], a1 = ppos[e + lpp], a2 = ppos[e + 2 * lpp], a3 = ppos[e + 3 * lpp];
+    w32_part(a0, px, py, pz, b2, f);
+    w32_part(a1, px, py, pz, b2, f);
+    w32_part(a2, px, py, pz, b2, f);
+    w32_part(a3, px, py, pz, b2, f);
+  }
+  for (; e < cnt; e += lpp) w32_part(ppos[e], px, py, pz, b2, f);
+  ax += (double)f.x; ay += (double)f.y; az += (double)f.z;
+}
 
 template <bool QUAD, bool STATS, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WAVES_PER_EU, 8))) void k_walk32m(
@@ -561,9 +713,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       }
       if (T == 0) break;  // uniform: sp is the same in every wave
       const int base = sp - T;
-      const int k = T - 64 * w < 0 ? 0 : (T - 64 * w > 64 ? 64 : T - 64 * w);
+      // dealt evenly: every wave's share of a small batch is short
+      const int share = (T + NW - 1) / NW;
+      const int k = T - share * w < 0 ? 0 : (T - share * w > share ? share : T - share * w);
       const bool has = lane < k;
-      const uint32_t e = has ? stk[base + 64 * w + lane] : 0u;
+      const uint32_t e = has ? stk[base + share * w + lane] : 0u;
       NodeLink lk = {0u, 0u, 0u, 0u};
       double4 mc = make_double4(0.0, 0.0, 0.0, 0.0);
       float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -582,12 +736,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       }
       // full lists are evaluated while the node records are in flight
       if (cl >= W32M_CFLUSH) {
-        w32_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
+        w32m_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
         if (STATS) n_cell += (unsigned long long)cl * (unsigned long long)cnt;
         cl = 0;
       }
       if (pl >= W32M_PFLUSH) {
-        w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
+        w32m_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
         if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
         pl = 0;
       }
@@ -661,7 +815,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
         const double bx = __shfl(ox, src, 64), by = __shfl(oy, src, 64);
         for (uint32_t c0 = 0; c0 < count; c0 += 64) {
           if (pl + 64 > W32M_PL) {
-            w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
+            w32m_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
             if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
             pl = 0;
           }
@@ -683,11 +837,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
     }
     if (overflow && threadIdx.x == 0) atomicOr(err, RB_ERR_STACK);
     if (cl > 0) {
-      w32_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
+      w32m_eval_cells(cel, cl, sub, lpp, px, py, pz, b2, QUAD, ax, ay, az);
       if (STATS) n_cell += (unsigned long long)cl * (unsigned long long)cnt;
     }
     if (pl > 0) {
-      w32_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
+      w32m_eval_parts(ppos, pl, sub, lpp, px, py, pz, b2, ax, ay, az);
       if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
     }
     // the partial forces of member m sit in lanes m, m + cnt, ... of every
@@ -735,15 +889,21 @@ hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const do
       sy, sz,                                                                             \
       c->d_msrc, c->d_sched, c->d_ctr, c->P, c->p.G, c->p.softening, th2, c->d_acc,       \
       c->cap, c->d_stats, c->d_err, slot
-  const int nw = c->p.walk_waves;
-  if (nw == 2 || nw == 4) {
+  // Four waves asked for, and too few items for the chip (a group holds 30 to
+  // 40 of its 64 particles): eight.  A sheet's step, us, with 4 / 8 waves:
+  // 3,000 particles 133 / 116, 16,000 155 / 147, 24,000 155 / 165; G = 32:
+  // 10,000 125 / 122, 30,000 170 / 199.  (Sixteen lose to eight throughout.)
+  int nw = c->p.walk_waves;
+  if (nw == 4 && max_items <= 320ull * (uint64_t)c->p.group_size) nw = 8;
+  if (nw >= 2) {
     // persistent grid of workgroups
-    uint64_t gridm = 256ull * (nw == 2 ? 12ull : 6ull);
+    uint64_t gridm = 256ull * (nw == 2 ? 12ull : nw == 4 ? 6ull : 3ull);
     if (gridm > max_items) gridm = max_items;
     const dim3 gm((unsigned)gridm), bm(64 * nw);
 #define RB_W32M(Q, S)                                                                   \
   if (nw == 2) hipLaunchKernelGGL((k_walk32m<Q, S, 2>), gm, bm, 0, c->stream, RB_W32_ARGS); \
-  else hipLaunchKernelGGL((k_walk32m<Q, S, 4>), gm, bm, 0, c->stream, RB_W32_ARGS);
+  else if (nw == 4) hipLaunchKernelGGL((k_walk32m<Q, S, 4>), gm, bm, 0, c->stream, RB_W32_ARGS); \
+  else hipLaunchKernelGGL((k_walk32m<Q, S, 8>), gm, bm, 0, c->stream, RB_W32_ARGS);
     if (quad && stats) { RB_W32M(true, true) }
     else if (quad) { RB_W32M(true, false) }
     else if (stats) { RB_W32M(false, true) }

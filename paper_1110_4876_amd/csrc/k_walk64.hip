@@ -451,8 +451,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
 // 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
 // 11.6 against 11.4 ms on 64 patches: four waves read a common part of the
-// tree).
+// tree).  The items of small patches are shared by RB_WALK64_SHARES
+// workgroups: all walk the item from the root until the stack holds W64G_SHARE
+// entries for each, the first alone adding what is accepted on the way; then
+// each keeps its own, and writes an accumulator set of its own.
 #define W64G_ENTRY 16  // bytes per stack entry
+#define W64G_SHARE 4   // stack entries per part when the parts take their shares
 // entries that depth-first descent may need on top of a full stack: one
 // entry popped and at most eight pushed per level
 #define W64G_RESERVE (7 * RB_DEPTH + 8)
@@ -549,8 +553,8 @@ __device__ __forceinline__ void w64g_sync() {
 
 template <bool QUAD, bool STATS, int NW, bool RS32, bool OFF32>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk64(
-    const WalkItem *__restrict__ items, uint32_t n_units, int img_split, int n_img, int ngx,
-    int ngy, int boundary, const PatchInfo *__restrict__ patch,
+    const WalkItem *__restrict__ items, uint32_t n_units, int img_split, int n_sets, int n_img,
+    int ngx, int ngy, int boundary, const PatchInfo *__restrict__ patch,
     const uint32_t *__restrict__ nlive, const uint32_t *__restrict__ root,
     const NodeLink *__restrict__ link, const double4 *__restrict__ mcom_g,
     const double *__restrict__ Q_g, const double *__restrict__ sx_g,
@@ -583,6 +587,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   const int im0 = img_split ? (int)(unit % (uint32_t)n_img) : 0;
   const int nim = img_split ? 1 : n_img;
   const WalkItem it = items[item];
+  // the item's workgroups, and which of them this is (a split walk has one);
+  // before they take their shares of the stack, the first one alone adds
+  const int parts = (int)(it.node >> 8), part = (int)(it.node & 255u);
+  // (sixteen waves only: what the others' compilers see is constant)
+  bool whole = NW == 16 && parts > 1, adds = !whole || part == 0;
   const uint32_t p = it.patch;
   const double W = patch[p].W;
   // (W 2^-l)^2 = fl(W W) 2^-2l exactly: scaling by a power of two is exact
@@ -633,6 +642,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   };
   w64g_sync<NW>();
   for (;;) {
+    if (NW == 16 && whole && sp >= W64G_SHARE * parts && sp <= 64 * NW) {
+      // every part keeps each parts-th entry (neighbours on the stack are
+      // siblings) and adds from here on
+      const int keep = (sp - part + parts - 1) / parts;
+      uint4 en = make_uint4(0u, 0u, 0u, 0u);
+      if ((int)threadIdx.x < keep) en = stk[(int)threadIdx.x * parts + part];
+      __syncthreads();
+      if ((int)threadIdx.x < keep) stk[threadIdx.x] = en;
+      __syncthreads();
+      sp = keep;
+      whole = false;
+      adds = true;
+    }
     // entries of this round: eight per wave, dealt to the waves in turn
     int k = sp < 8 * NW ? sp : 8 * NW;
     if (sp + 7 * k > CAP - W64G_RESERVE) {
@@ -682,7 +704,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
       if (own < 32u) mlo &= ~(1u << own);
       else if (own < 64u) mhi &= ~(1u << (own - 32u));
     }
-    if (STATS) {
+    if (STATS && adds) {
       const uint32_t cnt = (uint32_t)(__popc(mlo) + __popc(mhi));
       if (cell && below) n_open += cnt;
       if (all_in) n_cell += cnt;
@@ -711,7 +733,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
         const double R2 = __builtin_fma(d2, d2, __builtin_fma(d1, d1, d0 * d0));
         const bool take = __builtin_amdgcn_inverse_ballot_w64(mask) && w2q < theta2 * R2;
         const uint64_t opened = mask & ~__ballot(take);
-        if (take) {
+        if (take && adds) {
           w64g_cell<QUAD, RS32>(nd, d0, d1, d2, R2 + b2, ax, ay, az);
           if (STATS) ++n_cell;
         }
@@ -748,7 +770,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
       stk[at + (int)rb_mbcnt(pm)] = make_uint4(lk.child_or_first, nch | (im << 8), plo, phi);
     }
     // accepted cells, then single-particle leaves
-    const uint64_t b_in = __ballot(all_in), b_single = __ballot(single);
+    const uint64_t b_in = adds ? __ballot(all_in) : 0ull;
+    const uint64_t b_single = adds ? __ballot(single) : 0ull;
     for (int q8 = 0; q8 < 8 * n_mine; q8 += 8) {
       uint32_t m = (uint32_t)(b_in >> q8) & 255u;
       uint32_t ms = (uint32_t)(b_single >> q8) & 255u;
@@ -780,7 +803,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
       }
     }
     // opened bucket leaves: their members one by one
-    for (uint64_t m = __ballot(opens && leaf); m; m &= m - 1) {
+    for (uint64_t m = adds ? __ballot(opens && leaf) : 0ull; m; m &= m - 1) {
       const int j = __ffsll((long long)m) - 1;
       const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lk.child_or_first, j);
       const uint32_t e = a + (uint32_t)__builtin_amdgcn_readlane((int)lk.count, j);
@@ -803,7 +826,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
     }
     w64g_sync<NW>();  // entries written before the next round reads them
   }
-  double *a = acc + (size_t)(img_split ? im0 : 0) * 3 * cap;
+  double *a = acc + (size_t)(im0 + part) * 3 * cap;
   if (NW > 1) {
     // the waves' sums, added in wave order
     double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(&stk[0]);
@@ -819,6 +842,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   }
   if (w == 0 && s < it.end) {
     a[s] = G * ax; a[cap + s] = G * ay; a[2 * cap + s] = G * az;
+    // the sets that only other items' shares fill
+    for (int q = parts; q < n_sets; ++q) {
+      a += 3 * cap;
+      a[s] = 0.0; a[cap + s] = 0.0; a[2 * cap + s] = 0.0;
+    }
   }
   if (STATS) {
     unsigned long long o = n_open, c = n_cell, q2 = n_pp;
@@ -1063,7 +1091,8 @@ hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const do
     const dim3 g(units);
     const bool rs32 = w64_fp32_seed(c, th2, b2);
 #define RB_W64G_ARGS                                                                        \
-  c->d_items64, units, split, c->n_img, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,     \
+  c->d_items64, units, split, c->walk_parts, c->n_img, c->p.n_ghost[0], c->p.n_ghost[1],     \
+      c->p.boundary,                                                                         \
       c->d_patch, c->d_nlive, c->d_root, c->d_link, c->d_mcom, c->d_Q, sx, sy, sz, c->d_msrc, \
       c->d_sched, c->d_ctr, c->P, c->p.G, b2, th2, c->d_acc, c->cap, c->d_stats,             \
       c->d_lev_off, c->d_err, slot

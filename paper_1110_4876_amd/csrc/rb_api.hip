@@ -149,7 +149,7 @@ double shear_offset(const rb_params &p, double Lx, double Ly, double t) {
 // 16384 items.  The grouped FP32 walk draws from a device queue and splits
 // only on request.
 void set_split(rb_ctx *c) {
-  const uint32_t n_items = (uint32_t)c->h_items64.size();
+  const uint32_t n_items = c->n_items64;
   const bool fp64 = c->p.precision == RB_FP64;
   int mode = c->p.walk64_schedule;
   c->walk64_waves = n_items < RB_WALK64_WAVES16 ? 16 : n_items < RB_WALK64_WAVES8 ? 8 : 4;
@@ -164,6 +164,7 @@ void set_split(rb_ctx *c) {
   if (mode == 3 && per * parts > c->acc_sets) mode = 2;
   c->walk64_mode = mode;
   c->walk_parts = (fp64 && mode == 3) ? parts : 1;
+  if (fp64 && mode == 0 && !c->img_split) c->walk_parts = c->item_shares;
 }
 
 // tiles of RB_TILE slots inside each patch; walk items of `g` slots
@@ -243,15 +244,24 @@ int build_layout(rb_ctx *c) {
   std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
     return c->h_patch[a].n > c->h_patch[b].n;
   });
-  auto make_items = [&](uint32_t g, std::vector<WalkItem> &out) {
-    out.clear();
-    for (uint32_t p : order) {
-      const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1];
-      for (uint32_t s = s0; s < s1; s += g) out.push_back({s, std::min<uint32_t>(s + g, s1), p, 0});
-    }
-  };
-  make_items(64, c->h_items64);
-  if (c->h_items64.size() > c->cap / 16 + 2 * P + 8)
+  c->n_items64 = 0;
+  for (uint32_t p = 0; p < P; ++p) c->n_items64 += (c->h_starts[p + 1] - c->h_starts[p] + 63) / 64;
+  // (the rounds of the FP64 walk: an entry for every workgroup that shares the
+  // item, with its share and the number of shares in `node`)
+  const bool shares = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
+                      !(c->p.split_images == 1 && c->n_img > 1) &&
+                      c->n_items64 < RB_WALK64_WAVES16 && c->acc_sets >= (int)RB_WALK64_SHARES;
+  c->h_items64.clear();
+  c->item_shares = 1;
+  for (uint32_t p : order) {
+    const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1], np = (s1 - s0 + 63) / 64;
+    const uint32_t k = shares && np <= RB_WALK64_SHARED ? RB_WALK64_SHARES : 1u;
+    if (np > 0) c->item_shares = std::max(c->item_shares, (int)k);
+    for (uint32_t s = s0; s < s1; s += 64)
+      for (uint32_t q = 0; q < k; ++q)
+        c->h_items64.push_back({s, std::min<uint32_t>(s + 64, s1), p, (k << 8) | q});
+  }
+  if (c->h_items64.size() > c->cap / 16 + RB_WALK64_SHARES * (uint64_t)P + 8)
     return fail(RB_ECAPACITY, "walk item table overflow");
   RB_TRY(upload_sync(c, c->d_items64, c->h_items64.data(), c->h_items64.size() * sizeof(WalkItem)));
   set_split(c);
@@ -292,7 +302,7 @@ int init_ctx(rb_ctx *c, const rb_params *p, uint32_t P, const int64_t *off, cons
   c->node_cap = (uint64_t)(nf * (double)cap) + 64 * (uint64_t)P + 64;
   if (c->node_cap > 0xFFFFFFF0ull) return fail(RB_ECAPACITY, "node capacity beyond 32-bit indices");
   const uint64_t max_tiles = cap / RB_TILE_MIN + P + 1;
-  const uint64_t max_items = cap / 16 + 2 * (uint64_t)P + 8;
+  const uint64_t max_items = cap / 16 + RB_WALK64_SHARES * (uint64_t)P + 8;
   const uint64_t cap_pad = (cap + 31) / 32 * 32;  // (each array starts on a 256-byte line)
   RB_TRY(dalloc(c, &c->d_patch, P));
   RB_TRY(dalloc(c, &c->d_starts, P + 1));

@@ -136,7 +136,10 @@ struct rb_ctx {
   bool fp64_partial = false;  // the last tree (an FP32-mixed step) lacks FP64 records
 
   // walk
-  std::vector<WalkItem> h_items64;  // FP64 walk: 64 Morton-consecutive slots
+  // FP64 walk: 64 Morton-consecutive slots; an entry per workgroup of the rounds
+  std::vector<WalkItem> h_items64;
+  uint32_t n_items64 = 0;  // distinct items
+  int item_shares = 1;     // most workgroups of one item
   WalkItem *d_items64 = nullptr;
   WalkItem *d_witems = nullptr;     // FP32 walk: packed work items (big ones, small ones)
   WalkItem *d_witems_mid = nullptr; // FP32 walk: packed work items of middle size
@@ -343,6 +346,17 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // in the FP64 walk; four above
 #define RB_WALK64_WAVES16 1024u
 #define RB_WALK64_WAVES8 8192u
+// In launches of sixteen-wave workgroups, RB_WALK64_SHARES of them share each
+// item of a patch of at most RB_WALK64_SHARED items: one fills its CU's FP64
+// units, and so few leave most of the 256 CUs idle.  (By the patch's size, so
+// that a patch of a batch gets the sums that it gets alone.)  Sheets, us, with
+// 1 / 4 per item: gravity of 800 particles (13 items) 135 / 110, 1,500 (24)
+// 145 / 115, two steps of 1,000 295 / 223 (one to each subtree two levels
+// below the root: 124, 148, 259).  Above 24 items single systems still gain
+// (6,000 particles with two each: 9 %) but batches lose more (eight patches
+// of 2,500 to 5,000 particles, 2 to each item of up to 94: 231 -> 277).
+#define RB_WALK64_SHARES 4u
+#define RB_WALK64_SHARED 24u
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot);
 hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const double *sz,

@@ -47,3 +47,42 @@ def test_eight_waves_match_one(n):
     pr = inputs.sheet(n, seed=3).with_params(theta=0.4)
     kw = dict(precision=rb.RB_FP32_MIXED, group_size=16)
     _close(_gravity(pr, walk_waves=4, **kw), _gravity(pr, walk_waves=1, **kw), 1e-6)
+
+
+@pytest.mark.parametrize("n", [40, 64, 65, 700, 1536, 1537, 4000])
+@pytest.mark.parametrize("leaf", [1, 4])
+def test_fp64_items_shared_by_workgroups(n, leaf):
+    # up to 24 items of 64 particles: four workgroups an item, against each
+    # lane's own walk.  The sums differ in their order only: at most a few
+    # thousand FP64 terms (1.1e-16 each), and the in-plane cancellation of a
+    # sheet (under 100)
+    for pr in (inputs.sheet(n, seed=n).with_params(theta=0.5),
+               inputs.plummer(n, seed=n, b=0.01).with_params(theta=0.6)):
+        _close(_gravity(pr, leaf_size=leaf), _gravity(pr, leaf_size=leaf, walk64_schedule=1), 1e-11)
+
+
+def test_shared_items_beside_whole_ones():
+    # a batch of patches under and over 24 items, with one large enough that
+    # none is shared: every patch has the lanes' own walks' forces
+    import torch
+    from gpu_util import Dev
+    from paper_1110_4876_amd import rb
+    from test_gpu_batch import _batch_ctx, _concat
+    for sizes in ((100, 1536, 1537, 5000, 64), (100, 1536, 66000)):
+        ps = [inputs.sheet(n, seed=n).with_params(theta=0.5) for n in sizes]
+        big, off = _concat(ps)
+        out = []
+        for kw in ({}, {"walk64_schedule": 1}):
+            ctx = _batch_ctx(ps, off, rb.RB_FP64, **kw)
+            try:
+                d = Dev(big)
+                a = [torch.empty(big.n, dtype=torch.float64, device="cuda") for _ in range(3)]
+                for _ in range(2):
+                    rb.rb_batch_gravity(ctx, d.parts, 50.0, *a)
+                rb.rb_sync(ctx)
+                out.append(torch.stack(a, 1).cpu().numpy())
+            finally:
+                rb.rb_destroy(ctx)
+        for k in range(len(ps)):
+            sl = slice(off[k], off[k + 1])
+            _close(out[0][sl], out[1][sl], 1e-11)

@@ -86,3 +86,32 @@ def test_shared_items_beside_whole_ones():
         for k in range(len(ps)):
             sl = slice(off[k], off[k + 1])
             _close(out[0][sl], out[1][sl], 1e-11)
+
+
+@pytest.mark.parametrize("G,leaf", [(16, 1), (16, 8), (64, 1)])
+def test_sparse_children_of_populous_nodes(orc, G, leaf):
+    # A sphere's sparse octants beside its core are items of their own.  A
+    # group accepts a cell only where each member would, so the grouped walk
+    # errs no more than the FP64 walk, but for FP32 rounding (1e-5 of the rms
+    # covers it, as at theta = 0).
+    from gpu_util import Dev, export, make_ctx
+    from paper_1110_4876_amd import rb
+    pr = inputs.plummer(30000, seed=8, b=0.01, quadrupole=True).with_params(theta=0.6)
+    tg = inputs.sample_targets(pr.n, 1000, seed=1)
+    p = orc.make_params(**pr.params)
+    ref = orc.direct(p, pr.x, pr.y, pr.z, pr.m, n_active=pr.n, targets=tg)
+    a64 = _gravity(pr, leaf_size=leaf)[tg]
+    a32 = _gravity(pr, precision=rb.RB_FP32_MIXED, group_size=G, leaf_size=leaf)[tg]
+    den = np.sqrt(np.sum(ref ** 2))
+    e64, e32 = (np.sqrt(np.sum((a - ref) ** 2)) / den for a in (a64, a32))
+    assert e32 <= e64 + 1e-5, (e32, e64)
+    # and the FP64 moments of an FP32-mixed tree, which the items also carry
+    c = make_ctx(pr, precision=rb.RB_FP32_MIXED, group_size=G, leaf_size=leaf)
+    try:
+        rb.rb_tree_build(c, Dev(pr, with_v=False).parts, pr.n, pr.n)
+        t = export(c)
+    finally:
+        rb.rb_destroy(c)
+    i = int(np.argmin(t["level"]))
+    assert t["count"][i] == pr.n
+    assert abs(t["M"][i] - pr.m.sum()) <= 1e-12 * pr.m.sum()

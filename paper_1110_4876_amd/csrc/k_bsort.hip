@@ -13,20 +13,22 @@
 //                      more CUs busy and networks short);
 //   k_bsort_scatter -- every key to its bucket (one atomic per bucket and
 //                      wave);
-//   k_bsort_local   -- per segment: a bitonic sort of (key, slot) held in
-//                      registers, by one wave up to 512 keys (partners in
-//                      the same lane or swizzled across lanes), by a
-//                      workgroup up to 1024 (four rows of 256; partners
-//                      within a wave by shuffles, across rows in registers,
-//                      across waves through LDS), or, for a larger bucket,
-//                      eight-bit radix passes over the slot and the low 51
-//                      key bits by one workgroup in global memory.
+//   k_bsort_local   -- per segment of up to 512 keys: a bitonic sort of
+//                      (key, slot) held in registers, by one wave (partners
+//                      in the same lane or swizzled across lanes); a larger
+//                      bucket is first split by a workgroup, by the ten bits
+//                      below its keys' common prefix, as often as it takes.
 // Keys and slots arrive in buffer 0, go to their buckets in buffer 1 and
 // come back sorted to buffer 0.
 #include "rb_internal.h"
 
 #define BS_WIN 64    // segment window (slots)
-#define BS_LDS 1024  // largest segment sorted by the bitonic network
+#define BS_WAVE_MAX 512  // segments up to this size are sorted by one wave
+#define BS_SPLIT 1024    // parts that a larger one is split into
+#define BS_RUNS 1024     // windows of one split at most
+// parts still to be split (each above BS_WAVE_MAX, of the 2^18 slots of the
+// largest patch)
+#define BS_TODO ((1 << 18) / BS_WAVE_MAX)
 
 // lanes of the wave holding the same value in the low `bits` bits
 __device__ __forceinline__ uint64_t bs_match(uint64_t peers, uint32_t v, bool valid, int bits) {
@@ -43,6 +45,7 @@ __global__ __launch_bounds__(1024) void k_bsort_scan(uint32_t *__restrict__ bcnt
                                                      uint32_t *__restrict__ bcur,
                                                      const uint32_t *__restrict__ starts,
                                                      uint2 *__restrict__ seg,
+                                                     uint2 *__restrict__ big,
                                                      uint32_t *__restrict__ ctl) {
   constexpr int PER = (BS_NB + 1023) / 1024;
   __shared__ uint32_t wsum[16];
@@ -75,6 +78,8 @@ __global__ __launch_bounds__(1024) void k_bsort_scan(uint32_t *__restrict__ bcnt
     off += c[k];
     const uint32_t b = tid * PER + k;
     if (b < BS_NB) bcur[(size_t)p * BS_NB + b] = st + start[k];
+    if (c[k] > BS_WAVE_MAX)
+      big[atomicAdd(&ctl[2], 1u)] = make_uint2(st + start[k], st + start[k] + c[k]);
   }
   // window of the last non-empty bucket before this thread's: an
   // exclusive max-scan (windows never decrease along the buckets)
@@ -115,9 +120,8 @@ __global__ __launch_bounds__(1024) void k_bsort_scan(uint32_t *__restrict__ bcnt
 __global__ __launch_bounds__(256) void k_bsort_scatter(
     const uint64_t *__restrict__ kin, const uint32_t *__restrict__ vin,
     uint64_t *__restrict__ kout, uint32_t *__restrict__ vout, const uint32_t *__restrict__ starts,
-    uint32_t P, uint32_t n, uint32_t *__restrict__ bcur, uint32_t *__restrict__ ctl) {
+    uint32_t P, uint32_t n, uint32_t *__restrict__ bcur) {
   const uint32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s == 0) ctl[1] = 0;  // segments taken by k_bsort_local
   const bool valid = s < n;
   const uint64_t k = valid ? kin[s] : 0ull;
   const uint32_t v = valid ? vin[s] : 0u;
@@ -140,109 +144,6 @@ __global__ __launch_bounds__(256) void k_bsort_scatter(
 
 __device__ __forceinline__ bool bs_less(uint64_t ka, uint32_t va, uint64_t kb, uint32_t vb) {
   return ka < kb || (ka == kb && va < vb);
-}
-
-// digit q (8 bits) of the composite (low 51 key bits, slot): slot bits first
-__device__ __forceinline__ uint32_t bs_digit(uint64_t k, uint32_t v, int q) {
-  const uint64_t klow = k & ((1ull << 51) - 1ull);
-  const uint64_t lo = (klow << 18) | (uint64_t)v;  // v < 2^18 for small systems
-  return q < 8 ? (uint32_t)(lo >> (8 * q)) & 255u : (uint32_t)(klow >> 46) & 255u;
-}
-
-// One large bucket by one workgroup: nine stable 8-bit radix passes over
-// the composite, from buffer 1 to buffer 0 and back (ending in buffer 0).
-__device__ void bs_big(uint64_t *__restrict__ k1, uint32_t *__restrict__ v1,
-                       uint64_t *__restrict__ k0, uint32_t *__restrict__ v0, uint32_t a,
-                       uint32_t e, uint32_t *hist, uint32_t *wcnt /* [waves][256] */) {
-  const uint32_t tid = threadIdx.x, w = tid >> 6;
-  const uint32_t nw = blockDim.x >> 6;
-  for (int q = 0; q < 9; ++q) {
-    const uint64_t *ki = (q & 1) ? k0 : k1;
-    const uint32_t *vi = (q & 1) ? v0 : v1;
-    uint64_t *ko = (q & 1) ? k1 : k0;
-    uint32_t *vo = (q & 1) ? v1 : v0;
-    for (uint32_t i = tid; i < 256; i += blockDim.x) hist[i] = 0;
-    __syncthreads();
-    for (uint32_t s = a + tid; s < e; s += blockDim.x)
-      atomicAdd(&hist[bs_digit(ki[s], vi[s], q)], 1u);
-    __syncthreads();
-    if (tid < 64) {  // exclusive scan of the 256 bins, 4 per lane
-      uint32_t h4[4], t = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { h4[j] = hist[4 * tid + j]; t += h4[j]; }
-      uint32_t o = rb_wave_incl_scan(t) - t + a;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) { hist[4 * tid + j] = o; o += h4[j]; }
-    }
-    __syncthreads();
-    for (uint32_t c0 = a; c0 < e; c0 += blockDim.x) {
-      const uint32_t s = c0 + tid;
-      const bool valid = s < e;
-      const uint64_t kk = valid ? ki[s] : 0ull;
-      const uint32_t vv = valid ? vi[s] : 0u;
-      const uint32_t d = valid ? bs_digit(kk, vv, q) : 0u;
-      const uint64_t peers = bs_match(__ballot(valid), d, valid, 8);
-      const uint32_t rank = rb_mbcnt(peers);
-      for (uint32_t i = tid; i < nw * 256; i += blockDim.x) wcnt[i] = 0;
-      __syncthreads();
-      if (valid && rank == 0) wcnt[w * 256 + d] = (uint32_t)__popcll(peers);
-      __syncthreads();
-      if (tid < 256) {  // per digit: offsets of the waves, running total
-        uint32_t o = hist[tid];
-        for (uint32_t q2 = 0; q2 < nw; ++q2) {
-          const uint32_t t = wcnt[q2 * 256 + tid];
-          wcnt[q2 * 256 + tid] = o;
-          o += t;
-        }
-        hist[tid] = o;
-      }
-      __syncthreads();
-      if (valid) {
-        const uint32_t pos = wcnt[w * 256 + d] + rank;
-        ko[pos] = kk;
-        vo[pos] = vv;
-      }
-      __syncthreads();
-    }
-  }
-}
-
-// keep the smaller or the larger of (own, partner) key per element
-__device__ __forceinline__ void bs_take(uint64_t (&k)[4], uint32_t (&v)[4], const uint64_t (&pk)[4],
-                                        const uint32_t (&pv)[4], int nr, uint32_t tid,
-                                        uint32_t size, uint32_t stride) {
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    if (r < nr) {
-      const uint32_t el = (uint32_t)r * 256 + tid;
-      const bool asc = (el & size) == 0;
-      const bool keep_min = ((el & stride) == 0) == asc;
-      if (keep_min == (pk[r] < k[r]) && pk[r] != k[r]) { k[r] = pk[r]; v[r] = pv[r]; }
-    }
-  }
-}
-
-// one stage with the partner S lanes away in the same wave
-template <int S>
-__device__ __forceinline__ void bs_stage_wave(uint64_t (&k)[4], uint32_t (&v)[4], int nr,
-                                              uint32_t tid, uint32_t size) {
-  uint64_t pk[4];
-  uint32_t pv[4];
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    if (S < 32) {
-      // ds_swizzle, bit-mask mode: lane ^ S inside each half-wave
-      constexpr int pat = 0x1F | (S << 10);
-      const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)k[r], pat);
-      const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_swizzle((int)(uint32_t)(k[r] >> 32), pat);
-      pk[r] = ((uint64_t)hi << 32) | lo;
-      pv[r] = (uint32_t)__builtin_amdgcn_ds_swizzle((int)v[r], pat);
-    } else {
-      pk[r] = __shfl_xor(k[r], S, 64);
-      pv[r] = __shfl_xor(v[r], S, 64);
-    }
-  }
-  bs_take(k, v, pk, pv, nr, tid, size, (uint32_t)S);
 }
 
 // Bitonic network on (key, slot) pairs of one segment of at most 64 R
@@ -282,17 +183,16 @@ __device__ __forceinline__ void bs_wave_lanes(uint64_t (&k)[R], uint32_t (&v)[R]
 }
 
 template <int R>
-__device__ __forceinline__ void bs_wave_sort(const uint64_t *__restrict__ k1,
-                                             const uint32_t *__restrict__ v1,
-                                             uint64_t *__restrict__ k0, uint32_t *__restrict__ v0,
-                                             uint32_t a, uint32_t m, uint32_t lane) {
+__device__ __forceinline__ void bs_wave_sort(const uint64_t *k1, const uint32_t *v1, uint32_t b,
+                                             uint64_t *k0, uint32_t *v0, uint32_t a, uint32_t m,
+                                             uint32_t lane) {
   uint64_t k[R];
   uint32_t v[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const uint32_t e = lane * R + (uint32_t)r;
-    k[r] = e < m ? k1[a + e] : ~0ull;
-    v[r] = e < m ? v1[a + e] : ~0u;
+    k[r] = e < m ? k1[b + e] : ~0ull;
+    v[r] = e < m ? v1[b + e] : ~0u;
   }
 #pragma unroll
   for (uint32_t size = 2; size <= 64u * R; size <<= 1) {
@@ -342,162 +242,209 @@ __device__ __forceinline__ void bs_segment(const uint2 *__restrict__ seg,
   }
 }
 
-#define BS_WAVE_MAX 512  // segments up to this size are sorted by one wave
+// m <= BS_WAVE_MAX pairs from place b of (k1, v1), sorted to place a of (k0,
+// v0) by one wave (which may be the same: all are read before any is written).
+__device__ __forceinline__ void bs_wave(const uint64_t *k1, const uint32_t *v1, uint32_t b,
+                                        uint64_t *k0, uint32_t *v0, uint32_t a, uint32_t m,
+                                        uint32_t lane) {
+  if (m == 1) {
+    if (lane == 0) { k0[a] = k1[b]; v0[a] = v1[b]; }
+  } else if (m <= 64) {
+    bs_wave_sort<1>(k1, v1, b, k0, v0, a, m, lane);
+  } else if (m <= 128) {
+    bs_wave_sort<2>(k1, v1, b, k0, v0, a, m, lane);
+  } else if (m <= 256) {
+    bs_wave_sort<4>(k1, v1, b, k0, v0, a, m, lane);
+  } else {
+    bs_wave_sort<8>(k1, v1, b, k0, v0, a, m, lane);
+  }
+}
 
-// Persistent workgroups of four waves take segments four at a time (the
-// first four by grid position, the rest from a counter): each wave sorts
-// one segment of up to BS_WAVE_MAX keys on its own, then the workgroup sorts
-// the larger ones of the four together: a bitonic network over four rows of
-// 256 (element i in row i / 256 of thread i % 256) up to BS_LDS keys, with
-// equal keys put in slot order afterwards, or radix passes beyond.
-__global__ __launch_bounds__(256) void k_bsort_local(
-    uint64_t *__restrict__ k1, uint32_t *__restrict__ v1, uint64_t *__restrict__ k0,
-    uint32_t *__restrict__ v0, const uint2 *__restrict__ seg, uint32_t *__restrict__ ctl,
-    const uint32_t *__restrict__ starts) {
-  __shared__ uint64_t sk[BS_LDS];
-  __shared__ uint32_t sv[BS_LDS];
-  __shared__ uint32_t s_i;
+template <int NT>
+struct BsSplit {
+  uint64_t k[BS_SPLIT];  // the pairs of a bucket of up to BS_SPLIT keys
+  uint32_t v[BS_SPLIT];
+  uint32_t cnt[BS_SPLIT];  // counts, then cursors
+  uint32_t run[2 * BS_RUNS + 3];  // (two start in a window at most)
+  uint2 todo[BS_TODO];  // slots [x, y), the top bit of y: in buffer 1
+  unsigned long long any, all;
+  uint32_t vany, vall, n_todo, wsum[NT / 64];
+  int wmax[NT / 64];
+};
+
+// A bucket of more than BS_WAVE_MAX keys by one workgroup: its keys are dealt
+// to BS_SPLIT parts by the ten bits from the first in which they differ on
+// (equal keys by their slots' bits) and put in the other buffer, or in LDS if
+// they fit; runs of whole parts are sorted by a wave each, larger parts split
+// again.  A split
+// tells at least two keys apart and its parts share ten more bits, so they
+// end.  Bound by the waves' networks, one after another.  Concentrated systems
+// have most of their particles in a few buckets: forces of spheres at theta 0.9
+// (nine radix passes over global memory by one workgroup before, and four
+// large buckets in turn), 30,000 particles 579 -> 315 us, 260,000 2314 -> 1195.
+template <int NT>
+__device__ void bs_split(uint64_t *k1, uint32_t *v1, uint64_t *k0, uint32_t *v0, uint32_t a,
+                         uint32_t e, BsSplit<NT> &sh) {
+  constexpr int PER = BS_SPLIT / NT, NW = NT / 64;
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  const uint32_t nseg = ctl[0];
-  bool first = true;
+  uint32_t one = 1u;  // the keys are in buffer 1
+  if (tid == 0) sh.n_todo = 0;
   for (;;) {
-    if (tid == 0) s_i = first ? 4u * blockIdx.x : 4u * gridDim.x + atomicAdd(&ctl[1], 4u);
-    first = false;
-    __syncthreads();
-    const uint32_t i0 = s_i;
-    __syncthreads();
-    if (i0 >= nseg) break;  // uniform over the block
-    {
-      const uint32_t i = i0 + w;
-      if (i < nseg) {
-        uint32_t a, e;
-        bs_segment(seg, starts, nseg, i, a, e);
-        const uint32_t m = e - a;
-        if (m == 1) {
-          if (lane == 0) { k0[a] = k1[a]; v0[a] = v1[a]; }
-        } else if (m <= 64) {
-          bs_wave_sort<1>(k1, v1, k0, v0, a, m, lane);
-        } else if (m <= 128) {
-          bs_wave_sort<2>(k1, v1, k0, v0, a, m, lane);
-        } else if (m <= 256) {
-          bs_wave_sort<4>(k1, v1, k0, v0, a, m, lane);
-        } else if (m <= BS_WAVE_MAX) {
-          bs_wave_sort<8>(k1, v1, k0, v0, a, m, lane);
-        }
-      }
-    }
-    for (uint32_t q = 0; q < 4; ++q) {
-      const uint32_t i = i0 + q;
-      if (i >= nseg) break;  // uniform
-      uint32_t a, e;
-      bs_segment(seg, starts, nseg, i, a, e);
-      const uint32_t m = e - a;
-      if (m <= BS_WAVE_MAX) continue;  // uniform: done by a wave above
-      if (m > BS_LDS) {
-        // the LDS arrays serve as the radix scratch of the large-bucket path
-        uint32_t *scratch = reinterpret_cast<uint32_t *>(sk);
-        bs_big(k1, v1, k0, v0, a, e, scratch, scratch + 256);
-        __syncthreads();  // LDS reused by the next segment
-        continue;
-      }
-      uint32_t n2 = 256;
-      while (n2 < m) n2 <<= 1;
-      const int nr = (int)(n2 >> 8);  // rows in use (1, 2 or 4)
-      uint64_t k[4];
-      uint32_t v[4];
-      // removed particles' all-ones keys become all-ones minus one, so that
-      // the padding (all ones) sorts after them (live keys are below 2^63)
+    const uint64_t *ki = one ? k1 : k0;
+    const uint32_t *vi = one ? v1 : v0;
+    uint64_t *ko = one ? k0 : k1;
+    uint32_t *vo = one ? v0 : v1;
+    // the pairs from s0 on, four per thread, read once if they are few
+    const bool few = e - a <= BS_SPLIT;
+    uint64_t k[4];
+    uint32_t v[4], at = RB_NONE;
+    auto load = [&](uint32_t s0) {
+      if (at == s0) return;
+      at = s0;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const uint32_t j = (uint32_t)r * 256 + tid;
-        const bool in = r < nr && j < m;
-        const uint64_t kk = in ? k1[a + j] : RB_KEY_DEAD;
-        k[r] = in && kk == RB_KEY_DEAD ? RB_KEY_DEAD - 1ull : kk;
-        v[r] = in ? v1[a + j] : 0xFFFFFFFFu;
+        const uint32_t s = s0 + (uint32_t)(NT * r) + tid;
+        if (s < e) { k[r] = ki[s]; v[r] = vi[s]; }
       }
-      // the network orders the keys; equal keys (rare) are put in slot order
-      // afterwards
-      for (uint32_t size = 2; size <= n2; size <<= 1) {
-        for (uint32_t stride = size >> 1; stride >= 64; stride >>= 1) {
-          if (stride >= 256) {  // partner in another row of the same thread
-            const int rs = (int)(stride >> 8);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const int rr = r ^ rs;
-              if (r < nr && r < rr) {
-                const bool asc = ((((uint32_t)r * 256 + tid) & size) == 0);
-                if ((k[rr] < k[r]) == asc) {
-                  const uint64_t tk = k[r]; k[r] = k[rr]; k[rr] = tk;
-                  const uint32_t tv = v[r]; v[r] = v[rr]; v[rr] = tv;
-                }
-              }
-            }
-          } else {  // partner in another wave: through LDS
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (r < nr) { sk[r * 256 + tid] = k[r]; sv[r * 256 + tid] = v[r]; }
-            __syncthreads();
-            uint64_t pk[4];
-            uint32_t pv[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-              if (r < nr) {
-                pk[r] = sk[(r * 256 + tid) ^ stride];
-                pv[r] = sv[(r * 256 + tid) ^ stride];
-              }
-            __syncthreads();
-            bs_take(k, v, pk, pv, nr, tid, size, stride);
-          }
-        }
-        // partners inside the wave: constant strides
-        if (size >= 64) bs_stage_wave<32>(k, v, nr, tid, size);
-        if (size >= 32) bs_stage_wave<16>(k, v, nr, tid, size);
-        if (size >= 16) bs_stage_wave<8>(k, v, nr, tid, size);
-        if (size >= 8) bs_stage_wave<4>(k, v, nr, tid, size);
-        if (size >= 4) bs_stage_wave<2>(k, v, nr, tid, size);
-        bs_stage_wave<1>(k, v, nr, tid, size);
-      }
-      // equal keys in slot order: odd-even passes over runs of equal keys
-      // until nothing moves (at most the run length)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (r < nr) { sk[r * 256 + tid] = k[r]; sv[r * 256 + tid] = v[r]; }
-      __syncthreads();
-      bool ties = false;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t j = (uint32_t)r * 256 + tid;
-        if (r < nr && j > 0 && j < m && sk[j - 1] == sk[j]) ties = true;
-      }
-      if (__syncthreads_or(ties)) {
-        for (uint32_t it = 0; it < m; ++it) {
-          bool moved = false;
-          for (int ph = 0; ph < 2; ++ph) {
-            for (uint32_t j = 2 * tid + (uint32_t)ph; j + 1 < m; j += 2 * blockDim.x) {
-              if (sk[j] == sk[j + 1] && sv[j + 1] < sv[j]) {
-                const uint32_t t = sv[j]; sv[j] = sv[j + 1]; sv[j + 1] = t;
-                moved = true;
-              }
-            }
-            __syncthreads();
-          }
-          if (!__syncthreads_or(moved)) break;
-        }
+    };
+    auto each = [&](auto &&f) {
+      for (uint32_t s0 = a; s0 < e; s0 += 4 * NT) {
+        load(s0);
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          if (r < nr) { k[r] = sk[r * 256 + tid]; v[r] = sv[r * 256 + tid]; }
+          if (s0 + (uint32_t)(NT * r) + tid < e) f(k[r], v[r]);
       }
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t j = (uint32_t)r * 256 + tid;
-        if (r < nr && j < m) {
-          k0[a + j] = k[r] == RB_KEY_DEAD - 1ull ? RB_KEY_DEAD : k[r];
-          v0[a + j] = v[r];
-        }
-      }
-      __syncthreads();  // LDS reused by the next segment
+    };
+    // the bits that differ
+    if (tid == 0) { sh.any = 0; sh.all = ~0ull; sh.vany = 0; sh.vall = ~0u; }
+    for (uint32_t i = tid; i < BS_SPLIT; i += NT) sh.cnt[i] = 0;
+    __syncthreads();
+    {
+      uint64_t any = 0, all = ~0ull;
+      uint32_t vany = 0, vall = ~0u;
+      each([&](uint64_t kk, uint32_t vv) { any |= kk; all &= kk; vany |= vv; vall &= vv; });
+      atomicOr(&sh.any, (unsigned long long)any);
+      atomicAnd(&sh.all, (unsigned long long)all);
+      atomicOr(&sh.vany, vany);
+      atomicAnd(&sh.vall, vall);
     }
+    __syncthreads();
+    const uint64_t diff = sh.any & ~sh.all;
+    const uint32_t vdiff = sh.vany & ~sh.vall;
+    const bool by_key = diff != 0;  // (slots differ)
+    const int top = by_key ? 63 - __clzll((long long)diff) : 31 - __clz((int)vdiff);
+    const int shift = top > 9 ? top - 9 : 0;
+    auto part = [&](uint64_t kk, uint32_t vv) {
+      return (uint32_t)((by_key ? kk : (uint64_t)vv) >> shift) & (BS_SPLIT - 1u);
+    };
+    each([&](uint64_t kk, uint32_t vv) { atomicAdd(&sh.cnt[part(kk, vv)], 1u); });
+    __syncthreads();
+    // cursors, and runs of whole parts that start in the same window (a part
+    // as large as a window by itself): as the segments of k_bsort_scan
+    uint32_t c[PER], tot = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) { c[q] = sh.cnt[PER * tid + q]; tot += c[q]; }
+    const uint32_t incl = rb_wave_incl_scan(tot);
+    if (lane == 63) sh.wsum[w] = incl;
+    __syncthreads();
+    uint32_t off = incl - tot;
+    for (uint32_t q = 0; q < w; ++q) off += sh.wsum[q];
+    // the smallest windows of at least 64 pairs that are few enough
+    int wl = 6;
+    while (((e - a - 1) >> wl) >= BS_RUNS) ++wl;
+    uint32_t start[PER];
+    int mx = -1;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      start[q] = off;
+      if (c[q]) mx = (int)(off >> wl);
+      sh.cnt[PER * tid + q] = a + off;
+      off += c[q];
+    }
+    int run = mx;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(run, d, 64);
+      if (lane >= (uint32_t)d) run = o > run ? o : run;
+    }
+    if (lane == 63) sh.wmax[w] = run;
+    const int up = __shfl_up(run, 1, 64);
+    __syncthreads();
+    int prev = -1;
+    for (uint32_t q = 0; q < w; ++q) prev = sh.wmax[q] > prev ? sh.wmax[q] : prev;
+    if (lane > 0 && up > prev) prev = up;
+    uint32_t flags = 0, nf = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      const int win = (int)(start[q] >> wl);
+      if (c[q] && (win != prev || (c[q] >> wl) != 0)) { flags |= 1u << q; ++nf; }
+      if (c[q]) prev = win;
+    }
+    const uint32_t fin = rb_wave_incl_scan(nf);
+    if (lane == 63) sh.wsum[w] = fin;
+    __syncthreads();
+    uint32_t fo = fin - nf, n_run = 0;
+    for (uint32_t q = 0; q < NW; ++q) {
+      if (q < w) fo += sh.wsum[q];
+      n_run += sh.wsum[q];
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (flags & (1u << q)) sh.run[fo++] = a + start[q];
+    if (tid == 0) sh.run[n_run] = e;
+    uint64_t *const tk = few ? sh.k : ko;
+    uint32_t *const tv = few ? sh.v : vo;
+    const uint32_t base = few ? a : 0u;
+    each([&](uint64_t kk, uint32_t vv) {
+      const uint32_t to = atomicAdd(&sh.cnt[part(kk, vv)], 1u) - base;
+      tk[to] = kk;
+      tv[to] = vv;
+    });
+    __syncthreads();
+    for (uint32_t i = w; i < n_run; i += NW) {
+      const uint32_t x = sh.run[i], y = sh.run[i + 1];
+      if (y - x <= BS_WAVE_MAX) {
+        bs_wave(tk, tv, x - base, k0, v0, x, y - x, lane);
+        continue;
+      }
+      if (few)
+        for (uint32_t j = x + lane; j < y; j += 64) { ko[j] = tk[j - a]; vo[j] = tv[j - a]; }
+      if (lane == 0)
+        sh.todo[atomicAdd(&sh.n_todo, 1u)] = make_uint2(x, y | (one ? 0u : 0x80000000u));
+    }
+    __syncthreads();
+    const uint32_t left = sh.n_todo;
+    if (left == 0) break;  // uniform
+    const uint2 next = sh.todo[left - 1];
+    __syncthreads();
+    if (tid == 0) sh.n_todo = left - 1;
+    a = next.x;
+    e = next.y & 0x7FFFFFFFu;
+    one = next.y >> 31;
+  }
+  __syncthreads();  // LDS is used again by the next segment
+}
+
+// Workgroups split the large buckets, one each in turn, and then every wave
+// sorts segments of up to BS_WAVE_MAX keys, one in the grid's number of waves
+// (with a counter and barriers between them, a step of 64 patches took 4 %
+// longer).
+template <int NT>
+__global__ __launch_bounds__(NT) void k_bsort_local(
+    uint64_t *k1, uint32_t *v1, uint64_t *k0, uint32_t *v0, const uint2 *__restrict__ seg,
+    const uint2 *__restrict__ big, const uint32_t *__restrict__ ctl,
+    const uint32_t *__restrict__ starts) {
+  __shared__ BsSplit<NT> sh;
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t nseg = ctl[0], nbig = ctl[2];
+  for (uint32_t i = blockIdx.x; i < nbig; i += gridDim.x)
+    bs_split<NT>(k1, v1, k0, v0, big[i].x, big[i].y, sh);
+  for (uint32_t i = NT / 64 * blockIdx.x + w; i < nseg; i += NT / 64 * gridDim.x) {
+    uint32_t a, e;
+    bs_segment(seg, starts, nseg, i, a, e);
+    if (e - a <= BS_WAVE_MAX) bs_wave(k1, v1, a, k0, v0, a, e - a, lane);
   }
 }
 
@@ -505,12 +452,18 @@ hipError_t launch_bsort(rb_ctx *c) {
   const uint32_t n = (uint32_t)c->h_starts[c->P];
   if (n == 0) return hipSuccess;
   hipLaunchKernelGGL(k_bsort_scan, dim3(c->P), dim3(1024), 0, c->stream, c->d_bcnt, c->d_bcur,
-                     c->d_starts, c->d_bseg, c->d_bctl);
+                     c->d_starts, c->d_bseg, c->d_bbig, c->d_bctl);
   hipLaunchKernelGGL(k_bsort_scatter, dim3(rb_div_up(n, 256)), dim3(256), 0, c->stream,
                      c->d_key[0], c->d_idx[0], c->d_key[1], c->d_idx[1], c->d_starts, c->P, n,
-                     c->d_bcur, c->d_bctl);
-  const unsigned grid = (unsigned)std::min<uint64_t>(1024, rb_div_up(n, 256) + c->P);
-  hipLaunchKernelGGL(k_bsort_local, dim3(grid), dim3(256), 0, c->stream, c->d_key[1],
-                     c->d_idx[1], c->d_key[0], c->d_idx[0], c->d_bseg, c->d_bctl, c->d_starts);
+                     c->d_bcur);
+  const int nt = c->sort_threads;
+  const unsigned grid = (unsigned)std::min<uint64_t>(262144 / nt, rb_div_up(n, nt) + c->P);
+#define RB_BS_LOCAL(NT)                                                                       \
+  hipLaunchKernelGGL(k_bsort_local<NT>, dim3(grid), dim3(NT), 0, c->stream, c->d_key[1],       \
+                     c->d_idx[1], c->d_key[0], c->d_idx[0], c->d_bseg, c->d_bbig, c->d_bctl,  \
+                     c->d_starts)
+  if (nt == 256) RB_BS_LOCAL(256);
+  else RB_BS_LOCAL(1024);
+#undef RB_BS_LOCAL
   return hipGetLastError();
 }

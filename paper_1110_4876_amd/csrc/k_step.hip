@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void k_prologue(
   key[s] = k;
   idx[s] = s;
   if (bcnt) {
-    if (s == 0) bctl[0] = 0;  // segments of the bucket sort, counted anew
+    if (s == 0) bctl[0] = bctl[2] = 0;  // segments of the bucket sort, counted anew
     rb_bucket_add(bcnt, p, P, k);
   }
 }
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(256) void k_post(
     key[s] = k2;
     idx[s] = s;
     if (bcnt) {
-      if (s == 0) bctl[0] = 0;
+      if (s == 0) bctl[0] = bctl[2] = 0;
       rb_bucket_add(bcnt, p, P, k2);
     }
   }

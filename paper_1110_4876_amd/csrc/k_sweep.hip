@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256) void k_sw_keys(
     key[s] = k;
     idx[s] = s;
     if (bcnt) {
-      if (s == 0) bctl[0] = 0;  // segments of the bucket sort, counted anew
+      if (s == 0) bctl[0] = bctl[2] = 0;  // segments of the bucket sort, counted anew
       rb_bucket_add(bcnt, 0, 1, k);
     }
   }

@@ -208,6 +208,11 @@ int build_layout(rb_ctx *c) {
     for (uint32_t p = 0; p < P; ++p)
       largest = std::max<uint64_t>(largest, c->h_starts[p + 1] - c->h_starts[p]);
     c->sort_small = largest <= c->small_sort_max;
+    // workgroups of k_bsort_local: sixteen waves split a large bucket sooner,
+    // four spread the rest better (with 4 / 16, spheres of 50,000 447 / 414
+    // us, 260,000 1370 / 1195; four steps of sheets of 50,000 643 / 649 us,
+    // 260,000 2091 / 2134)
+    c->sort_threads = largest > (1u << 16) ? 1024 : 256;
     c->sort_rows = n < (1u << 19) ? 4 : 8;
     const uint32_t st = c->sort_small ? 256u : 256u * (uint32_t)c->sort_rows;
     c->stile = st;
@@ -335,6 +340,7 @@ int init_ctx(rb_ctx *c, const rb_params *p, uint32_t P, const int64_t *off, cons
   RB_TRY(dalloc(c, &c->d_bcnt, (uint64_t)BS_NB * P));
   RB_TRY(dalloc(c, &c->d_bcur, (uint64_t)BS_NB * P));
   RB_TRY(dalloc(c, &c->d_bseg, cap + P + 1));
+  RB_TRY(dalloc(c, &c->d_bbig, cap / 512 + 1));
   RB_TRY(dalloc(c, &c->d_bctl, 4));
   RB_HIP(hipMemsetAsync(c->d_bcnt, 0, 4 * (size_t)BS_NB * P, c->stream));
   RB_HIP(hipMemsetAsync(c->d_bctl, 0, 16, c->stream));

@@ -99,10 +99,12 @@ struct rb_ctx {
   // small systems: bucket sort (k_bsort.hip)
   bool sort_small = false;
   uint64_t small_sort_max = 0;  // largest patch the bucket sort takes
+  int sort_threads = 256;       // threads per workgroup of k_bsort_local
   uint32_t *d_bcnt = nullptr;   // P x 4097 bucket counts (zero between sorts)
   uint32_t *d_bcur = nullptr;   // P x 4097 scatter cursors
   uint2 *d_bseg = nullptr;      // segments (first slot, patch)
-  uint32_t *d_bctl = nullptr;   // [segments, segments taken]
+  uint2 *d_bbig = nullptr;      // buckets of more than 512 keys (slots [x, y))
+  uint32_t *d_bctl = nullptr;   // [segments, unused, large buckets]
 
   // particles in sorted order (ping-pong for rb_step): x y z vx vy vz m, or
   // records in the caller's order (StateRec) on the way in and out

@@ -671,14 +671,40 @@ __device__ __forceinline__ uint64_t ml_touch(const double *p, uint32_t a, uint32
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return s;
 }
+// Bottom large nodes (no large child) from the i0-th on, every step-th.
+__device__ __forceinline__ void ml_bottom(uint32_t i0, uint32_t step,
+                                          const uint32_t *__restrict__ bottom,
+                                          const uint32_t *__restrict__ large_cnt,
+                                          const uint32_t *__restrict__ lev_off,
+                                          const uint8_t *__restrict__ nlevel, RB_MOMENT_PARAMS) {
+  const uint32_t cnt = large_cnt[RB_BOTTOM];
+  for (uint32_t i = i0; i < cnt; i += step) {
+    const uint32_t id = bottom[i];
+    const int l = nlevel[id];
+    const bool leaf = nleaf[id] != 0;
+    const uint32_t first = nfirst[id], last = nlast[id], skip = nskip[id];
+    const uint32_t ca = leaf ? 0u : nchild[id], cb = leaf ? 0u : nlastchild[id];
+    const uint32_t clo = (l < RB_DEPTH) ? lev_off[l + 1] : 0u;
+    const uint32_t chi = (l < RB_DEPTH) ? lev_off[l + 2] : 0u;
+    if (!leaf && ca >= clo && ca <= cb && cb < chi && cb - ca < 8)
+      ml_internal(id, l, first, last, ca, cb, skip, quad, link, mcom, Sarr, Qarr, wn);
+    else  // leaves, and anything inconsistent (reported there)
+      rb_node_moments_at(id, l, first, last, leaf, ca, cb, skip, clo, chi, sx, sy, sz, msrc,
+                         quad, link, mcom, Sarr, Qarr, wn, n_slots, err);
+  }
+}
+
 __global__ __launch_bounds__(512) void k_moments_large(
-    const uint32_t *__restrict__ large, const uint32_t *__restrict__ large_cnt,
-    const uint32_t *__restrict__ lev_off, RB_MOMENT_PARAMS) {
+    const uint32_t *__restrict__ large, const uint32_t *__restrict__ bottom,
+    const uint32_t *__restrict__ large_cnt, const uint32_t *__restrict__ lev_off,
+    const uint8_t *__restrict__ nlevel, RB_MOMENT_PARAMS) {
   __shared__ uint32_t s_cnt[RB_NLEV], s_off[RB_NLEV + 2], s_pos[RB_NLEV + 1];
   __shared__ uint32_t l_id[ML_CAP], l_first[ML_CAP], l_last[ML_CAP], l_ca[ML_CAP],
       l_cb[ML_CAP], l_skip[ML_CAP];
   __shared__ uint8_t l_leaf[ML_CAP];
   const uint32_t tid = threadIdx.x;
+  // (small systems: no launch of their own)
+  if (bottom) ml_bottom(tid, blockDim.x, bottom, large_cnt, lev_off, nlevel, RB_MOMENT_ARGS);
   if (tid < RB_NLEV) s_cnt[tid] = large_cnt[tid];
   if (tid < RB_NLEV + 2) s_off[tid] = lev_off[tid];
   __syncthreads();
@@ -751,7 +777,6 @@ __global__ __launch_bounds__(512) void k_moments_large(
   }
 }
 
-// large nodes of one level over the whole chip (large systems)
 // The bottom large nodes, one per thread, spread over many CUs (their
 // children's records are read from memory by each node's own thread).
 __global__ __launch_bounds__(64) void k_moments_bottom(const uint32_t *__restrict__ bottom,
@@ -759,23 +784,11 @@ __global__ __launch_bounds__(64) void k_moments_bottom(const uint32_t *__restric
                                                        const uint32_t *__restrict__ lev_off,
                                                        const uint8_t *__restrict__ nlevel,
                                                        RB_MOMENT_PARAMS) {
-  const uint32_t cnt = large_cnt[RB_BOTTOM];
-  for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += gridDim.x * blockDim.x) {
-    const uint32_t id = bottom[i];
-    const int l = nlevel[id];
-    const bool leaf = nleaf[id] != 0;
-    const uint32_t first = nfirst[id], last = nlast[id], skip = nskip[id];
-    const uint32_t ca = leaf ? 0u : nchild[id], cb = leaf ? 0u : nlastchild[id];
-    const uint32_t clo = (l < RB_DEPTH) ? lev_off[l + 1] : 0u;
-    const uint32_t chi = (l < RB_DEPTH) ? lev_off[l + 2] : 0u;
-    if (!leaf && ca >= clo && ca <= cb && cb < chi && cb - ca < 8)
-      ml_internal(id, l, first, last, ca, cb, skip, quad, link, mcom, Sarr, Qarr, wn);
-    else  // leaves, and anything inconsistent (reported there)
-      rb_node_moments_at(id, l, first, last, leaf, ca, cb, skip, clo, chi, sx, sy, sz, msrc,
-                         quad, link, mcom, Sarr, Qarr, wn, n_slots, err);
-  }
+  ml_bottom(blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, bottom, large_cnt,
+            lev_off, nlevel, RB_MOMENT_ARGS);
 }
 
+// large nodes of one level over the whole chip (large systems)
 __global__ __launch_bounds__(256) void k_moments_large_level(
     int l, const uint32_t *__restrict__ large, const uint32_t *__restrict__ large_cnt,
     const uint32_t *__restrict__ lev_off, RB_MOMENT_PARAMS) {
@@ -819,14 +832,21 @@ hipError_t launch_moments(rb_ctx *c, const double *sx, const double *sy, const d
                      (int)c->h_patch[0].nvirt, c->p.quadrupole, c->d_link, c->d_mcom, c->d_S, c->d_Q, wnode,
                      (wnode && roots_only) ? 1 : 0, c->d_err);
   // bottom large nodes are disjoint subtrees of more than G particles each
+  const int lv = c->p.moments_level_log2 > 0 ? c->p.moments_level_log2 : 22;
+  const bool one = (uint64_t)n <= (1ull << lv);  // (one workgroup for the levels)
+  // a launch saved where the bottom nodes' records are few for one CU (four
+  // steps of sheets, us, with a launch of their own / without: 3,000 particles
+  // 432 / 424, 12,000 475 / 470, 24,000 542 / 536, 50,000 701 / 719; forces of
+  // spheres 1,024 150 / 149, 24,000 333 / 336)
+  const bool with_bottom = one && n <= 16384;
   unsigned bgrid = rb_div_up(n / (G + 1) + 1, 64);
   if (bgrid > 2048) bgrid = 2048;
-  hipLaunchKernelGGL(k_moments_bottom, dim3(bgrid), dim3(64), 0, c->stream, c->d_bottom,
+  if (!with_bottom) hipLaunchKernelGGL(k_moments_bottom, dim3(bgrid), dim3(64), 0, c->stream, c->d_bottom,
                      c->d_large_cnt, c->d_lev_off, c->d_nlevel, RB_MARGS);
-  const int lv = c->p.moments_level_log2 > 0 ? c->p.moments_level_log2 : 22;
-  if ((uint64_t)n <= (1ull << lv)) {
+  if (one) {
     hipLaunchKernelGGL(k_moments_large, dim3(1), dim3(512), 0, c->stream, c->d_large,
-                       c->d_large_cnt, c->d_lev_off, RB_MARGS);
+                       with_bottom ? c->d_bottom : nullptr, c->d_large_cnt, c->d_lev_off,
+                       c->d_nlevel, RB_MARGS);
   } else {
     for (int l = RB_DEPTH; l >= 0; --l)
       hipLaunchKernelGGL(k_moments_large_level, dim3(512), dim3(256), 0, c->stream, l,

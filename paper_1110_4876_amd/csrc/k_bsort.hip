@@ -25,6 +25,7 @@
 #define BS_WIN 64    // segment window (slots)
 #define BS_WAVE_MAX 512  // segments up to this size are sorted by one wave
 #define BS_SPLIT 1024    // parts that a larger one is split into
+#define BS_ONE 2048      // patches up to this size are sorted by one workgroup
 #define BS_RUNS 1024     // windows of one split at most
 // parts still to be split (each above BS_WAVE_MAX, of the 2^18 slots of the
 // largest patch)
@@ -448,9 +449,130 @@ __global__ __launch_bounds__(NT) void k_bsort_local(
   }
 }
 
+// Patches of up to BS_ONE slots: all of it by one workgroup, the buckets in
+// LDS, where three launches are bound by their latency (four steps of sheets:
+// 300 particles 355 -> 335 us, 1,024 396 -> 379, 2,048 423 -> 417; 4,000
+// 444 -> 466, sixteen waves taking longer than many workgroups).
+__global__ __launch_bounds__(1024) void k_bsort_one(uint64_t *k1, uint32_t *v1, uint64_t *k0,
+                                                    uint32_t *v0,
+                                                    const uint32_t *__restrict__ starts,
+                                                    uint32_t *__restrict__ bcnt) {
+  constexpr int PER = (BS_NB + 1023) / 1024, ROWS = BS_ONE / 1024;
+  struct One {
+    uint64_t k[BS_ONE];
+    uint32_t v[BS_ONE], cur[BS_NB];
+  };
+  // (the pairs have left LDS when a large bucket is split)
+  __shared__ union { One o; BsSplit<1024> split; } sh;
+  __shared__ uint32_t seg[2 * (BS_ONE / BS_WIN) + 2], wsum[16], s_big[BS_ONE / BS_WAVE_MAX][2], n_big;
+  __shared__ int wmax[16];
+  const uint32_t p = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const uint32_t w = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t st = starts[p], n = starts[p + 1] - st;
+  if (n == 0 || n > BS_ONE) return;  // (larger: never launched)
+  uint64_t k[ROWS];
+  uint32_t v[ROWS];
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    const uint32_t i = 1024u * (uint32_t)r + tid;
+    k[r] = i < n ? k0[st + i] : 0ull;
+    v[r] = i < n ? v0[st + i] : 0u;
+  }
+  // bucket offsets and segments, as k_bsort_scan finds them
+  uint32_t *cnt = bcnt + (size_t)p * BS_NB;
+  uint32_t c[PER], tot = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t b = tid * PER + q;
+    c[q] = (b < BS_NB) ? cnt[b] : 0u;
+    if (b < BS_NB) cnt[b] = 0u;  // ready for the next sort
+    tot += c[q];
+  }
+  if (tid == 0) n_big = 0;
+  const uint32_t incl = rb_wave_incl_scan(tot);
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  uint32_t off = incl - tot;
+  for (uint32_t q = 0; q < w; ++q) off += wsum[q];
+  uint32_t start[PER];
+  int mx = -1;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const uint32_t b = tid * PER + q;
+    start[q] = off;
+    if (c[q]) mx = (int)(off / BS_WIN);
+    if (b < BS_NB) sh.o.cur[b] = off;
+    if (c[q] > BS_WAVE_MAX) {
+      const uint32_t i = atomicAdd(&n_big, 1u);
+      s_big[i][0] = off;
+      s_big[i][1] = off + c[q];
+    }
+    off += c[q];
+  }
+  int run = mx;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(run, d, 64);
+    if (lane >= (uint32_t)d) run = o > run ? o : run;
+  }
+  if (lane == 63) wmax[w] = run;
+  const int up = __shfl_up(run, 1, 64);
+  __syncthreads();
+  int prev = -1;
+  for (uint32_t q = 0; q < w; ++q) prev = wmax[q] > prev ? wmax[q] : prev;
+  if (lane > 0 && up > prev) prev = up;
+  uint32_t flags = 0, nf = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    const int win = (int)(start[q] / BS_WIN);
+    if (c[q] && (win != prev || c[q] > BS_WIN)) { flags |= 1u << q; ++nf; }
+    if (c[q]) prev = win;
+  }
+  const uint32_t fin = rb_wave_incl_scan(nf);
+  if (lane == 63) wsum[w] = fin;
+  __syncthreads();
+  uint32_t fo = fin - nf, nseg = 0;
+  for (uint32_t q = 0; q < 16; ++q) {
+    if (q < w) fo += wsum[q];
+    nseg += wsum[q];
+  }
+#pragma unroll
+  for (int q = 0; q < PER; ++q)
+    if (flags & (1u << q)) seg[fo++] = start[q];
+  if (tid == 0) seg[nseg] = n;
+  // keys to their buckets
+#pragma unroll
+  for (int r = 0; r < ROWS; ++r) {
+    if (1024u * (uint32_t)r + tid < n) {
+      const uint32_t to = atomicAdd(&sh.o.cur[bs_bucket(k[r])], 1u);
+      if (to < BS_ONE) { sh.o.k[to] = k[r]; sh.o.v[to] = v[r]; }
+    }
+  }
+  __syncthreads();
+  for (uint32_t i = w; i < nseg; i += 16) {
+    const uint32_t x = seg[i], y = seg[i + 1];
+    if (y - x <= BS_WAVE_MAX) bs_wave(sh.o.k, sh.o.v, x, k0, v0, st + x, y - x, lane);
+  }
+  const uint32_t big = n_big;
+  if (big == 0) return;  // uniform
+  for (uint32_t i = 0; i < big; ++i)
+    for (uint32_t j = s_big[i][0] + tid; j < s_big[i][1]; j += 1024) {
+      k1[st + j] = sh.o.k[j];
+      v1[st + j] = sh.o.v[j];
+    }
+  __syncthreads();
+  for (uint32_t i = 0; i < big; ++i)
+    bs_split<1024>(k1, v1, k0, v0, st + s_big[i][0], st + s_big[i][1], sh.split);
+}
+
 hipError_t launch_bsort(rb_ctx *c) {
   const uint32_t n = (uint32_t)c->h_starts[c->P];
   if (n == 0) return hipSuccess;
+  if (c->sort_largest <= BS_ONE) {
+    hipLaunchKernelGGL(k_bsort_one, dim3(c->P), dim3(1024), 0, c->stream, c->d_key[1], c->d_idx[1],
+                       c->d_key[0], c->d_idx[0], c->d_starts, c->d_bcnt);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_bsort_scan, dim3(c->P), dim3(1024), 0, c->stream, c->d_bcnt, c->d_bcur,
                      c->d_starts, c->d_bseg, c->d_bbig, c->d_bctl);
   hipLaunchKernelGGL(k_bsort_scatter, dim3(rb_div_up(n, 256)), dim3(256), 0, c->stream,

@@ -94,11 +94,17 @@ __global__ __launch_bounds__(64) void k_topo_count(
     }
   }
   if (lane < RB_NLEV) {
-    cnt[(size_t)lane * n_tiles + b] = cs;
-    cnt[(size_t)(RB_NLEV + lane) * n_tiles + b] = ce;
+    // by level, or by tile where k_topo_write adds the tiles up itself
+    const size_t at = n_tiles <= RB_TOPO_FEW ? (size_t)b * 2 * RB_NLEV + lane
+                                             : (size_t)lane * n_tiles + b;
+    const size_t ends = n_tiles <= RB_TOPO_FEW ? RB_NLEV : (size_t)RB_NLEV * n_tiles;
+    cnt[at] = cs;
+    cnt[at + ends] = ce;
   }
 }
 
+// FEW: the tiles' counts are added up here (and held in registers)
+template <bool FEW>
 __global__ __launch_bounds__(64) void k_topo_write(
     const uint64_t *__restrict__ key, const uint32_t *__restrict__ tile_start,
     const uint32_t *__restrict__ tile_end, const uint32_t *__restrict__ tile_patch,
@@ -122,7 +128,27 @@ __global__ __launch_bounds__(64) void k_topo_write(
     return;
   }
   // level offsets: lane l holds the first node of level l
-  const uint32_t tot = (lane < RB_NLEV) ? lev_tot[lane] : 0u;
+  uint32_t tot = 0, before_s = 0, before_e = 0;  // of level l: nodes, starts and ends in earlier tiles
+  if (FEW) {
+    uint32_t before = 0;  // lanes 0..21 the starts, 22..43 the ends
+    const uint32_t col = lane < 2 * RB_NLEV ? lane : 0u;
+    uint32_t v[RB_TOPO_FEW];  // all requested at once
+#pragma unroll
+    for (uint32_t t = 0; t < RB_TOPO_FEW; ++t)
+      v[t] = t < n_tiles ? cnt[(size_t)t * 2 * RB_NLEV + col] : 0u;
+#pragma unroll
+    for (uint32_t t = 0; t < RB_TOPO_FEW; ++t) {
+      tot += v[t];
+      before += t < b ? v[t] : 0u;
+    }
+    before_s = before;
+    before_e = __shfl(before, lane < RB_NLEV ? (int)(RB_NLEV + lane) : 0, 64);
+    if (lane >= RB_NLEV) tot = 0;
+  } else if (lane < RB_NLEV) {
+    tot = lev_tot[lane];
+    before_s = cnt[(size_t)lane * n_tiles + b];
+    before_e = cnt[(size_t)(RB_NLEV + lane) * n_tiles + b];
+  }
   const uint32_t lincl = rb_wave_incl_scan(tot);
   const uint32_t lbase_lane = lincl - tot;
   const uint32_t total = __shfl(lincl, 63, 64);
@@ -145,8 +171,8 @@ __global__ __launch_bounds__(64) void k_topo_write(
   // per level (lane l): first node of this tile's starts and ends
   uint32_t off_s = 0, off_e = 0;
   if (lane < RB_NLEV) {
-    off_s = lbase_lane + cnt[(size_t)lane * n_tiles + b];
-    off_e = lbase_lane + cnt[(size_t)(RB_NLEV + lane) * n_tiles + b];
+    off_s = lbase_lane + before_s;
+    off_e = lbase_lane + before_e;
   }
   const uint32_t lend_lane = lincl;  // one past the last node of level `lane`
   const uint32_t p = tile_patch[b], st = starts[p], nl = nlive[p];
@@ -242,14 +268,22 @@ hipError_t launch_topology(rb_ctx *c, const uint32_t *reuse) {
   hipLaunchKernelGGL(k_topo_count, dim3(c->n_tiles), dim3(64), 0, c->stream, c->d_key[0],
                      c->d_tile_start, c->d_tile_end, c->d_tile_patch, c->d_starts, c->d_nlive, L,
                      nv, c->n_tiles, c->d_cnt, reuse);
-  hipError_t e = launch_rowscan_levels(c, reuse);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_topo_write, dim3(c->n_tiles), dim3(64), 0, c->stream, c->d_key[0],
-                     c->d_tile_start, c->d_tile_end, c->d_tile_patch, c->d_starts, c->d_nlive,
-                     c->P, L, nv, c->n_tiles, c->d_cnt, c->d_lev_tot, (uint32_t)c->node_cap,
-                     c->d_lev_off, c->d_nfirst, c->d_nlast, c->d_nchild, c->d_nlastchild,
-                     c->d_nskip, c->d_nlevel, c->d_nleaf, c->d_root, c->d_err, c->d_gctr,
-                     c->d_large_cnt, c->d_csr, c->d_start_ids, reuse, c->d_stats);
+  if (c->n_tiles > RB_TOPO_FEW) {
+    const hipError_t e = launch_rowscan_levels(c, reuse);
+    if (e != hipSuccess) return e;
+  }
+#define RB_TOPO_ARGS                                                                           \
+      c->d_key[0], c->d_tile_start, c->d_tile_end, c->d_tile_patch, c->d_starts, c->d_nlive,   \
+      c->P, L, nv, c->n_tiles, c->d_cnt, c->d_lev_tot, (uint32_t)c->node_cap, c->d_lev_off,    \
+      c->d_nfirst, c->d_nlast, c->d_nchild, c->d_nlastchild, c->d_nskip, c->d_nlevel,          \
+      c->d_nleaf, c->d_root, c->d_err, c->d_gctr, c->d_large_cnt, c->d_csr, c->d_start_ids,    \
+      reuse, c->d_stats
+  const dim3 grid(c->n_tiles), block(64);
+  if (c->n_tiles <= RB_TOPO_FEW)
+    hipLaunchKernelGGL(k_topo_write<true>, grid, block, 0, c->stream, RB_TOPO_ARGS);
+  else
+    hipLaunchKernelGGL(k_topo_write<false>, grid, block, 0, c->stream, RB_TOPO_ARGS);
+#undef RB_TOPO_ARGS
   return hipGetLastError();
 }
 

@@ -208,6 +208,7 @@ int build_layout(rb_ctx *c) {
     for (uint32_t p = 0; p < P; ++p)
       largest = std::max<uint64_t>(largest, c->h_starts[p + 1] - c->h_starts[p]);
     c->sort_small = largest <= c->small_sort_max;
+    c->sort_largest = largest;
     // workgroups of k_bsort_local: sixteen waves split a large bucket sooner,
     // four spread the rest better (with 4 / 16, spheres of 50,000 447 / 414
     // us, 260,000 1370 / 1195; four steps of sheets of 50,000 643 / 649 us,

@@ -99,6 +99,7 @@ struct rb_ctx {
   // small systems: bucket sort (k_bsort.hip)
   bool sort_small = false;
   uint64_t small_sort_max = 0;  // largest patch the bucket sort takes
+  uint64_t sort_largest = 0;    // slots of the largest patch
   int sort_threads = 256;       // threads per workgroup of k_bsort_local
   uint32_t *d_bcnt = nullptr;   // P x 4097 bucket counts (zero between sorts)
   uint32_t *d_bcur = nullptr;   // P x 4097 scatter cursors
@@ -358,6 +359,10 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // (6,000 particles with two each: 9 %) but batches lose more (eight patches
 // of 2,500 to 5,000 particles, 2 to each item of up to 94: 231 -> 277).
 #define RB_WALK64_SHARES 4u
+// topology tiles whose counts are added up by every tile itself instead of by
+// a launch in between (four steps of sheets: 1,000 particles 404 -> 396 us, 3,000
+// 430 -> 423, 4,096 441 -> 436)
+#define RB_TOPO_FEW 64u
 #define RB_WALK64_SHARED 24u
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot);

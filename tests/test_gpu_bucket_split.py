@@ -49,7 +49,10 @@ def _removed(rng, n):
 CASES = [("plummer", 20000, None), ("plummer70000", 70000, None)] + \
     [(f"cell{k}", 3000, _cell(k)) for k in (511, 512, 513, 1024, 1025, 2900)] + \
     [(f"equal{k}", 3000, _equal(k)) for k in (1, 2, 5, 600)] + \
-    [("geometric", 6000, _geometric), ("removed", 3000, _removed)]
+    [("geometric", 6000, _geometric), ("removed", 3000, _removed)] + \
+    [(f"one{n}", n, None) for n in (1, 2, 64, 65, 1023, 1025, 2047, 2048, 2049, 4096, 4097)] + \
+    [("one_equal", 2048, _equal(1)), ("one_cells", 2048, _cell(1500)),
+     ("one_removed", 1700, _removed)]
 
 
 @pytest.mark.parametrize("name,n,f", CASES, ids=[c[0] for c in CASES])

@@ -259,15 +259,25 @@ __device__ __forceinline__ void rb_sw_test(const SwRec &E, const SwRec &F, int c
   }
 }
 
-#define SW_SUB 16                // lanes per interval
-#define SW_EPB (64 / SW_SUB)     // intervals per workgroup (one wave)
+// Lanes per interval: a plane's intervals have few candidates, a ring's many
+// (ring of 50,000 particles, us, with 16 / 8 / 4 / 2 lanes: 286 / 237 / 208 /
+// 206, of 5,000 128 / 132 / 121 / 131; sheets 219 / 214 / 250 and 114 / 127 /
+// 138; larger workgroups and chunks gain nothing).
+#define SW_SUB(PHI) ((PHI) ? 4 : 16)
 
-// One wave per SW_EPB consecutive sorted live intervals, SW_SUB lanes per
-// interval (lane sub takes every SW_SUB-th candidate).  Image ix = 0: the
+// One wave per 64 / SUB consecutive sorted live intervals, SUB lanes per
+// interval (lane sub takes every SUB-th candidate).  Image ix = 0: the
 // intervals after e that start before it ends, read from chunks of 64
 // staged in LDS.  Then for every ix != 0 the intervals that overlap e once
 // shifted by ix W, read directly (they exist only near the x boundaries),
 // kept when e is the lower caller index.
+// PHI: the angle is periodic, and besides the intervals after e that start
+// before it ends there are those that e reaches through a turn, from the
+// list's start to e's end less 2 pi (they exist only for intervals past pi),
+// left out where either of the two reaches the other directly.  (Both ways
+// from every interval, found by binary search and kept from the lower caller
+// index, 50,000 particles of a ring took 317 us in all.)
+template <bool PHI>
 __global__ __launch_bounds__(64) void k_sw_pairs(
     const uint64_t *__restrict__ key, const uint32_t *__restrict__ orig,
     const double *__restrict__ sx, const double *__restrict__ sy,
@@ -277,13 +287,14 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
     const uint32_t *__restrict__ nlive, const PatchInfo *__restrict__ patch, int ngx, int ngy,
     int boundary, double omega, double t, double dt, SweepGrid g,
     const unsigned long long *__restrict__ lmax_bits, CollQueue Q) {
+  constexpr uint32_t SUB = SW_SUB(PHI);
   __shared__ uint64_t c_key[64];
   __shared__ double c_x[64], c_y[64], c_z[64], c_vx[64], c_vy[64], c_vz[64], c_R[64];
   __shared__ uint32_t c_p[64];
   const uint32_t lane = threadIdx.x;
-  const uint32_t sub = lane % SW_SUB;
-  const uint32_t r0 = blockIdx.x * SW_EPB;
-  const uint32_t r = r0 + lane / SW_SUB;
+  const uint32_t sub = lane % SUB;
+  const uint32_t r0 = blockIdx.x * (64 / SUB);
+  const uint32_t r = r0 + lane / SUB;
   const uint32_t n = nlive[0];
   if (r0 >= n) return;  // uniform over the wave
   const bool act = r < n;
@@ -316,7 +327,7 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
       __syncthreads();
       if (going) {
         const uint32_t hi = min(64u, n - base);
-        for (uint32_t q = ((r + 1 > base) ? r + 1 - base : 0u) + sub; q < hi; q += SW_SUB) {
+        for (uint32_t q = ((r + 1 > base) ? r + 1 - base : 0u) + sub; q < hi; q += SUB) {
           if (c_key[q] > qend) {
             going = false;
             break;
@@ -333,8 +344,22 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
       if (!__syncthreads_or(going)) break;
     }
   }
+  if (PHI) {
+    const uint64_t turn = rb_sw_key(ehi - 2.0 * RB_PI, g);
+    if (act && ehi >= RB_PI) {
+      const uint64_t ke = key[r], qend = rb_sw_key(ehi, g);
+      for (uint32_t f = sub; f < n && key[f] <= turn; f += SUB) {
+        if (f == r || (f > r && key[f] <= qend) || (f < r && ke <= rb_sw_key(shi[f], g))) continue;
+        SwRec F;
+        F.x = sx[f]; F.y = sy[f]; F.z = sz[f];
+        F.vx = svx[f]; F.vy = svy[f]; F.vz = svz[f];
+        F.R = sR[f]; F.p = orig[f];
+        rb_sw_test(E, F, 0, 0, 0, RB_OPEN, W, 0.0, 0.0, dt, mine, nm, Q);
+      }
+    }
+  }
   // images ix != 0 (both ends of the sorted list, near the x boundaries)
-  if (act && ngs > 0) {
+  if (!PHI && act && ngs > 0) {
     // the longest interval, widened against rounding in lo - ix W - L
     const double L =
         __longlong_as_double((long long)lmax_bits[0]) * (1.0 + 1e-9) + 1e-9 * W;
@@ -345,7 +370,7 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
       const double sft = (double)c * W;
       const uint64_t qend = rb_sw_key(ehi - sft, g);
       for (uint32_t f = rb_sw_lower(key, n, rb_sw_key((elo - sft) - L, g)) + sub;
-           f < n && key[f] <= qend; f += SW_SUB) {
+           f < n && key[f] <= qend; f += SUB) {
         const uint32_t pf = orig[f];
         if (pf <= E.p) continue;  // kept from the lower caller index only
         SwRec F;
@@ -353,64 +378,6 @@ __global__ __launch_bounds__(64) void k_sw_pairs(
         F.vx = svx[f]; F.vy = svy[f]; F.vz = svz[f];
         F.R = sR[f]; F.p = pf;
         rb_sw_test(E, F, c, ngx, ngy, boundary, W, sh, omega, dt, mine, nm, Q);
-      }
-    }
-  }
-  rb_coll_rest(mine, nm, Q);
-}
-
-// The azimuthal sweep: one wave per SW_EPB consecutive sorted intervals,
-// SW_SUB lanes per interval.  The angle is periodic, so interval e checks
-// the intervals that overlap it directly (c = 0) or through a turn
-// (c = +-1: its own interval shifted by -c 2 pi): for each c the sorted
-// intervals starting after lo_e - c 2 pi - L and before hi_e - c 2 pi.  A
-// pair is a single pair whatever c (there are no images), so it is kept
-// from its lower caller index, and only for the first c whose range holds
-// it.
-__global__ __launch_bounds__(64) void k_sw_pairs_phi(
-    const uint64_t *__restrict__ key, const uint32_t *__restrict__ orig,
-    const double *__restrict__ sx, const double *__restrict__ sy,
-    const double *__restrict__ sz, const double *__restrict__ svx,
-    const double *__restrict__ svy, const double *__restrict__ svz,
-    const double *__restrict__ sR, const uint32_t *__restrict__ nlive,
-    const PatchInfo *__restrict__ patch, double dt, SweepGrid g,
-    const unsigned long long *__restrict__ lmax_bits, CollQueue Q) {
-  const uint32_t lane = threadIdx.x;
-  const uint32_t sub = lane % SW_SUB;
-  const uint32_t r = blockIdx.x * SW_EPB + lane / SW_SUB;
-  const uint32_t n = nlive[0];
-  const bool act = r < n;
-  const double W = patch[0].W;
-  uint64_t mine[RB_COLL_LOCAL];
-  uint32_t nm = 0;
-  if (act) {
-    SwRec E;
-    E.x = sx[r]; E.y = sy[r]; E.z = sz[r];
-    E.vx = svx[r]; E.vy = svy[r]; E.vz = svz[r];
-    E.R = sR[r]; E.p = orig[r];
-    double elo, ehi;
-    rb_sw_phi_extent(E.x, E.y, E.vx, E.vy, E.R, dt, elo, ehi);
-    const double L = __longlong_as_double((long long)lmax_bits[0]) * (1.0 + 1e-9) + 1e-9;
-    uint64_t qs[3], qe[3];
-    for (int c = -1; c <= 1; ++c) {
-      const double sft = (double)c * 2.0 * RB_PI;
-      qs[c + 1] = rb_sw_key((elo - sft) - L, g);
-      qe[c + 1] = rb_sw_key(ehi - sft, g);
-    }
-    for (int c = -1; c <= 1; ++c) {
-      for (uint32_t f = rb_sw_lower(key, n, qs[c + 1]) + sub; f < n && key[f] <= qe[c + 1];
-           f += SW_SUB) {
-        const uint32_t pf = orig[f];
-        if (pf <= E.p) continue;  // kept from the lower caller index only
-        const uint64_t kf = key[f];
-        bool seen = false;
-        for (int c2 = -1; c2 < c; ++c2) seen |= kf >= qs[c2 + 1] && kf <= qe[c2 + 1];
-        if (seen) continue;
-        SwRec F;
-        F.x = sx[f]; F.y = sy[f]; F.z = sz[f];
-        F.vx = svx[f]; F.vy = svy[f]; F.vz = svz[f];
-        F.R = sR[f]; F.p = pf;
-        rb_sw_test(E, F, 0, 0, 0, RB_OPEN, W, 0.0, 0.0, dt, mine, nm, Q);
       }
     }
   }
@@ -449,16 +416,13 @@ hipError_t launch_sweep_pairs(rb_ctx *c, const rb_particles *pp, const double *r
                      c->d_key[0], c->d_idx[0], pp->x, pp->y, pp->z, pp->vx, pp->vy, pp->vz,
                      radius, c->d_patch, n, phi, dt, s[0], s[1], s[2], s[3], s[4], s[5],
                      c->d_swR, c->d_swhi, c->d_orig[0], c->d_nlive);
-  if (phi) {
-    hipLaunchKernelGGL(k_sw_pairs_phi, dim3(rb_div_up(n, SW_EPB)), dim3(64), 0, c->stream,
-                       c->d_key[0], c->d_orig[0], s[0], s[1], s[2], s[3], s[4], s[5],
-                       c->d_swR, c->d_nlive, c->d_patch, dt, sweep_grid(c, 1), c->d_cmax,
-                       rb_coll_queue(c));
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_sw_pairs, dim3(rb_div_up(n, SW_EPB)), dim3(64), 0, c->stream,
-                     c->d_key[0], c->d_orig[0], s[0], s[1], s[2], s[3], s[4], s[5], c->d_swR,
-                     c->d_swhi, c->d_nlive, c->d_patch, c->p.n_ghost[0], c->p.n_ghost[1],
-                     c->p.boundary, c->p.omega, t, dt, sweep_grid(c, 0), c->d_cmax, rb_coll_queue(c));
+#define RB_SW_ARGS                                                                            \
+  c->d_key[0], c->d_orig[0], s[0], s[1], s[2], s[3], s[4], s[5], c->d_swR, c->d_swhi, c->d_nlive, \
+      c->d_patch, c->p.n_ghost[0], c->p.n_ghost[1], phi ? RB_OPEN : c->p.boundary, c->p.omega, t, \
+      dt, sweep_grid(c, phi), c->d_cmax, rb_coll_queue(c)
+  const dim3 grid(rb_div_up(n, 64 / SW_SUB(phi))), block(64);
+  if (phi) hipLaunchKernelGGL(k_sw_pairs<true>, grid, block, 0, c->stream, RB_SW_ARGS);
+  else hipLaunchKernelGGL(k_sw_pairs<false>, grid, block, 0, c->stream, RB_SW_ARGS);
+#undef RB_SW_ARGS
   return hipGetLastError();
 }

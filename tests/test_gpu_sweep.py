@@ -211,3 +211,16 @@ def test_phi_needs_an_open_box():
                         axis=1)
     finally:
         rb.rb_destroy(ctx)
+
+
+@pytest.mark.parametrize("n,dt", [(2, 3.0), (3, 0.2), (64, 0.5), (65, 3.0), (300, 1.0), (1500, 0.3)])
+def test_phi_long_intervals_match_oracle(orc, n, dt):
+    # trajectories over a large part of the turn, past phi = pi and around the
+    # axis: pairs that reach each other directly, through a turn, or both ways
+    # are each found once
+    pr = inputs.uniform_sphere(n, seed=n)
+    rng = np.random.default_rng(n + 1)
+    pr.vx[:], pr.vy[:], pr.vz[:] = rng.normal(size=(3, n))
+    R = rng.uniform(0.05, 0.1, n) * (1.0 if n > 10 else 6.0)
+    npair, nres, codes = _compare(orc, pr, R, 0.0, dt, 0.5, 5, axis=1)
+    assert len(set(int(c) for c in codes[:npair])) == npair

@@ -74,9 +74,6 @@ __device__ __forceinline__ void coll_wave_sync() {
 #define CG_SCAP 768   // traversal stack entries per wave (node << 5 | image)
 #define CG_RESERVE (7 * RB_DEPTH + 8)
 #define CG_LL 128     // opened-leaf list capacity per wave (tested at >= 64)
-#ifndef CG_SUB
-#define CG_SUB 16     // particles one wave searches for (64 / CG_SUB lanes each)
-#endif
 
 __device__ __forceinline__ double rb_wave_min_d(double v) {
   for (int d = 32; d >= 1; d >>= 1) v = fmin(v, __shfl_xor(v, d, 64));
@@ -139,9 +136,9 @@ __global__ __launch_bounds__(256) void k_coll_geom(
   out[node] = r;
 }
 
-// One wave searches for CG_SUB particles of a work item (consecutive sibling
+// One wave searches for SUB particles of a work item (consecutive sibling
 // subtrees of at most group_size particles; an item is split into parts of
-// CG_SUB slots, one part per wave), 64 / CG_SUB lanes per particle.  Four
+// SUB slots, one part per wave), 64 / SUB lanes per particle.  Four
 // waves per workgroup, parts strided over the grid.
 //
 // STEP: the search at the end of a step, on the tree built mid-step.  The
@@ -151,7 +148,7 @@ __global__ __launch_bounds__(256) void k_coll_geom(
 // every cell's reach widened by D, and a pair found through image k' of the
 // unwrapped positions is the pair through image k' + w_j - w_i of the
 // wrapped ones, where the contact test is evaluated.
-template <bool STEP>
+template <bool STEP, uint32_t SUB>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_coll_detect(
     const WalkItem *__restrict__ items, const WalkItem *__restrict__ items_mid,
     const uint32_t *__restrict__ gctr, uint64_t cap, const double *__restrict__ sx,
@@ -164,7 +161,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
     const uint16_t *__restrict__ wrap, const unsigned long long *__restrict__ disp_bits,
     const double *__restrict__ sched, const uint32_t *__restrict__ ctr, int slot,
     uint32_t P) {
-  constexpr uint32_t NS = 64 / CG_SUB;  // parts per item (items hold <= 64 slots)
+  constexpr uint32_t NS = 64 / SUB;  // parts per item (items hold <= 64 slots)
   __shared__ uint32_t stk_all[4][CG_SCAP];
   __shared__ uint32_t lfa_all[4][CG_LL], lfb_all[4][CG_LL], lsc_all[4][64];
   // staged candidates: position, radius, caller index, image (ix + 8) |
@@ -179,7 +176,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   double *cx_ = cx_all[wv], *cy_ = cy_all[wv], *cz_ = cz_all[wv], *cr_ = cr_all[wv];
   uint32_t *co_ = co_all[wv];
   uint8_t *ck_ = ck_all[wv];
-  const uint32_t pidx = lane % CG_SUB, sub = lane / CG_SUB;
+  const uint32_t pidx = lane % SUB, sub = lane / SUB;
   const uint32_t n_big = gctr[2], n_mid = gctr[3], n_items = n_big + n_mid + gctr[4];
   const double rmax = __longlong_as_double((long long)rmax_bits[0]);
   const double slack = STEP ? __longlong_as_double((long long)disp_bits[0]) : 0.0;
@@ -189,7 +186,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
   const double *s_end = STEP ? sched + (size_t)ctr[slot] * 2 * P + P : nullptr;
   for (uint32_t u = 4u * blockIdx.x + wv; u < n_items * NS; u += 4u * gridDim.x) {
     const WalkItem it = rb_walk_item(items, items_mid, u / NS, n_big, n_mid, cap);
-    const uint32_t s0 = it.start + (u % NS) * CG_SUB;
+    const uint32_t s0 = it.start + (u % NS) * SUB;
     if (s0 >= it.end || it.end - it.start > 64u) continue;  // uniform
     const uint32_t p = it.patch, st = starts[p];
     const uint32_t s = s0 + pidx;
@@ -236,7 +233,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5, 8))) voi
       // test the opened leaves' particles against the lanes' particles: up
       // to 64 leaves at a time, their particles staged in LDS 64 at a time
       // (image-shifted, one load per lane), candidate q then tested by the
-      // lanes with sub = q mod (64 / CG_SUB)
+      // lanes with sub = q mod (64 / SUB)
       if (nl >= 64 || (T == 0 && nl > 0)) {
         for (int lb = 0; lb < nl; lb += 64) {
           const int L = min(64, nl - lb);
@@ -564,15 +561,32 @@ hipError_t launch_coll_prep(rb_ctx *c, const double *radius) {
   return launch_groups(c);
 }
 
+// Particles per wave of the search: few where the waves are too few for the
+// chip, many where they are plenty and share more of the descent (search, us,
+// with 8 / 16 / 32: sheets of 5,000 particles 25 / 35 / 45, 20,000 45 / 43 / 62,
+// 50,000 79 / 65 / 67, in a step 87 / 72 / 91, 200,000 264 / 179 / 144).
+static int coll_sub(uint32_t n) { return n <= 15000 ? 8 : n <= 100000 ? 16 : 32; }
+
+// about one wave per non-empty item part (parts average over half their
+// particles); the loop strides over any others
+static unsigned coll_grid(uint32_t n, int sub) {
+  return std::min(4096u, rb_div_up(n, 4 * (uint64_t)sub / 2));
+}
+
+#define RB_COLL_DETECT(STEP, SUB, ...)                                                      \
+  do {                                                                                      \
+    const dim3 g(coll_grid(n, SUB)), b(256);                                                \
+    if (SUB == 8) hipLaunchKernelGGL((k_coll_detect<STEP, 8>), g, b, 0, c->stream, __VA_ARGS__);        \
+    else if (SUB == 16) hipLaunchKernelGGL((k_coll_detect<STEP, 16>), g, b, 0, c->stream, __VA_ARGS__); \
+    else hipLaunchKernelGGL((k_coll_detect<STEP, 32>), g, b, 0, c->stream, __VA_ARGS__);                \
+  } while (0)
+
 hipError_t launch_coll_detect(rb_ctx *c, const double *radius, double t) {
   const uint32_t n = (uint32_t)c->h_starts[c->P];
   if (n == 0) return hipSuccess;
   CollNode *cells = reinterpret_cast<CollNode *>(c->d_cgeo);
-  // about one wave per non-empty item part (parts average over CG_SUB / 2
-  // particles); the loop strides over any others
-  unsigned ggrid = rb_div_up(n, 4 * CG_SUB / 2);
-  if (ggrid > 4096) ggrid = 4096;
-  hipLaunchKernelGGL(k_coll_detect<false>, dim3(ggrid), dim3(256), 0, c->stream, c->d_witems,
+  const int sub = coll_sub(n);
+  RB_COLL_DETECT(false, sub, c->d_witems,
                      c->d_witems_mid, c->d_gctr, c->cap, c->d_px[0][0], c->d_px[0][1],
                      c->d_px[0][2], c->d_orig[0], radius, c->d_patch, c->d_starts, c->d_nlive,
                      c->d_root, cells, c->p.n_ghost[0], c->p.n_ghost[1], c->p.boundary,
@@ -614,9 +628,8 @@ hipError_t launch_coll_step_search(rb_ctx *c, int buf, int slot) {
   const uint32_t n = (uint32_t)c->h_starts[c->P];
   if (n == 0) return hipSuccess;
   CollNode *cells = reinterpret_cast<CollNode *>(c->d_cgeo);
-  unsigned ggrid = rb_div_up(n, 4 * CG_SUB / 2);
-  if (ggrid > 4096) ggrid = 4096;
-  hipLaunchKernelGGL(k_coll_detect<true>, dim3(ggrid), dim3(256), 0, c->stream, c->d_witems,
+  const int sub = coll_sub(n);
+  RB_COLL_DETECT(true, sub, c->d_witems,
                      c->d_witems_mid, c->d_gctr, c->cap, c->d_px[buf][0], c->d_px[buf][1],
                      c->d_px[buf][2], c->d_orig[buf], c->coll_R, c->d_patch, c->d_starts,
                      c->d_nlive, c->d_root, cells, c->p.n_ghost[0], c->p.n_ghost[1],

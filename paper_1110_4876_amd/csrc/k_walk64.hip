@@ -451,12 +451,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
 // 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
 // 11.6 against 11.4 ms on 64 patches: four waves read a common part of the
-// tree).  The items of small patches are shared by RB_WALK64_SHARES
-// workgroups: all walk the item from the root until the stack holds W64G_SHARE
-// entries for each, the first alone adding what is accepted on the way; then
-// each keeps its own, and writes an accumulator set of its own.
+// tree).  The items of small patches are shared by several workgroups: all
+// walk the item from the root until the stack holds W64G_SHARE entries for
+// each, the first alone adding what is accepted on the way; then each keeps
+// its own, and writes an accumulator set of its own.  (Shares of 4 entries are
+// uneven -- the item's own subtree is one entry -- and of 32 walk too much of
+// the tree together: two per item, 6,000 particles, 357 / 307 / 312 us.)
 #define W64G_ENTRY 16  // bytes per stack entry
-#define W64G_SHARE 4   // stack entries per part when the parts take their shares
+#define W64G_SHARE 8   // stack entries per part when the parts take their shares
 // entries that depth-first descent may need on top of a full stack: one
 // entry popped and at most eight pushed per level
 #define W64G_RESERVE (7 * RB_DEPTH + 8)
@@ -842,8 +844,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   }
   if (w == 0 && s < it.end) {
     a[s] = G * ax; a[cap + s] = G * ay; a[2 * cap + s] = G * az;
-    // the sets that only other items' shares fill
-    for (int q = parts; q < n_sets; ++q) {
+    // the sets that only other items' shares fill, after the last share's
+    for (int q = parts; part == parts - 1 && q < n_sets; ++q) {
       a += 3 * cap;
       a[s] = 0.0; a[cap + s] = 0.0; a[2 * cap + s] = 0.0;
     }

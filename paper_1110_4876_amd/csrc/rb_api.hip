@@ -256,12 +256,15 @@ int build_layout(rb_ctx *c) {
   // item, with its share and the number of shares in `node`)
   const bool shares = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
                       !(c->p.split_images == 1 && c->n_img > 1) &&
-                      c->n_items64 < RB_WALK64_WAVES16 && c->acc_sets >= (int)RB_WALK64_SHARES;
+                      c->n_items64 < RB_WALK64_FULL && c->acc_sets >= (int)RB_WALK64_SHARES;
   c->h_items64.clear();
   c->item_shares = 1;
   for (uint32_t p : order) {
     const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1], np = (s1 - s0 + 63) / 64;
-    const uint32_t k = shares && np <= RB_WALK64_SHARED ? RB_WALK64_SHARES : 1u;
+    const uint32_t k = !shares                      ? 1u
+                       : np <= RB_WALK64_SHARED4 ? RB_WALK64_SHARES
+                       : np <= RB_WALK64_SHARED2 ? 2u
+                                                 : 1u;
     if (np > 0) c->item_shares = std::max(c->item_shares, (int)k);
     for (uint32_t s = s0; s < s1; s += 64)
       for (uint32_t q = 0; q < k; ++q)

@@ -349,21 +349,24 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // in the FP64 walk; four above
 #define RB_WALK64_WAVES16 1024u
 #define RB_WALK64_WAVES8 8192u
-// In launches of sixteen-wave workgroups, RB_WALK64_SHARES of them share each
-// item of a patch of at most RB_WALK64_SHARED items: one fills its CU's FP64
-// units, and so few leave most of the 256 CUs idle.  (By the patch's size, so
-// that a patch of a batch gets the sums that it gets alone.)  Sheets, us, with
-// 1 / 4 per item: gravity of 800 particles (13 items) 135 / 110, 1,500 (24)
-// 145 / 115, two steps of 1,000 295 / 223 (one to each subtree two levels
-// below the root: 124, 148, 259).  Above 24 items single systems still gain
-// (6,000 particles with two each: 9 %) but batches lose more (eight patches
-// of 2,500 to 5,000 particles, 2 to each item of up to 94: 231 -> 277).
+// Below RB_WALK64_FULL items (the sixteen-wave workgroups that the chip holds
+// at once; one fills its CU's FP64 units) several workgroups share each item
+// of a small patch: RB_WALK64_SHARES for a patch of up to RB_WALK64_SHARED4
+// items, two up to RB_WALK64_SHARED2.  (By the patch's size, so that a patch
+// of a batch gets the sums that it gets alone.)  Us with 1 / 2 / 4 per item:
+// two steps of sheets of 1,000 particles (16 items) 312 / 244 / 215, 3,000 370
+// / 278 / 248, 6,000 406 / 307 / 310, 12,000 433 / 381 / 418, 25,000 586 / 586
+// / 636; forces of spheres of 3,000 187 / 168 / 169, 6,000 221 / 207 / 224,
+// 12,000 246 / 250 / 279; eight patches of 1,500 to 3,000 211 / 200 / 221, of
+// 2,500 to 5,000 228 / 241 / 285, sixteen 351 / 391 / 501.
+#define RB_WALK64_FULL 512u
 #define RB_WALK64_SHARES 4u
 // topology tiles whose counts are added up by every tile itself instead of by
 // a launch in between (four steps of sheets: 1,000 particles 404 -> 396 us, 3,000
 // 430 -> 423, 4,096 441 -> 436)
 #define RB_TOPO_FEW 64u
-#define RB_WALK64_SHARED 24u
+#define RB_WALK64_SHARED4 32u
+#define RB_WALK64_SHARED2 128u
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot);
 hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const double *sz,

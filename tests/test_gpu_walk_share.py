@@ -49,11 +49,11 @@ def test_eight_waves_match_one(n):
     _close(_gravity(pr, walk_waves=4, **kw), _gravity(pr, walk_waves=1, **kw), 1e-6)
 
 
-@pytest.mark.parametrize("n", [40, 64, 65, 700, 1536, 1537, 4000])
+@pytest.mark.parametrize("n", [40, 64, 65, 700, 2048, 2049, 8192, 8193])
 @pytest.mark.parametrize("leaf", [1, 4])
 def test_fp64_items_shared_by_workgroups(n, leaf):
-    # up to 24 items of 64 particles: four workgroups an item, against each
-    # lane's own walk.  The sums differ in their order only: at most a few
+    # up to 32 items of 64 particles four workgroups an item, up to 128 two,
+    # against each lane's own walk.  The sums differ in their order only: at most a few
     # thousand FP64 terms (1.1e-16 each), and the in-plane cancellation of a
     # sheet (under 100)
     for pr in (inputs.sheet(n, seed=n).with_params(theta=0.5),
@@ -62,13 +62,13 @@ def test_fp64_items_shared_by_workgroups(n, leaf):
 
 
 def test_shared_items_beside_whole_ones():
-    # a batch of patches under and over 24 items, with one large enough that
+    # a batch of patches under and over 32 and 128 items, and one so large that
     # none is shared: every patch has the lanes' own walks' forces
     import torch
     from gpu_util import Dev
     from paper_1110_4876_amd import rb
     from test_gpu_batch import _batch_ctx, _concat
-    for sizes in ((100, 1536, 1537, 5000, 64), (100, 1536, 66000)):
+    for sizes in ((100, 2048, 2049, 9000, 64), (100, 2048, 33000)):
         ps = [inputs.sheet(n, seed=n).with_params(theta=0.5) for n in sizes]
         big, off = _concat(ps)
         out = []

@@ -537,7 +537,7 @@ def sweep_ring_run(args):
         "search_ms": {k: v[2] for k, v in res.items()},
         "roofline": {"bound": "hbm", "achieved": achieved / 1e9, "peak": 8000.0,
                      "unit": "GB/s", "frac": achieved / 8e12, "traffic": None,
-                     "kernel": "k_sw_gather + k_sw_pairs_phi"},
+                     "kernel": "k_sw_gather + k_sw_pairs"},
         "cpu_baseline": cpu,
     }
     print(json.dumps(out), flush=True)

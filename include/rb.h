@@ -104,7 +104,8 @@ typedef enum { RB_DRIFT_LEAPFROG = 0, RB_DRIFT_EPICYCLE = 1 } rb_drift;
  *                   traversal (1, 2 or 4; 0 selects 1).  More waves shorten
  *                   each group's chain of dependent steps when there are few
  *                   groups for the chip.  (4: eight for up to 320 group_size
- *                   particles, where there are fewer groups still.)
+ *                   particles, where there are fewer groups still, and several
+ *                   workgroups of eight up to 110 group_size.)
  *  moments_level_log2  the moments of the nodes above the walk's work items
  *                   (bottom-up, Sect. 4.2) run in one workgroup for systems
  *                   of up to 2^k slots and level by level over the whole chip

@@ -25,6 +25,7 @@
 #include "rb_internal.h"
 
 #define W32_SCAP 1024  // traversal stack entries per wave (node << 5 | image)
+#define W32M_SHARE 8   // stack entries per workgroup when an item's take their shares
 #define W32_LIST 128   // cell and particle list capacities (64 taken at 64 entries)
 #define W32_RESERVE (7 * RB_DEPTH + 8)
 
@@ -532,7 +533,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // dependent rounds is up to NW times shorter.  A round's entries are dealt
 // evenly: with 64 to each wave in turn the first wave evaluated a small
 // round's list while the others waited (a step of 3,000 particles 121 -> 117
-// us with eight waves, of 50,000 212 -> 206 with four).
+// us with eight waves, of 50,000 212 -> 206 with four).  Few items are shared
+// by several workgroups (`parts`): all walk the item until the stack holds
+// W32M_SHARE entries for each, the first alone adding what is accepted on the
+// way; then each keeps its own, and writes an accumulator set of its own.
 // list capacities of the multi-wave walk: a list is evaluated at the start
 // of a round once it holds W32M_CFLUSH cells (W32M_PFLUSH particles), while
 // that round's node records are in flight; a round adds at most 64 entries
@@ -596,7 +600,7 @@ __device__ __forceinline__ void w32m_eval_parts(const float4 *__restrict__ ppos,
 template <bool QUAD, bool STATS, int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WAVES_PER_EU, 8))) void k_walk32m(
     const WalkItem *__restrict__ groups, const WalkItem *__restrict__ groups_mid,
-    uint32_t *__restrict__ gctr, int img_split, int n_img,
+    uint32_t *__restrict__ gctr, int img_split, int parts, int n_img,
     int ngx, int ngy, int boundary, const PatchInfo *__restrict__ patch,
     const uint32_t *__restrict__ root, const WNode *__restrict__ wn, const double *__restrict__ sx,
     const double *__restrict__ sy, const double *__restrict__ sz,
@@ -620,7 +624,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
   float4 *ppos = ppos_all[w];
   const uint32_t n_big = gctr[2], n_mid = gctr[3];  // walk items by size
   const uint32_t n_groups = n_big + n_mid + gctr[4];
-  const uint32_t per = img_split ? (uint32_t)n_img : 1u;
+  const uint32_t per = img_split ? (uint32_t)n_img : NW < 8 ? 1u : (uint32_t)parts;
   const uint32_t n_items = n_groups * per;
   const double theta2d = theta2;
   const uint32_t step = ctr[slot];
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
   // (which follow the tree's slot order within a level), so its L2 holds
   // their part of the tree, and every XCD gets the same mix of sizes.
   uint32_t item0 = blockIdx.x;
-  if (!img_split && (gridDim.x & 7u) == 0 && n_items + 24u <= gridDim.x) {
+  if (!img_split && (NW < 8 || parts == 1) && (gridDim.x & 7u) == 0 && n_items + 24u <= gridDim.x) {
     const uint32_t x = blockIdx.x & 7u, j = blockIdx.x >> 3;
     const uint32_t n_small = n_groups - n_big - n_mid;
     const uint32_t b0 = n_big * x / 8u, nb = n_big * (x + 1u) / 8u - b0;
@@ -652,7 +656,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
     const uint32_t item = (uint32_t)w32_uniform((int)s_item);
     __syncthreads();  // every thread has read the item before it changes
     if (item >= n_items) break;  // uniform over the block
-    const uint32_t gi = img_split ? item % n_groups : item;
+    // (a split walk has one workgroup per item)
+    const uint32_t gi = img_split ? item % n_groups : NW < 8 ? item : item / (uint32_t)parts;
+    const int part = NW < 8 || img_split ? 0 : (int)(item % (uint32_t)parts);
     const int im0 =
         img_split ? (int)((item / n_groups + (uint32_t)(n_img / 2)) % (uint32_t)n_img) : 0;
     const int nim = img_split ? 1 : n_img;
@@ -700,11 +706,27 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       img[lane] = make_double2(ox, oy);
     }
     int sp = nim;  // every wave keeps the same copy
+    // before the item's workgroups take their shares of the stack, the first
+    // one alone adds
+    // (eight waves only: what the others' compilers see is constant)
+    bool whole = NW == 8 && !img_split && parts > 1, adds = !whole || part == 0;
     int cl = 0, pl = 0;
     bool overflow = false;
     const float gqs = (float)gq_scale;
     __syncthreads();
     for (;;) {
+      if (NW == 8 && whole && sp >= W32M_SHARE * parts && sp <= 64 * NW) {
+        // every workgroup keeps each parts-th entry (neighbours on the stack
+        // are siblings) and adds from here on
+        const int keep = (sp - part + parts - 1) / parts, t = (int)threadIdx.x;
+        const uint32_t en = t < keep ? stk[t * parts + part] : 0u;
+        __syncthreads();
+        if (t < keep) stk[t] = en;
+        __syncthreads();
+        sp = keep;
+        whole = false;
+        adds = true;
+      }
       // this round's batch: the top T entries, 64 per wave
       int T = sp < 64 * NW ? sp : 64 * NW;
       if (sp + 7 * T > W32M_SCAP - W32_RESERVE) {
@@ -783,8 +805,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       sp = overflow ? 0 : base + (int)all;
       // accepted cells
       {
-        const uint64_t m = __ballot(accept);
-        if (accept) {
+        const uint64_t m = adds ? __ballot(accept) : 0ull;
+        if (accept && adds) {
           const int pos = cl + (int)rb_mbcnt(m);
           cel[pos].pos = make_float4((float)((cx - gx) * invW), (float)((cy - gy) * invW),
                                      (float)((cz - gz) * invW), (float)(mc.w * gm_scale));
@@ -797,8 +819,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       }
       // single-particle leaves
       {
-        const uint64_t m = __ballot(single);
-        if (single) {
+        const uint64_t m = adds ? __ballot(single) : 0ull;
+        if (single && adds) {
           const int pos = pl + (int)rb_mbcnt(m);
           ppos[pos] = make_float4((float)((cx - gx) * invW), (float)((cy - gy) * invW),
                                   (float)((cz - gz) * invW), (float)(mc.w * gm_scale));
@@ -806,7 +828,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
         pl += __popcll(m);
       }
       // opened bucket leaves: the wave expands them one after another
-      uint64_t bm = __ballot(open_leaf);
+      uint64_t bm = adds ? __ballot(open_leaf) : 0ull;
       while (bm) {
         const int src = __ffsll((long long)bm) - 1;
         bm &= bm - 1;
@@ -859,7 +881,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
           tz += s_red[q][2][lane + k * cnt];
         }
       }
-      double *a = acc + (size_t)(img_split ? im0 : 0) * 3 * cap;
+      double *a = acc + (size_t)(im0 + part) * 3 * cap;
       a[s] = tx; a[cap + s] = ty; a[2 * cap + s] = tz;
     }
     __syncthreads();  // s_red and the stack are reused by the next item
@@ -882,28 +904,24 @@ hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const do
   if (grid > max_items) grid = max_items;
   const double th2 = c->p.theta * c->p.theta;
   const bool quad = c->p.quadrupole != 0, stats = (c->p.profile & 2) != 0;
-#define RB_W32_ARGS                                                                      \
-  c->d_witems, c->d_witems_mid, c->d_gctr, c->img_split, c->n_img, c->p.n_ghost[0],      \
+#define RB_W32_ARGS(...)                                                                      \
+  c->d_witems, c->d_witems_mid, c->d_gctr, c->img_split, __VA_ARGS__ c->n_img, c->p.n_ghost[0], \
       c->p.n_ghost[1],                                                                    \
       c->p.boundary, c->d_patch, c->d_root, c->d_wnode, sx,                               \
       sy, sz,                                                                             \
       c->d_msrc, c->d_sched, c->d_ctr, c->P, c->p.G, c->p.softening, th2, c->d_acc,       \
       c->cap, c->d_stats, c->d_err, slot
-  // Four waves asked for, and too few items for the chip (a group holds 30 to
-  // 40 of its 64 particles): eight.  A sheet's step, us, with 4 / 8 waves:
-  // 3,000 particles 133 / 116, 16,000 155 / 147, 24,000 155 / 165; G = 32:
-  // 10,000 125 / 122, 30,000 170 / 199.  (Sixteen lose to eight throughout.)
-  int nw = c->p.walk_waves;
-  if (nw == 4 && max_items <= 320ull * (uint64_t)c->p.group_size) nw = 8;
+  const int nw = c->walk32_waves;
   if (nw >= 2) {
     // persistent grid of workgroups
     uint64_t gridm = 256ull * (nw == 2 ? 12ull : nw == 4 ? 6ull : 3ull);
-    if (gridm > max_items) gridm = max_items;
+    const int parts = c->walk_parts;
+    if (gridm > max_items * (uint64_t)parts) gridm = max_items * (uint64_t)parts;
     const dim3 gm((unsigned)gridm), bm(64 * nw);
 #define RB_W32M(Q, S)                                                                   \
-  if (nw == 2) hipLaunchKernelGGL((k_walk32m<Q, S, 2>), gm, bm, 0, c->stream, RB_W32_ARGS); \
-  else if (nw == 4) hipLaunchKernelGGL((k_walk32m<Q, S, 4>), gm, bm, 0, c->stream, RB_W32_ARGS); \
-  else hipLaunchKernelGGL((k_walk32m<Q, S, 8>), gm, bm, 0, c->stream, RB_W32_ARGS);
+  if (nw == 2) hipLaunchKernelGGL((k_walk32m<Q, S, 2>), gm, bm, 0, c->stream, RB_W32_ARGS(parts, )); \
+  else if (nw == 4) hipLaunchKernelGGL((k_walk32m<Q, S, 4>), gm, bm, 0, c->stream, RB_W32_ARGS(parts, )); \
+  else hipLaunchKernelGGL((k_walk32m<Q, S, 8>), gm, bm, 0, c->stream, RB_W32_ARGS(parts, ));
     if (quad && stats) { RB_W32M(true, true) }
     else if (quad) { RB_W32M(true, false) }
     else if (stats) { RB_W32M(false, true) }
@@ -913,13 +931,13 @@ hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const do
   }
   const dim3 g4((unsigned)((grid + 3) / 4)), b4(256);  // four waves per workgroup
   if (quad && stats)
-    hipLaunchKernelGGL((k_walk32<true, true>), g4, b4, 0, c->stream, RB_W32_ARGS);
+    hipLaunchKernelGGL((k_walk32<true, true>), g4, b4, 0, c->stream, RB_W32_ARGS());
   else if (quad)
-    hipLaunchKernelGGL((k_walk32<true, false>), g4, b4, 0, c->stream, RB_W32_ARGS);
+    hipLaunchKernelGGL((k_walk32<true, false>), g4, b4, 0, c->stream, RB_W32_ARGS());
   else if (stats)
-    hipLaunchKernelGGL((k_walk32<false, true>), g4, b4, 0, c->stream, RB_W32_ARGS);
+    hipLaunchKernelGGL((k_walk32<false, true>), g4, b4, 0, c->stream, RB_W32_ARGS());
   else
-    hipLaunchKernelGGL((k_walk32<false, false>), g4, b4, 0, c->stream, RB_W32_ARGS);
+    hipLaunchKernelGGL((k_walk32<false, false>), g4, b4, 0, c->stream, RB_W32_ARGS());
 #undef RB_W32_ARGS
   return hipGetLastError();
 }

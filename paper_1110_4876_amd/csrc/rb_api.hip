@@ -165,6 +165,24 @@ void set_split(rb_ctx *c) {
   c->walk64_mode = mode;
   c->walk_parts = (fp64 && mode == 3) ? parts : 1;
   if (fp64 && mode == 0 && !c->img_split) c->walk_parts = c->item_shares;
+  // FP32-mixed: eight waves per item where four are asked for and the items
+  // are too few for the chip (a group holds 30 to 40 of its 64 particles).  A
+  // sheet's step, us, with 4 / 8 waves: 3,000 particles 133 / 116, 16,000 155
+  // / 147, 24,000 155 / 165; G = 32: 10,000 125 / 122, 30,000 170 / 199.
+  // (Sixteen lose to eight throughout.)
+  c->walk32_waves = c->p.walk_waves;
+  const uint64_t units = (uint64_t)c->h_starts[c->P] * (c->img_split ? (uint64_t)c->n_img : 1ull);
+  if (!fp64 && c->p.walk_waves == 4 && units <= 320ull * (uint64_t)c->p.group_size) {
+    c->walk32_waves = 8;
+    // ... and workgroups per item, where the items leave CUs idle (four steps
+    // of sheets, us, with 1 / 2 / 4: 1,000 particles 410 / 370 / 354, 3,000 449
+    // / 413 / 398, 6,000 463 / 431 / 440, 9,000 494 / 484 / 571, at theta 0.5
+    // 452 / 455 / 544; of spheres 3,000 594 / 580 / 592, 6,000 764 / 697 / 852,
+    // 9,000 850 / 898 / 941)
+    const uint64_t g = (uint64_t)c->p.group_size;
+    if (!c->img_split && c->acc_sets >= 4)
+      c->walk_parts = units <= 56 * g ? 4 : units <= 110 * g ? 2 : 1;
+  }
 }
 
 // tiles of RB_TILE slots inside each patch; walk items of `g` slots

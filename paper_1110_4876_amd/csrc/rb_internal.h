@@ -69,6 +69,7 @@ struct rb_ctx {
   int walk64_mode = 0;
   int walk64_waves = 4;
   int walk_parts = 1;
+  int walk32_waves = 1;      // waves per item of the grouped walk
   int acc_sets = 1;          // sets of 3 * cap doubles that d_acc holds
 
   // host mirrors

@@ -40,12 +40,14 @@ def test_one_wave_matches_two(n, G, leaf):
     _close(_gravity(pr, walk_waves=1, **kw), _gravity(pr, walk_waves=2, **kw), 1e-6)
 
 
-@pytest.mark.parametrize("n", [63, 64, 65, 1000, 5120, 5121])
-def test_eight_waves_match_one(n):
-    # walk_waves = 4 runs eight waves per item up to 320 G particles, four above
+@pytest.mark.parametrize("n", [63, 64, 65, 896, 897, 1760, 1761, 5120, 5121])
+@pytest.mark.parametrize("leaf", [1, 8])
+def test_eight_waves_match_one(n, leaf):
+    # walk_waves = 4 runs eight waves per item up to 320 G particles, four
+    # above, and four workgroups per item up to 56 G, two up to 110 G
     from paper_1110_4876_amd import rb
     pr = inputs.sheet(n, seed=3).with_params(theta=0.4)
-    kw = dict(precision=rb.RB_FP32_MIXED, group_size=16)
+    kw = dict(precision=rb.RB_FP32_MIXED, group_size=16, leaf_size=leaf)
     _close(_gravity(pr, walk_waves=4, **kw), _gravity(pr, walk_waves=1, **kw), 1e-6)
 
 

@@ -18,89 +18,24 @@
 // every node's children are contiguous.
 //
 // One wave handles one tile of consecutive slots: count starts and ends per
-// level (k_topo_count), scan the counts (rowscan), then write every node's
+// level (with the permutation, which needs the same sorted keys, or
+// k_topo_count), scan the counts (rowscan), then write every node's
 // first slot, last slot, first and last child and skip pointer
 // (k_topo_write).  k_topo_write also lists the nodes slot by slot:
 // start_ids[csr[s] + (l - first start level of s)] is the node of level l
 // starting at slot s, so the moments can find a subtree's nodes from its
 // slots without walking down the levels.
-#include "rb_internal.h"
+#include "rb_topo.h"
 
-struct TopoRange {
-  int lo_s, hi_s, lo_e, hi_e;  // start and end level ranges (empty if lo > hi)
-};
-
-__device__ __forceinline__ TopoRange rb_topo_range(const uint64_t *__restrict__ key,
-                                                   uint32_t st, uint32_t i, uint32_t nl, int L,
-                                                   int nvirt) {
-  const uint64_t *k = key + st;
-  int lf = 0;
-  if (nl > (uint32_t)L) {
-    int D = 0;
-    const uint32_t jlo = (i >= (uint32_t)L) ? i - L : 0u;
-    const uint32_t jhi = (i <= nl - 1 - L) ? i : nl - 1 - L;
-    for (uint32_t j = jlo; j <= jhi; ++j) {
-      const int v = rb_lcp(k[j], k[j + L]);
-      D = v > D ? v : D;
-    }
-    lf = D + 1 < RB_DEPTH ? D + 1 : RB_DEPTH;
-  }
-  // the cells above the root boxes are never leaves: every occupied one
-  // exists down to its root box (the root of that box's own tree)
-  if (lf < nvirt) lf = nvirt;
-  TopoRange r;
-  r.lo_s = (i == 0) ? 0 : rb_lcp(k[i - 1], k[i]) + 1;
-  r.hi_s = lf;
-  r.lo_e = (i + 1 == nl) ? 0 : rb_lcp(k[i], k[i + 1]) + 1;
-  r.hi_e = lf;
-  return r;
-}
-
-// the levels at which any lane of the wave starts or ends a node
-__device__ __forceinline__ void rb_topo_levels(const TopoRange &tr, bool valid, int &lmin,
-                                               int &lmax) {
-  lmin = valid ? min(tr.lo_s, tr.lo_e) : RB_NLEV;
-  lmax = valid ? max(tr.hi_s, tr.hi_e) : -1;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    lmin = min(lmin, __shfl_xor(lmin, d, 64));
-    lmax = max(lmax, __shfl_xor(lmax, d, 64));
-  }
-}
-
-__global__ __launch_bounds__(64) void k_topo_count(
-    const uint64_t *__restrict__ key, const uint32_t *__restrict__ tile_start,
-    const uint32_t *__restrict__ tile_end, const uint32_t *__restrict__ tile_patch,
-    const uint32_t *__restrict__ starts, const uint32_t *__restrict__ nlive, int L,
-    int nvirt, uint32_t n_tiles, uint32_t *__restrict__ cnt, const uint32_t *__restrict__ reuse) {
-  if (reuse && *reuse == 0u) return;  // the step keeps the last tree
-  const uint32_t b = blockIdx.x, lane = threadIdx.x;
-  const uint32_t p = tile_patch[b], st = starts[p], nl = nlive[p];
-  const uint32_t s0 = tile_start[b], s1 = tile_end[b];
-  uint32_t cs = 0, ce = 0;  // lane l < 22 keeps the counts of level l
-  for (uint32_t r0 = s0; r0 < s1; r0 += 64) {
-    const uint32_t s = r0 + lane;
-    const bool valid = s < s1 && (s - st) < nl;
-    TopoRange tr = {1, 0, 1, 0};
-    if (valid) tr = rb_topo_range(key, st, s - st, nl, L, nvirt);
-    int lmin, lmax;
-    rb_topo_levels(tr, valid, lmin, lmax);
-#pragma unroll
-    for (int l = 0; l < RB_NLEV; ++l) {
-      if (l < lmin || l > lmax) continue;  // uniform: nothing starts or ends here
-      const uint32_t ns = (uint32_t)__popcll(__ballot(l >= tr.lo_s && l <= tr.hi_s));
-      const uint32_t ne = (uint32_t)__popcll(__ballot(l >= tr.lo_e && l <= tr.hi_e));
-      if (lane == (uint32_t)l) { cs += ns; ce += ne; }
-    }
-  }
-  if (lane < RB_NLEV) {
-    // by level, or by tile where k_topo_write adds the tiles up itself
-    const size_t at = n_tiles <= RB_TOPO_FEW ? (size_t)b * 2 * RB_NLEV + lane
-                                             : (size_t)lane * n_tiles + b;
-    const size_t ends = n_tiles <= RB_TOPO_FEW ? RB_NLEV : (size_t)RB_NLEV * n_tiles;
-    cnt[at] = cs;
-    cnt[at + ends] = ce;
-  }
+// (steps that may keep their tree; otherwise the permutation's launch counts)
+__global__ __launch_bounds__(64) void k_topo_count(const uint64_t *__restrict__ key,
+                                                   const uint32_t *__restrict__ starts,
+                                                   const uint32_t *__restrict__ nlive,
+                                                   TopoCount t,
+                                                   const uint32_t *__restrict__ reuse) {
+  if (*reuse == 0u) return;  // the step keeps the last tree
+  const uint32_t p = t.tile_patch[blockIdx.x];
+  rb_topo_count_tile(t, blockIdx.x, threadIdx.x, key, starts[p], nlive[p]);
 }
 
 // FEW: the tiles' counts are added up here (and held in registers)
@@ -265,9 +200,9 @@ hipError_t launch_topology(rb_ctx *c, const uint32_t *reuse) {
   if (n == 0 || c->n_tiles == 0) return hipSuccess;
   const int L = c->p.leaf_size;
   const int nv = (int)c->h_patch[0].nvirt;
-  hipLaunchKernelGGL(k_topo_count, dim3(c->n_tiles), dim3(64), 0, c->stream, c->d_key[0],
-                     c->d_tile_start, c->d_tile_end, c->d_tile_patch, c->d_starts, c->d_nlive, L,
-                     nv, c->n_tiles, c->d_cnt, reuse);
+  if (reuse)
+    hipLaunchKernelGGL(k_topo_count, dim3(c->n_tiles), dim3(64), 0, c->stream, c->d_key[0],
+                       c->d_starts, c->d_nlive, rb_topo_tiles(c), reuse);
   if (c->n_tiles > RB_TOPO_FEW) {
     const hipError_t e = launch_rowscan_levels(c, reuse);
     if (e != hipSuccess) return e;

@@ -120,7 +120,8 @@ hipError_t launch_permute_gravity(rb_ctx *c, const double *x, const double *y,
 // later from the last step's sorted arrays (whose order changes little).
 // Bound by HBM lines: one per particle and step from records (278 us on
 // 8.9e6 particles, 317 on 8.4e6), where seven arrays in the caller's order took
-// seven (748 and 1337 us).
+// seven (748 and 1337 us).  With the tiles' counts in the launch 359 and 400 us,
+// as the two launches took (355 and 395); on 1e6 particles 50 for 57 us.
 __global__ __launch_bounds__(256) void k_permute_state(
     const uint64_t *__restrict__ key, const uint32_t *__restrict__ idx,
     const double *__restrict__ ax, const double *__restrict__ ay,

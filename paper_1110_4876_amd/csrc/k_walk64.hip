@@ -451,7 +451,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
 // 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
 // 11.6 against 11.4 ms on 64 patches: four waves read a common part of the
-// tree).  The items of small patches are shared by several workgroups: all
+// tree).  The items of small patches, and the last ones of larger patches that
+// an XCD is dealt, are shared by several workgroups (rb_internal.h): all
 // walk the item from the root until the stack holds W64G_SHARE entries for
 // each, the first alone adding what is accepted on the way; then each keeps
 // its own, and writes an accumulator set of its own.  (Shares of 4 entries are
@@ -592,8 +593,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   // the item's workgroups, and which of them this is (a split walk has one);
   // before they take their shares of the stack, the first one alone adds
   const int parts = (int)(it.node >> 8), part = (int)(it.node & 255u);
-  // (sixteen waves only: what the others' compilers see is constant)
-  bool whole = NW == 16 && parts > 1, adds = !whole || part == 0;
+  // (eight and sixteen waves only: what four's compiler sees is constant)
+  bool whole = NW >= 8 && parts > 1, adds = !whole || part == 0;
   const uint32_t p = it.patch;
   const double W = patch[p].W;
   // (W 2^-l)^2 = fl(W W) 2^-2l exactly: scaling by a power of two is exact
@@ -644,7 +645,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   };
   w64g_sync<NW>();
   for (;;) {
-    if (NW == 16 && whole && sp >= W64G_SHARE * parts && sp <= 64 * NW) {
+    if (NW >= 8 && whole && sp >= W64G_SHARE * parts && sp <= 64 * NW) {
       // every part keeps each parts-th entry (neighbours on the stack are
       // siblings) and adds from here on
       const int keep = (sp - part + parts - 1) / parts;

@@ -272,21 +272,33 @@ int build_layout(rb_ctx *c) {
   for (uint32_t p = 0; p < P; ++p) c->n_items64 += (c->h_starts[p + 1] - c->h_starts[p] + 63) / 64;
   // (the rounds of the FP64 walk: an entry for every workgroup that shares the
   // item, with its share and the number of shares in `node`)
-  const bool shares = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
+  const bool rounds = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
                       !(c->p.split_images == 1 && c->n_img > 1) &&
-                      c->n_items64 < RB_WALK64_FULL && c->acc_sets >= (int)RB_WALK64_SHARES;
+                      c->acc_sets >= (int)RB_WALK64_SHARES;
+  const bool few = rounds && c->n_items64 < RB_WALK64_FULL;
+  // smallest patch of whose eighths (an XCD each) the last items are shared
+  const uint32_t ends = !rounds                             ? RB_NONE
+                        : c->n_items64 < RB_WALK64_WAVES16 ? RB_WALK64_ENDS16
+                        : c->n_items64 < RB_WALK64_WAVES8  ? RB_WALK64_ENDS8
+                                                           : RB_NONE;
+  const uint32_t n_end = c->n_items64 < RB_WALK64_WAVES16 ? 4u : 8u;
   c->h_items64.clear();
   c->item_shares = 1;
   for (uint32_t p : order) {
     const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1], np = (s1 - s0 + 63) / 64;
-    const uint32_t k = !shares                      ? 1u
-                       : np <= RB_WALK64_SHARED4 ? RB_WALK64_SHARES
-                       : np <= RB_WALK64_SHARED2 ? 2u
-                                                 : 1u;
-    if (np > 0) c->item_shares = std::max(c->item_shares, (int)k);
-    for (uint32_t s = s0; s < s1; s += 64)
-      for (uint32_t q = 0; q < k; ++q)
-        c->h_items64.push_back({s, std::min<uint32_t>(s + 64, s1), p, (k << 8) | q});
+    const uint32_t k = !few || np > RB_WALK64_SHARED2 ? 1u
+                       : np <= RB_WALK64_SHARED4      ? RB_WALK64_SHARES
+                                                      : 2u;
+    uint32_t i = 0;
+    for (uint32_t x = 0; x < 8; ++x) {  // (eighths as the kernel deals a single patch's units)
+      const uint32_t i1 = i + np / 8 + (x < np % 8 ? 1u : 0u);
+      for (; i < i1; ++i) {
+        const uint32_t s = s0 + 64 * i, ki = np >= ends && i + n_end >= i1 ? 2u : k;
+        c->item_shares = std::max(c->item_shares, (int)ki);
+        for (uint32_t q = 0; q < ki; ++q)
+          c->h_items64.push_back({s, std::min<uint32_t>(s + 64, s1), p, (ki << 8) | q});
+      }
+    }
   }
   if (c->h_items64.size() > c->cap / 16 + RB_WALK64_SHARES * (uint64_t)P + 8)
     return fail(RB_ECAPACITY, "walk item table overflow");

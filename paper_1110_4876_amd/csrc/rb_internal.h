@@ -362,12 +362,26 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // 2,500 to 5,000 228 / 241 / 285, sixteen 351 / 391 / 501.
 #define RB_WALK64_FULL 512u
 #define RB_WALK64_SHARES 4u
+#define RB_WALK64_SHARED4 32u
+#define RB_WALK64_SHARED2 128u
+// Larger patches: the last items that each XCD is dealt of a patch have two
+// workgroups each, so that its CUs end closer together (their last items are a
+// large part of the walk: 98 items of 50,000 particles for the 64 workgroups of
+// an XCD).  Four items of an XCD with sixteen waves and a patch of more items
+// than CUs (three patches of 10,000 particles, 160 items each, lose: 238 / 274
+// us with none / 4; three of 18,000 368 / 355), eight with eight waves and a
+// patch of RB_WALK64_ENDS8 items.  Two steps of sheets, us, with none / 4 / 8 /
+// 16: 18,000 particles 526 / 427 / 434 / 445, 30,000 564 / 531 / 582 / 593, 50,000 836 / 738 / 755 / 752, 64,000 904 / 904
+// / 901 / 915; with eight waves 100,000 1317 / 1192 / 1152 / 1149, 250,000 2589
+// / 2550 / 2461 / 2452; forces of spheres of 60,000 705 / 684 / 687 / 740,
+// 100,000 910 / 878 / 876 / 910, 200,000 1567 / 1561 / 1559 / 1574.  (With four
+// waves 64 items gain 1.3% on 1,048,583 particles and lose 1.2% on 700,000.)
+#define RB_WALK64_ENDS16 257u
+#define RB_WALK64_ENDS8 1024u
 // topology tiles whose counts are added up by every tile itself instead of by
 // a launch in between (four steps of sheets: 1,000 particles 404 -> 396 us, 3,000
 // 430 -> 423, 4,096 441 -> 436)
 #define RB_TOPO_FEW 64u
-#define RB_WALK64_SHARED4 32u
-#define RB_WALK64_SHARED2 128u
 hipError_t launch_walk64(rb_ctx *c, const double *sx, const double *sy, const double *sz,
                          int slot);
 hipError_t launch_walk32(rb_ctx *c, const double *sx, const double *sy, const double *sz,

@@ -447,7 +447,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // 88 instead of 95 ns per cell and SIMD).
 //
 // NW: sixteen waves share an item below RB_WALK64_WAVES16 items, eight below
-// RB_WALK64_WAVES8, four above (FP64 steps, us, at NW = 4 / 8 / 16: sheets of
+// RB_WALK64_WAVES8, four above (FP64 steps, us, at NW = 4 / 8 / 16, with whole
+// items only: sheets of
 // 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
 // 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
 // 11.6 against 11.4 ms on 64 patches: four waves read a common part of the

@@ -277,10 +277,10 @@ int build_layout(rb_ctx *c) {
                       c->acc_sets >= (int)RB_WALK64_SHARES;
   const bool few = rounds && c->n_items64 < RB_WALK64_FULL;
   // smallest patch of whose eighths (an XCD each) the last items are shared
-  const uint32_t ends = !rounds                             ? RB_NONE
-                        : c->n_items64 < RB_WALK64_WAVES16 ? RB_WALK64_ENDS16
-                        : c->n_items64 < RB_WALK64_WAVES8  ? RB_WALK64_ENDS8
-                                                           : RB_NONE;
+  const uint32_t ends =
+      !rounds || c->n_items64 >= RB_WALK64_WAVES8 ? RB_NONE
+      : c->n_items64 < RB_WALK64_WAVES16          ? RB_WALK64_ENDS
+                                         : std::max(RB_WALK64_ENDS, c->n_items64 / 3 + 1);
   const uint32_t n_end = c->n_items64 < RB_WALK64_WAVES16 ? 4u : 8u;
   c->h_items64.clear();
   c->item_shares = 1;

@@ -348,7 +348,7 @@ hipError_t launch_rowscan_levels(rb_ctx *c, const uint32_t *reuse = nullptr);
 inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c->walk_parts; }
 // 64-particle items below which sixteen (eight) waves share an item's rounds
 // in the FP64 walk; four above
-#define RB_WALK64_WAVES16 1024u
+#define RB_WALK64_WAVES16 544u
 #define RB_WALK64_WAVES8 8192u
 // Below RB_WALK64_FULL items (the sixteen-wave workgroups that the chip holds
 // at once; one fills its CU's FP64 units) several workgroups share each item
@@ -366,18 +366,21 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 #define RB_WALK64_SHARED2 128u
 // Larger patches: the last items that each XCD is dealt of a patch have two
 // workgroups each, so that its CUs end closer together (their last items are a
-// large part of the walk: 98 items of 50,000 particles for the 64 workgroups of
-// an XCD).  Four items of an XCD with sixteen waves and a patch of more items
-// than CUs (three patches of 10,000 particles, 160 items each, lose: 238 / 274
-// us with none / 4; three of 18,000 368 / 355), eight with eight waves and a
-// patch of RB_WALK64_ENDS8 items.  Two steps of sheets, us, with none / 4 / 8 /
-// 16: 18,000 particles 526 / 427 / 434 / 445, 30,000 564 / 531 / 582 / 593, 50,000 836 / 738 / 755 / 752, 64,000 904 / 904
-// / 901 / 915; with eight waves 100,000 1317 / 1192 / 1152 / 1149, 250,000 2589
-// / 2550 / 2461 / 2452; forces of spheres of 60,000 705 / 684 / 687 / 740,
-// 100,000 910 / 878 / 876 / 910, 200,000 1567 / 1561 / 1559 / 1574.  (With four
-// waves 64 items gain 1.3% on 1,048,583 particles and lose 1.2% on 700,000.)
-#define RB_WALK64_ENDS16 257u
-#define RB_WALK64_ENDS8 1024u
+// large part of the walk: an XCD has 98 items of 50,000 particles for its 128
+// eight-wave or 64 sixteen-wave workgroups).  With sixteen waves four items of
+// an XCD, in patches of more items than CUs (three patches of 10,000 particles,
+// 160 items each, lose: 238 / 274 us with none / 4; three of 18,000 368 / 355);
+// with eight waves eight, in a patch of more than a third of all items (ten
+// patches of 2,000 to 64,000, of 512 items and more / none / such ones: 1228 /
+// 1207 / 1210; two of 17,000 to 30,000 310 with none, 294).  Two steps of sheets, us, sixteen waves with none / 4 / 8, eight with
+// none / 4 / 8 / 16: 30,000 particles 564 / 531 / 582, 643 / 583 / 583 / 583;
+// 33,500 696 / 591 / 601, 732 / 606 / 604 / -; 36,000 - / 635 / -, 744 / 644 /
+// 613 / 612; 50,000 836 / 738 / 755, 870 / 715 / 715 / 714; 64,000 904 / 904 /
+// 901, 875 / 856 / 854 / 837; 100,000 eight 1317 / 1192 / 1152 / 1149, 250,000
+// 2589 / 2550 / 2461 / 2452; forces of spheres of 60,000 705 / 684 / 687, 675 /
+// 663 / 659 / 694, 200,000 eight 1567 / 1561 / 1559 / 1574.  (With four waves 64
+// items gain 1.3% on 1,048,583 particles and lose 1.2% on 700,000.)
+#define RB_WALK64_ENDS 257u
 // topology tiles whose counts are added up by every tile itself instead of by
 // a launch in between (four steps of sheets: 1,000 particles 404 -> 396 us, 3,000
 // 430 -> 423, 4,096 441 -> 436)

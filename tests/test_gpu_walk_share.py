@@ -63,10 +63,10 @@ def test_fp64_items_shared_by_workgroups(n, leaf):
         _close(_gravity(pr, leaf_size=leaf), _gravity(pr, leaf_size=leaf, walk64_schedule=1), 1e-11)
 
 
-@pytest.mark.parametrize("n", [16384, 16385, 32769, 65472, 65473, 65537, 70001])
+@pytest.mark.parametrize("n", [16384, 16385, 32769, 34752, 34753, 65537, 70001])
 def test_fp64_last_items_shared(n):
     # more than 256 items: the last four of every eighth by two workgroups, from
-    # 1,024 items on (eight waves) the last eight; the bound as above
+    # 544 items on (eight waves) the last eight; the bound as above
     for pr in (inputs.sheet(n, seed=n).with_params(theta=0.5),
                inputs.plummer(n, seed=n, b=0.01).with_params(theta=0.6)):
         _close(_gravity(pr), _gravity(pr, walk64_schedule=1), 1e-11)

@@ -152,7 +152,9 @@ void set_split(rb_ctx *c) {
   const uint32_t n_items = c->n_items64;
   const bool fp64 = c->p.precision == RB_FP64;
   int mode = c->p.walk64_schedule;
-  c->walk64_waves = n_items < RB_WALK64_WAVES16 ? 16 : n_items < RB_WALK64_WAVES8 ? 8 : 4;
+  const uint32_t waves8 =
+      c->sort_largest > 64ull * (n_items / 3) ? RB_WALK64_WAVES8 : RB_WALK64_WAVES8_MANY;
+  c->walk64_waves = n_items < RB_WALK64_WAVES16 ? 16 : n_items < waves8 ? 8 : 4;
   const int sp = c->p.split_images;
   if (c->n_img <= 1 || sp == 0) c->img_split = 0;
   else if (sp == 1) c->img_split = 1;

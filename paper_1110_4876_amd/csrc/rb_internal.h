@@ -350,6 +350,11 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // in the FP64 walk; four above
 #define RB_WALK64_WAVES16 544u
 #define RB_WALK64_WAVES8 8192u
+// ... where no patch holds a third of them (us with eight / four waves: steps of
+// 10 patches of 2,000 to 64,000 particles 1210 / 1174, 16 1850 / 1761, 30 3490 /
+// 3242, 40 of 2,000 to 16,000 1383 / 1338; of a single sheet of 350,000 1716 /
+// 1768, 450,000 2138 / 2217, 850,000 3880 / 3822)
+#define RB_WALK64_WAVES8_MANY 4096u
 // Below RB_WALK64_FULL items (the sixteen-wave workgroups that the chip holds
 // at once; one fills its CU's FP64 units) several workgroups share each item
 // of a small patch: RB_WALK64_SHARES for a patch of up to RB_WALK64_SHARED4

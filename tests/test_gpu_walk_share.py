@@ -79,7 +79,10 @@ def test_shared_items_beside_whole_ones():
     from gpu_util import Dev
     from paper_1110_4876_amd import rb
     from test_gpu_batch import _batch_ctx, _concat
-    for sizes in ((100, 2048, 2049, 9000, 64), (100, 2048, 33000)):
+    # (and on both sides of 4,096 items and of a third of them: eight waves with
+    # the largest patch's last items shared, and four)
+    for sizes in ((100, 2048, 2049, 9000, 64), (100, 2048, 33000), (20000, 40000, 9000),
+                  (100000, 90000, 80000), (90000, 90000, 90000)):
         ps = [inputs.sheet(n, seed=n).with_params(theta=0.5) for n in sizes]
         big, off = _concat(ps)
         out = []

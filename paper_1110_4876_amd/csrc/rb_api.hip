@@ -187,6 +187,52 @@ void set_split(rb_ctx *c) {
   }
 }
 
+// The FP64 walk's items, by the patches' sizes, the schedule and the image split
+int make_items(rb_ctx *c) {
+  const uint32_t P = c->P;
+  // patches in descending cost order (n log n)
+  std::vector<uint32_t> order(P);
+  for (uint32_t p = 0; p < P; ++p) order[p] = p;
+  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
+    return c->h_patch[a].n > c->h_patch[b].n;
+  });
+  c->n_items64 = 0;
+  for (uint32_t p = 0; p < P; ++p) c->n_items64 += (c->h_starts[p + 1] - c->h_starts[p] + 63) / 64;
+  // (the rounds of the FP64 walk: an entry for every workgroup that shares the
+  // item, with its share and the number of shares in `node`)
+  const bool rounds = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
+                      !(c->p.split_images == 1 && c->n_img > 1) &&
+                      c->acc_sets >= (int)RB_WALK64_SHARES;
+  const bool few = rounds && c->n_items64 < RB_WALK64_FULL;
+  // smallest patch of whose eighths (an XCD each) the last items are shared
+  const uint32_t ends =
+      !rounds || c->n_items64 >= RB_WALK64_WAVES8 ? RB_NONE
+      : c->n_items64 < RB_WALK64_WAVES16          ? RB_WALK64_ENDS
+                                         : std::max(RB_WALK64_ENDS, c->n_items64 / 3 + 1);
+  const uint32_t n_end = c->n_items64 < RB_WALK64_WAVES16 ? 4u : 8u;
+  c->h_items64.clear();
+  c->item_shares = 1;
+  for (uint32_t p : order) {
+    const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1], np = (s1 - s0 + 63) / 64;
+    const uint32_t k = !few || np > RB_WALK64_SHARED2 ? 1u
+                       : np <= RB_WALK64_SHARED4      ? RB_WALK64_SHARES
+                                                      : 2u;
+    uint32_t i = 0;
+    for (uint32_t x = 0; x < 8; ++x) {  // (eighths as the kernel deals a single patch's units)
+      const uint32_t i1 = i + np / 8 + (x < np % 8 ? 1u : 0u);
+      for (; i < i1; ++i) {
+        const uint32_t s = s0 + 64 * i, ki = np >= ends && i + n_end >= i1 ? 2u : k;
+        c->item_shares = std::max(c->item_shares, (int)ki);
+        for (uint32_t q = 0; q < ki; ++q)
+          c->h_items64.push_back({s, std::min<uint32_t>(s + 64, s1), p, (ki << 8) | q});
+      }
+    }
+  }
+  if (c->h_items64.size() > c->cap / 16 + RB_WALK64_SHARES * (uint64_t)P + 8)
+    return fail(RB_ECAPACITY, "walk item table overflow");
+  return upload_sync(c, c->d_items64, c->h_items64.data(), c->h_items64.size() * sizeof(WalkItem));
+}
+
 // tiles of RB_TILE slots inside each patch; walk items of `g` slots
 int build_layout(rb_ctx *c) {
   const uint32_t P = c->P;
@@ -264,47 +310,7 @@ int build_layout(rb_ctx *c) {
   RB_TRY(upload_sync(c, c->d_starts, c->h_starts.data(), (P + 1) * 4));
   RB_TRY(upload_sync(c, c->d_patch, c->h_patch.data(), P * sizeof(PatchInfo)));
 
-  // walk items, patches in descending cost order (n log n)
-  std::vector<uint32_t> order(P);
-  for (uint32_t p = 0; p < P; ++p) order[p] = p;
-  std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) {
-    return c->h_patch[a].n > c->h_patch[b].n;
-  });
-  c->n_items64 = 0;
-  for (uint32_t p = 0; p < P; ++p) c->n_items64 += (c->h_starts[p + 1] - c->h_starts[p] + 63) / 64;
-  // (the rounds of the FP64 walk: an entry for every workgroup that shares the
-  // item, with its share and the number of shares in `node`)
-  const bool rounds = c->p.precision == RB_FP64 && c->p.walk64_schedule == 0 &&
-                      !(c->p.split_images == 1 && c->n_img > 1) &&
-                      c->acc_sets >= (int)RB_WALK64_SHARES;
-  const bool few = rounds && c->n_items64 < RB_WALK64_FULL;
-  // smallest patch of whose eighths (an XCD each) the last items are shared
-  const uint32_t ends =
-      !rounds || c->n_items64 >= RB_WALK64_WAVES8 ? RB_NONE
-      : c->n_items64 < RB_WALK64_WAVES16          ? RB_WALK64_ENDS
-                                         : std::max(RB_WALK64_ENDS, c->n_items64 / 3 + 1);
-  const uint32_t n_end = c->n_items64 < RB_WALK64_WAVES16 ? 4u : 8u;
-  c->h_items64.clear();
-  c->item_shares = 1;
-  for (uint32_t p : order) {
-    const uint32_t s0 = c->h_starts[p], s1 = c->h_starts[p + 1], np = (s1 - s0 + 63) / 64;
-    const uint32_t k = !few || np > RB_WALK64_SHARED2 ? 1u
-                       : np <= RB_WALK64_SHARED4      ? RB_WALK64_SHARES
-                                                      : 2u;
-    uint32_t i = 0;
-    for (uint32_t x = 0; x < 8; ++x) {  // (eighths as the kernel deals a single patch's units)
-      const uint32_t i1 = i + np / 8 + (x < np % 8 ? 1u : 0u);
-      for (; i < i1; ++i) {
-        const uint32_t s = s0 + 64 * i, ki = np >= ends && i + n_end >= i1 ? 2u : k;
-        c->item_shares = std::max(c->item_shares, (int)ki);
-        for (uint32_t q = 0; q < ki; ++q)
-          c->h_items64.push_back({s, std::min<uint32_t>(s + 64, s1), p, (ki << 8) | q});
-      }
-    }
-  }
-  if (c->h_items64.size() > c->cap / 16 + RB_WALK64_SHARES * (uint64_t)P + 8)
-    return fail(RB_ECAPACITY, "walk item table overflow");
-  RB_TRY(upload_sync(c, c->d_items64, c->h_items64.data(), c->h_items64.size() * sizeof(WalkItem)));
+  RB_TRY(make_items(c));
   set_split(c);
   c->graph_key = -1;
   return RB_OK;
@@ -873,7 +879,9 @@ int rb_set_params(rb_ctx *c, const rb_params *p) {
   if (p->boundary != c->p.boundary || p->n_ghost[0] != c->p.n_ghost[0] ||
       p->n_ghost[1] != c->p.n_ghost[1] || p->drift != c->p.drift)
     return fail(RB_EINVAL, "boundary, ghost rings and drift are fixed at creation");
-  const int old_group = c->p.group_size, old_split = c->p.split_images;
+  const bool items = p->precision != c->p.precision ||
+                     p->walk64_schedule != c->p.walk64_schedule ||
+                     p->split_images != c->p.split_images;
   const double nf = c->p.node_factor;
   rb_params q = *p;
   q.box_size = c->p.box_size;
@@ -882,8 +890,7 @@ int rb_set_params(rb_ctx *c, const rb_params *p) {
   q.node_factor = nf;
   if (q.omega_z == 0.0) q.omega_z = q.omega;
   c->p = q;
-  (void)old_group;
-  (void)old_split;
+  if (items) RB_TRY(make_items(c));  // (an item's workgroups depend on them)
   set_split(c);
   c->graph_key = -1;
   c->lcp_stale = true;

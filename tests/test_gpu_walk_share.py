@@ -102,6 +102,29 @@ def test_shared_items_beside_whole_ones():
             _close(out[0][sl], out[1][sl], 1e-11)
 
 
+@pytest.mark.parametrize("n", [3000, 20000])
+def test_items_follow_changed_parameters(n):
+    # shared items (four workgroups each, or a patch's last ones) and another
+    # schedule, image split or precision set on the same context and back; the
+    # bounds as above (FP32-mixed opens other cells: both are within 10% at
+    # theta = 0.5)
+    from gpu_util import Dev, gravity, make_ctx
+    from paper_1110_4876_amd import rb
+    pr = inputs.sheet(n, seed=n).with_params(theta=0.5)
+    d = Dev(pr, with_v=False)
+    ref = _gravity(pr, walk64_schedule=1)
+    c = make_ctx(pr)
+    try:
+        for kw, tol in (({}, 1e-11), ({"split_images": 1}, 1e-11), ({}, 1e-11),
+                        ({"walk64_schedule": 2}, 1e-11), ({"walk64_schedule": 3}, 1e-11),
+                        ({"precision": rb.RB_FP32_MIXED}, 0.1), ({}, 1e-11),
+                        ({"split_images": 0}, 1e-11)):
+            rb.rb_set_params(c, rb.params_from_problem(pr.params, **kw))
+            _close(gravity(c, d, n, 100.0), ref, tol)
+    finally:
+        rb.rb_destroy(c)
+
+
 @pytest.mark.parametrize("G,leaf", [(16, 1), (16, 8), (64, 1)])
 def test_sparse_children_of_populous_nodes(orc, G, leaf):
     # A sphere's sparse octants beside its core are items of their own.  A

@@ -441,15 +441,15 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // of the whole wave, accepted cells need no test, and the 88 scalar
 // instructions of a visit fall to 11 per cell.  Whole calls, parts -> rounds:
 // 1,024-particle sphere 155 -> 143 us; four steps of the 50,000-particle
-// sheet 2.57 -> 2.15 ms (64 accumulator sets per particle become one); a step
+// sheet 2.57 -> 2.15 ms (64 accumulator sets per particle become one; 1.84 with
+// shared ends, below); a step
 // of 64 patches (2.1e6 particles) 13.4 -> 11.1 ms; 1,048,583-particle sphere
 // 13.6 -> 10.6 ms (of these, FP32's start of the cells' reciprocal roots:
 // 88 instead of 95 ns per cell and SIMD).
 //
 // NW: sixteen waves share an item below RB_WALK64_WAVES16 items, eight below
 // RB_WALK64_WAVES8, four above (FP64 steps, us, at NW = 4 / 8 / 16, with whole
-// items only: sheets of
-// 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
+// items only: sheets of 50,000 743 / 611 / 579, 100,000 1074 / 934 / 947, 250,000 2008 / 1922 /
 // 2087, 700,000 5090 / 5145 / 5756; one wave is slower than four throughout,
 // 11.6 against 11.4 ms on 64 patches: four waves read a common part of the
 // tree).  The items of small patches, and the last ones of larger patches that

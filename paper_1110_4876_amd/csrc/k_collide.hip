@@ -640,8 +640,10 @@ hipError_t launch_coll_step_search(rb_ctx *c, int buf, int slot) {
   return hipGetLastError();
 }
 
-// then the queue, on the sorted state
+// then the queue, on the sorted state (without particles no search has
+// cleared and filled the queue: it may still hold an earlier call's pairs)
 hipError_t launch_coll_step_run(rb_ctx *c, int buf, int slot) {
+  if (c->h_starts[c->P] == 0) return hipSuccess;
   double *const *b = c->d_px[buf];
   hipLaunchKernelGGL(k_coll_run, dim3(CR_BLOCKS), dim3(CR_THREADS), 0, c->stream, rb_coll_queue(c),
                      c->d_csucc, 0ull, b[0], b[1], b[2], b[3], b[4], b[5], b[6], c->d_patch,

@@ -334,7 +334,8 @@ int rb_batch_gravity(rb_ctx *ctx, const rb_particles *p, double t, double *ax,
  * For a batch context n is the total and pairs stay inside their patches.
  * Synchronises.  Errors: RB_EINVAL (null pointer, epsilon, n), RB_EUNSUPPORTED
  * (capacity >= 2^28, or node capacity >= 2^27), RB_ECAPACITY (more than 8
- * pairs per particle), and the deferred errors of the tree build.  Phase
+ * pairs per particle), and the deferred errors of the tree build; a call that
+ * ends with an error leaves vx, vy, vz as they were.  Phase
  * times: "coll_search" is the search kernel, "collide" the rest (R_max, cell
  * records, work items, resolution).
  */
@@ -395,7 +396,8 @@ enum { RB_SWEEP_X = 0, RB_SWEEP_PHI = 1 };
  * RB_EUNSUPPORTED (batch context, phi without an open box, capacity >=
  * 2^28), RB_ECAPACITY (more
  * than 8 pairs per particle), RB_EOUTSIDE (a particle outside a periodic or
- * shear axis).  The context's tree is not kept (the sort reuses its
+ * shear axis); a call that ends with an error leaves vx, vy, vz as they
+ * were.  The context's tree is not kept (the sort reuses its
  * buffers).  Phase times: "coll_search" is the sweep, "collide" the
  * resolution.
  */

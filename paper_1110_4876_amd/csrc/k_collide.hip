@@ -476,6 +476,14 @@ __global__ __launch_bounds__(CR_THREADS) void k_coll_run(
     unsigned long long *__restrict__ n_res, const uint32_t *__restrict__ inv,
     const uint64_t *__restrict__ seedp, const double *__restrict__ sched,
     const uint32_t *__restrict__ ctr, int slot, unsigned long long *__restrict__ cum) {
+  // a call that ends with an error (a full queue, whose pairs are no particular
+  // ones, or any other) leaves the velocities as they were; nothing in this
+  // launch writes the error word
+  const uint32_t failed = inv ? 0u : Q.err[0];
+  if (failed) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) Q.cnt[3] = failed;
+    return;
+  }
   const uint32_t n = min(Q.cnt[0], Q.cap);
   const double *s_end = inv ? sched + (size_t)ctr[slot] * 2 * P + P : nullptr;
   if (inv) seed = seedp[0] + ctr[slot];

@@ -1095,7 +1095,8 @@ static int coll_check_args(rb_ctx *c, rb_particles *p, const double *radius, dou
 }
 
 // The queue the search left: optional copy of the codes, then every collision
-// in one launch; the counts and the error word come back in one copy.
+// in one launch, which changes nothing when the error word is set; the counts
+// and that word come back in one copy.
 static int coll_resolve(rb_ctx *c, rb_particles *p, double t, double epsilon, uint64_t seed,
                         uint64_t *codes, int64_t codes_cap, int64_t *n_pairs,
                         int64_t *n_resolved) {
@@ -1112,7 +1113,7 @@ static int coll_resolve(rb_ctx *c, rb_particles *p, double t, double epsilon, ui
   RB_PHASE(PH_COLLIDE, launch_coll_run(c, p, t, epsilon, seed));
   RB_HIP(hipMemcpyAsync(c->h_cpin, c->d_ccnt, 32, hipMemcpyDeviceToHost, c->stream));
   RB_HIP(hipStreamSynchronize(c->stream));
-  if (h_cnt[3]) return report_device_errors(c);  // (a full queue ends the call here)
+  if (h_cnt[3]) return report_device_errors(c);  // (a full queue: nothing was resolved)
   RB_TRY(mark(c, PH_TOTAL, false));
   if (n_pairs) *n_pairs = (int64_t)h_cnt[0];
   if (n_resolved) {

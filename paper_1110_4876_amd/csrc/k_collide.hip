@@ -504,7 +504,7 @@ __global__ __launch_bounds__(CR_THREADS) void k_coll_run(
         const uint64_t hq = rb_splitmix64(seed + Q.code[q]);
         node[e] = Q.link[node[e]];
         if (hq < h) pred[e] = true;
-        if (hq > h && hq < best[e]) {
+        if (hq > h && hq <= best[e]) {  // (the largest key there is counts too)
           best[e] = hq;
           next[e] = q;
         }

@@ -1,11 +1,13 @@
-"""The collision queue between calls: nothing of an earlier call's pairs is
-left for the next one."""
+"""The collision queue: nothing of an earlier call's pairs is left for the next
+one, and the pair with the largest key that there is has its turn."""
 import numpy as np
 import pytest
 
 from paper_1110_4876_amd import inputs
 
 pytestmark = pytest.mark.gpu
+
+M64 = (1 << 64) - 1
 
 
 @pytest.mark.parametrize("graph", [0, 1])
@@ -36,3 +38,32 @@ def test_steps_without_particles_leave_the_queue(graph):
         assert rb.rb_collision_counts(ctx)[0] > 0
     finally:
         rb.rb_destroy(ctx)
+
+
+def _unxor(z, s):
+    x = z
+    for _ in range(64 // s + 1):
+        x = z ^ (x >> s)
+    return x
+
+
+def _splitmix64_inverse(h):
+    z = _unxor(h, 31)
+    z = _unxor(z * pow(0x94D049BB133111EB, -1, 1 << 64) & M64, 27)
+    z = _unxor(z * pow(0xBF58476D1CE4E5B9, -1, 1 << 64) & M64, 30)
+    return (z - 0x9E3779B97F4A7C15) & M64
+
+
+@pytest.mark.parametrize("pair", [(0, 1), (1, 2)])
+def test_largest_key_is_resolved(orc, pair):
+    # three particles in a row, the outer ones moving in; the seed gives one of
+    # the two pairs the key 2^64 - 1, so that it follows the other
+    from test_gpu_collide import _compare
+    seed = (_splitmix64_inverse(M64) - ((pair[0] << 35) | (pair[1] << 7))) & M64
+    assert orc.splitmix64(seed + ((pair[0] << 35) | (pair[1] << 7))) == M64
+    zero = np.zeros(3)
+    params = inputs.base_params(G=1.0, b=0.0, W=16.0, x0=(-8.0,) * 3)
+    pr = inputs.Problem(np.array([-0.9, 0.0, 0.9]), zero, zero.copy(), np.array([1.0, 0.0, -1.0]),
+                        zero.copy(), zero.copy(), np.ones(3), params, 3, 0.1)
+    npair, nres = _compare(orc, pr, np.full(3, 0.5), 0.0, 0.5, seed)
+    assert npair == 2 and nres == 2

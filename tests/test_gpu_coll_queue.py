@@ -67,3 +67,28 @@ def test_largest_key_is_resolved(orc, pair):
                         zero.copy(), zero.copy(), np.ones(3), params, 3, 0.1)
     npair, nres = _compare(orc, pr, np.full(3, 0.5), 0.0, 0.5, seed)
     assert npair == 2 and nres == 2
+
+
+def test_pile_up_time():
+    # 300 particles in one place, 44,850 pairs, chains of about 800: resolved
+    # side by side by the lanes of a few waves (2.6 ms), not one after the other
+    # (55 ms)
+    from gpu_util import Dev, dev, make_ctx
+    from paper_1110_4876_amd import rb
+    n, pile = 20000, 300
+    rng = np.random.default_rng(5)
+    x, v = rng.uniform(-30.0, 30.0, (3, n)), rng.normal(size=(3, n))
+    x[:, :pile] = 7.0 + rng.uniform(0.0, 0.01, (3, pile))
+    params = inputs.base_params(G=1.0, b=0.0, W=64.0, x0=(-32.0,) * 3)
+    pr = inputs.Problem(*x, *v, rng.uniform(0.5, 2.0, n), params, n, 0.1)
+    r = dev(np.where(np.arange(n) < pile, 0.02, 1e-6))
+    ctx = make_ctx(pr, profile=1)
+    try:
+        ms = []
+        for _ in range(3):
+            npair, _ = rb.rb_collide(ctx, Dev(pr).parts, r, n, 0.0, 0.5, 3)
+            assert npair == pile * (pile - 1) // 2
+            ms.append(rb.rb_stats(ctx)["ms"]["collide"])
+    finally:
+        rb.rb_destroy(ctx)
+    assert min(ms) < 15.0, ms

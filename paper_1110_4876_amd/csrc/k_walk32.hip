@@ -867,22 +867,31 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
       if (STATS) n_pp += (unsigned long long)pl * (unsigned long long)cnt;
     }
     // the partial forces of member m sit in lanes m, m + cnt, ... of every
-    // wave: added in wave order, then lane order (every wave has finished
-    // its list evaluation before the lists' memory is reused)
+    // wave (every wave has finished its list evaluation before the lists'
+    // memory is reused): each lane's are added in wave order, then a member's
+    // lanes pairwise.  (One lane a member over all of them, NW lpp terms in
+    // turn, takes longer than a small group's walk: one particle alone, eight
+    // waves, 38 us.)
     __syncthreads();
     s_red[w][0][lane] = ax; s_red[w][1][lane] = ay; s_red[w][2][lane] = az;
     __syncthreads();
-    if (w == 0 && lane < cnt) {
+    if (w == 0) {
       double tx = 0.0, ty = 0.0, tz = 0.0;
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
-        for (int k = 0; k < lpp; ++k) {
-          tx += s_red[q][0][lane + k * cnt]; ty += s_red[q][1][lane + k * cnt];
-          tz += s_red[q][2][lane + k * cnt];
-        }
+        tx += s_red[q][0][lane]; ty += s_red[q][1][lane]; tz += s_red[q][2][lane];
       }
-      double *a = acc + (size_t)(im0 + part) * 3 * cap;
-      a[s] = tx; a[cap + s] = ty; a[2 * cap + s] = tz;
+      for (int d = 32; d >= 1; d >>= 1) {
+        if (d >= lpp) continue;  // uniform
+        const int from = lane + d * cnt;
+        const double ux = __shfl(tx, from & 63, 64), uy = __shfl(ty, from & 63, 64),
+                     uz = __shfl(tz, from & 63, 64);
+        if (sub < d && sub + d < lpp) { tx += ux; ty += uy; tz += uz; }
+      }
+      if (lane < cnt) {
+        double *a = acc + (size_t)(im0 + part) * 3 * cap;
+        a[s] = tx; a[cap + s] = ty; a[2 * cap + s] = tz;
+      }
     }
     __syncthreads();  // s_red and the stack are reused by the next item
   }

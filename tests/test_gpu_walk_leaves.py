@@ -1,0 +1,39 @@
+"""FP64 walk: leaves of many particles (64 of them held by a wave's lanes at a
+time), some without mass, against the oracle's walk."""
+import numpy as np
+import pytest
+
+from paper_1110_4876_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("pile", [2, 63, 64, 65, 128, 129, 200])
+@pytest.mark.parametrize("leaf", [1, 32])
+def test_large_leaves_match_oracle(orc, pile, leaf):
+    # `pile` particles in one place (a leaf on the deepest level), every third
+    # particle a massless one; decisions as the oracle's, so equal counts, and
+    # FP64 sums of a few thousand terms in another order: 1e-12 of the rms
+    import torch
+    from gpu_util import Dev, make_ctx, rms_rel
+    from paper_1110_4876_amd import rb
+    n = 1500
+    pr = inputs.plummer(n, seed=pile, b=0.05, theta=0.5, quadrupole=True)
+    rng = np.random.default_rng(pile)
+    at = rng.permutation(n)[:pile]
+    for a in (pr.x, pr.y, pr.z):
+        a[at] = 0.7
+    pr.m[rng.permutation(n)[:n // 3]] = 0.0
+    p = orc.make_params(**dict(pr.params, n_leaf=leaf))
+    T = orc.Tree(p, pr.x, pr.y, pr.z, pr.m, n - 100)
+    ref = T.walk()
+    ctx = make_ctx(pr, leaf_size=leaf, profile=2)
+    try:
+        a = torch.empty((3, n), dtype=torch.float64, device="cuda")
+        rb.rb_gravity(ctx, Dev(pr, with_v=False).parts, n, n - 100, 0.0, a[0], a[1], a[2])
+        st = rb.rb_stats(ctx)
+    finally:
+        rb.rb_destroy(ctx)
+    assert rms_rel(a.cpu().numpy().T, ref) <= 1e-12
+    for k in ("open_tests", "cells", "pp"):
+        assert st[k] == T.stats[k], (k, st[k], T.stats[k])

@@ -446,23 +446,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
         pl += __popcll(m);
         if (STATS) n_pp += (unsigned long long)__popcll(m) * (unsigned long long)cnt;
       }
-      // opened bucket leaves: the wave expands them one after another
-      uint64_t bm = __ballot(open_leaf);
-      while (bm) {
-        const int src = __ffsll((long long)bm) - 1;
-        bm &= bm - 1;
-        const uint32_t first = __shfl(lk.child_or_first, src, 64);
-        const uint32_t count = __shfl(lk.count, src, 64);
-        const double bx = __shfl(ox, src, 64), by = __shfl(oy, src, 64);
-        for (uint32_t c0 = 0; c0 < count; c0 += 64) {
+      // opened bucket leaves: their members, 64 of all leaves at a time
+      if (__ballot(open_leaf)) {
+        const uint32_t held = open_leaf ? lk.count : 0u;
+        const uint32_t upto = rb_wave_incl_scan(held);
+        const uint32_t total = (uint32_t)w32_uniform((int)__shfl(upto, 63, 64));
+        const uint32_t slot0 = lk.child_or_first - (upto - held);  // + member number
+        for (uint32_t e0 = 0; e0 < total; e0 += 64) {
           if (pl >= 64) {
             w32_eval_parts<4>(ppos + (pl - 64), h, b2, A, Bs);
             pl -= 64;
           }
-          const uint32_t j = first + c0 + (uint32_t)lane;
-          const bool inb = c0 + (uint32_t)lane < count;
-          const double mj = inb ? msrc[j] : 0.0;
-          const bool use = inb && mj != 0.0;
+          const uint32_t q = e0 + (uint32_t)lane;
+          int of = 0;  // the member's leaf: the first lane that counts past it
+#pragma unroll
+          for (int d = 32; d >= 1; d >>= 1)
+            if (__shfl(upto, of + d - 1, 64) <= q) of += d;
+          const uint32_t j = __shfl(slot0, of, 64) + q;
+          const double bx = __shfl(ox, of, 64), by = __shfl(oy, of, 64);
+          const double mj = q < total ? msrc[j] : 0.0;
+          const bool use = mj != 0.0;
           const uint64_t m = __ballot(use);
           if (use) {
             const int pos = pl + (int)rb_mbcnt(m);

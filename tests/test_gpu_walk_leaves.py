@@ -37,3 +37,28 @@ def test_large_leaves_match_oracle(orc, pile, leaf):
     assert rms_rel(a.cpu().numpy().T, ref) <= 1e-12
     for k in ("open_tests", "cells", "pp"):
         assert st[k] == T.stats[k], (k, st[k], T.stats[k])
+
+
+@pytest.mark.parametrize("pile", [2, 63, 64, 65, 129, 200])
+@pytest.mark.parametrize("leaf", [1, 5, 32])
+@pytest.mark.parametrize("waves", [1, 2])
+def test_large_leaves_fp32(orc, pile, leaf, waves):
+    # FP32-mixed: with theta = 0 every pair is summed, in FP32 with at most 64
+    # terms to a sum (unit roundoff 6e-8), positions rounded to FP32 relative to
+    # the item's centre: 1e-5 of the rms
+    from gpu_util import Dev, gravity, make_ctx, rms_rel
+    from paper_1110_4876_amd import rb
+    n = 700
+    pr = inputs.plummer(n, seed=pile, b=0.3).with_params(theta=0.0, W=16.0, x0=(-8.0,) * 3)
+    rng = np.random.default_rng(pile)
+    at = rng.permutation(n)[:pile]
+    for a in (pr.x, pr.y, pr.z):
+        np.clip(a, -7.0, 7.0, out=a)
+        a[at] = 0.7
+    pr.m[rng.permutation(n)[:n // 3]] = 0.0
+    c = make_ctx(pr, precision=rb.RB_FP32_MIXED, walk_waves=waves, leaf_size=leaf)
+    try:
+        a = gravity(c, Dev(pr, with_v=False), n)
+    finally:
+        rb.rb_destroy(c)
+    assert rms_rel(a, orc.direct(orc.make_params(**pr.params), pr.x, pr.y, pr.z, pr.m)) <= 1e-5

@@ -834,11 +834,13 @@ hipError_t launch_moments(rb_ctx *c, const double *sx, const double *sy, const d
   // bottom large nodes are disjoint subtrees of more than G particles each
   const int lv = c->p.moments_level_log2 > 0 ? c->p.moments_level_log2 : 22;
   const bool one = (uint64_t)n <= (1ull << lv);  // (one workgroup for the levels)
-  // a launch saved where the bottom nodes' records are few for one CU (four
-  // steps of sheets, us, with a launch of their own / without: 3,000 particles
-  // 432 / 424, 12,000 475 / 470, 24,000 542 / 536, 50,000 701 / 719; forces of
-  // spheres 1,024 150 / 149, 24,000 333 / 336)
-  const bool with_bottom = one && n <= 16384;
+  // a launch saved where the bottom nodes (about one in two group_size
+  // particles) are few for one CU (four steps of sheets, us, with a launch of
+  // their own / without: 3,000 particles 432 / 424, 12,000 475 / 470, 24,000 542 /
+  // 536, 50,000 701 / 719; forces of spheres 1,024 150 / 149, 24,000 333 / 336;
+  // builds of sheets, G = 64: 12,000 82 / 79; G = 32: 8,192 79 / 77, 16,384 87 / 88;
+  // G = 16: 4,096 85 / 84, 8,192 88 / 89, 12,000 91 / 96, with leaves of 32 98 / 140)
+  const bool with_bottom = one && (uint64_t)n <= 256ull * G;
   unsigned bgrid = rb_div_up(n / (G + 1) + 1, 64);
   if (bgrid > 2048) bgrid = 2048;
   if (!with_bottom) hipLaunchKernelGGL(k_moments_bottom, dim3(bgrid), dim3(64), 0, c->stream, c->d_bottom,

@@ -576,6 +576,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   __shared__ double2 img[RB_MAX_IMAGES];
   const w64_dbl_p mcom = (w64_dbl_p)mcom_g;
   const w64_dbl_p Qarr = (w64_dbl_p)Q_g;
+  const w64_dbl_p msrc = (w64_dbl_p)msrc_g;
+  const w64_dbl_p sxc = (w64_dbl_p)sx_g, syc = (w64_dbl_p)sy_g, szc = (w64_dbl_p)sz_g;
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t w = NW > 1 ? w64_uniform(threadIdx.x >> 6) : 0u;
   // workgroups are dealt to the eight XCDs in turn; workgroup b takes its
@@ -804,10 +806,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
         }
       }
     }
-    // opened bucket leaves: their members one by one, from lanes that hold one
-    // each (one round trip to memory a leaf and not one a member: forces of
-    // spheres with leaves of 32, 200 particles 149 -> 124 us, 3,000 259 -> 232;
-    // four scalar records at once spill, and cost leaves of one 1 to 2%)
+    // opened bucket leaves: their members one by one, all four words requested
+    // before the first is looked at (forces of spheres of 3,000 with leaves of
+    // 32 256 -> 227 us, 40 patches of 500 to 6,000 with leaves of 16 483 -> 453;
+    // from lanes that hold a member each, 64 of a leaf or of all leaves at a
+    // time, 236 and 509: what is read back lane by lane is issued by the VALU)
     for (uint64_t m = adds ? __ballot(opens && leaf) : 0ull; m; m &= m - 1) {
       const int j = __ffsll((long long)m) - 1;
       const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)lk.child_or_first, j);
@@ -819,19 +822,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
         if (lane == 0) atomicOr(err, RB_ERR_TREE);
         continue;
       }
-      for (uint32_t q0 = a; q0 < e; q0 += 64) {
-        const uint32_t n = min(64u, e - q0), ql = q0 + min(lane, n - 1u);
-        const double mv = msrc_g[ql], xv = sx_g[ql], yv = sy_g[ql], zv = sz_g[ql];
-        for (uint64_t b = __ballot(mv != 0.0 && lane < n); b; b &= b - 1) {
-          const int i = __ffsll((long long)b) - 1;
-          const double mj = w64_readlane_d(mv, i);
-          if (__builtin_amdgcn_inverse_ballot_w64(mine) &&
-              !(imj == self_img && q0 + (uint32_t)i == s)) {
-            const double f0 = w64_readlane_d(xv, i) - y0, f1 = w64_readlane_d(yv, i) - y1,
-                         f2 = w64_readlane_d(zv, i) - pz;
-            w64_mono(mj, f0, f1, f2, w64_r2(f0, f1, f2, b2), ax, ay, az);
-            if (STATS) ++n_pp;
-          }
+      for (uint32_t q = a; q < e; ++q) {
+        const double mj = msrc[q], xj = sxc[q], yj = syc[q], zj = szc[q];
+        const uint64_t on = mj != 0.0 ? mine : 0ull;
+        if (__builtin_amdgcn_inverse_ballot_w64(on) && !(imj == self_img && q == s)) {
+          const double f0 = xj - y0, f1 = yj - y1, f2 = zj - pz;
+          w64_mono(mj, f0, f1, f2, w64_r2(f0, f1, f2, b2), ax, ay, az);
+          if (STATS) ++n_pp;
         }
       }
     }

@@ -871,25 +871,39 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(W32M_WA
     }
     // the partial forces of member m sit in lanes m, m + cnt, ... of every
     // wave (every wave has finished its list evaluation before the lists'
-    // memory is reused): each lane's are added in wave order, then a member's
-    // lanes pairwise.  (One lane a member over all of them, NW lpp terms in
-    // turn, takes longer than a small group's walk: one particle alone, eight
-    // waves, 38 us.)
+    // memory is reused): of two waves they are added in wave order, then lane
+    // order, by the member's lane; of more each lane's in wave order, then a
+    // member's lanes pairwise.  (512 by one lane: a particle alone, eight waves,
+    // 38 us, four steps 328 -> 211; 40 patches of two 449 -> 341; a sphere of
+    // 3,000, groups of 16, 642 -> 550.  Of two waves, sphere of 250,000: 1,150 us
+    // by one lane, 1,160 pairwise.)
     __syncthreads();
     s_red[w][0][lane] = ax; s_red[w][1][lane] = ay; s_red[w][2][lane] = az;
     __syncthreads();
     if (w == 0) {
       double tx = 0.0, ty = 0.0, tz = 0.0;
+      if constexpr (NW == 2) {
+        if (lane < cnt) {
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        tx += s_red[q][0][lane]; ty += s_red[q][1][lane]; tz += s_red[q][2][lane];
-      }
-      for (int d = 32; d >= 1; d >>= 1) {
-        if (d >= lpp) continue;  // uniform
-        const int from = lane + d * cnt;
-        const double ux = __shfl(tx, from & 63, 64), uy = __shfl(ty, from & 63, 64),
-                     uz = __shfl(tz, from & 63, 64);
-        if (sub < d && sub + d < lpp) { tx += ux; ty += uy; tz += uz; }
+          for (int q = 0; q < NW; ++q) {
+            for (int k = 0; k < lpp; ++k) {
+              tx += s_red[q][0][lane + k * cnt]; ty += s_red[q][1][lane + k * cnt];
+              tz += s_red[q][2][lane + k * cnt];
+            }
+          }
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          tx += s_red[q][0][lane]; ty += s_red[q][1][lane]; tz += s_red[q][2][lane];
+        }
+        for (int d = 32; d >= 1; d >>= 1) {
+          if (d >= lpp) continue;  // uniform
+          const int from = lane + d * cnt;
+          const double ux = __shfl(tx, from & 63, 64), uy = __shfl(ty, from & 63, 64),
+                       uz = __shfl(tz, from & 63, 64);
+          if (sub < d && sub + d < lpp) { tx += ux; ty += uy; tz += uz; }
+        }
       }
       if (lane < cnt) {
         double *a = acc + (size_t)(im0 + part) * 3 * cap;

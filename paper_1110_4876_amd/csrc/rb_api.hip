@@ -660,6 +660,7 @@ int build_tree(rb_ctx *c, const rb_particles *p) {
   RB_PHASE(PH_PERMUTE, launch_permute_gravity(c, p->x, p->y, p->z, p->m, 0));
   RB_PHASE(PH_TOPO, launch_topology(c));
   RB_PHASE(PH_MOMENTS, launch_moments(c, c->d_px[0][0], c->d_px[0][1], c->d_px[0][2]));
+  c->cur = 0;
   c->fp64_partial = false;
   c->lcp_stale = true;
   return RB_OK;
@@ -795,6 +796,7 @@ int run_step(rb_ctx *c, rb_particles *p, double t, double dt, int32_t nsteps) {
       else RB_TRY(step_kernels(c, src));
       src = 1 - src;
     }
+    c->cur = src;
     RB_LAUNCH(launch_epilogue(c, p, src));
     RB_TRY(mark(c, PH_TOTAL, false));
     done += chunk;
@@ -952,7 +954,7 @@ int rb_tree_export(rb_ctx *c, int32_t patch, rb_tree_host *o) {
   std::vector<uint32_t> orig(nlive);
   if (nlive) {
     RB_HIP(hipMemcpy(keys.data(), c->d_key[0] + st, 8 * (size_t)nlive, hipMemcpyDeviceToHost));
-    RB_HIP(hipMemcpy(orig.data(), c->d_orig[0] + st, 4 * (size_t)nlive, hipMemcpyDeviceToHost));
+    RB_HIP(hipMemcpy(orig.data(), c->d_orig[c->cur] + st, 4 * (size_t)nlive, hipMemcpyDeviceToHost));
   }
   // nodes of this patch in global (level, patch, prefix) order -> local ids
   std::vector<int64_t> local(nn, -1);

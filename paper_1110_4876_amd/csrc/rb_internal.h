@@ -113,7 +113,7 @@ struct rb_ctx {
   double *d_px[2][7] = {};
   uint32_t *d_orig[2] = {nullptr, nullptr};
   double *d_msrc = nullptr;         // source mass of sorted slots
-  int cur = 0;                      // buffer holding the sorted state
+  int cur = 0;                      // buffer of the last tree's sorted state
 
   // topology; d_lcp: per sorted slot, the octal prefix level it shares with
   // the previous live key of the last tree (255 first slot, 254 dead), for

@@ -140,6 +140,7 @@ __global__ __launch_bounds__(256) void k_sw_keys(
       rb_bucket_add(bcnt, 0, 1, k);
     }
   }
+  if (phi) return;  // (only the images' lookup along x needs the longest one)
   // the longest interval (ordered bits of a non-negative double), one
   // atomic per workgroup: same-address atomics serialise
   __shared__ double part[4];

@@ -10,7 +10,7 @@
 // between the schedules.
 //
 // k_walk64, the walk unless another schedule is asked for: rounds over a
-// stack of opened nodes, one to sixteen waves per 64 Morton-consecutive
+// stack of opened nodes, four to sixteen waves per 64 Morton-consecutive
 // particles (described there).
 //
 // k_walk64_parts (schedules 2 and 3): one wave takes 64 Morton-consecutive
@@ -466,10 +466,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 #define W64G_RESERVE (7 * RB_DEPTH + 8)
 
 // stack entries per item: the rounds' full width while it holds less than
-// CAP - RESERVE - 56 NW; with NW = 1, 5 KB, so that LDS holds 32 waves a CU
+// CAP - RESERVE - 56 NW
 template <int NW>
 constexpr int w64g_cap() {
-  return NW == 1 ? 288 : 512 + 64 * NW;
+  return 512 + 64 * NW;
 }
 
 __device__ __forceinline__ double w64_readlane_d(double v, int j) {
@@ -545,16 +545,6 @@ __device__ __forceinline__ void w64g_cell(const W64Node &n, double d0, double d1
   }
 }
 
-template <int NW>
-__device__ __forceinline__ void w64g_sync() {
-  if (NW > 1) {
-    __syncthreads();
-  } else {  // one wave: order its LDS writes before its later reads
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
 template <bool QUAD, bool STATS, int NW, bool RS32, bool OFF32>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_walk64(
     const WalkItem *__restrict__ items, uint32_t n_units, int img_split, int n_sets, int n_img,
@@ -569,7 +559,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
     const uint32_t *__restrict__ lev_off, uint32_t *__restrict__ err, int slot) {
   constexpr int CAP = w64g_cap<NW>();
   // the stack's memory also takes the waves' partial sums at the end
-  static_assert(NW == 1 || CAP * W64G_ENTRY >= NW * 3 * 64 * 8, "reduction space");
+  static_assert(CAP * W64G_ENTRY >= NW * 3 * 64 * 8, "reduction space");
   static_assert(sizeof(uint4) == W64G_ENTRY, "stack entry");
   __shared__ uint4 stk[CAP];
   __shared__ uint32_t s_push[NW];
@@ -579,7 +569,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
   const w64_dbl_p msrc = (w64_dbl_p)msrc_g;
   const w64_dbl_p sxc = (w64_dbl_p)sx_g, syc = (w64_dbl_p)sy_g, szc = (w64_dbl_p)sz_g;
   const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t w = NW > 1 ? w64_uniform(threadIdx.x >> 6) : 0u;
+  const uint32_t w = w64_uniform(threadIdx.x >> 6);
   // workgroups are dealt to the eight XCDs in turn; workgroup b takes its
   // unit from the (b mod 8)-th eighth, so that each XCD's L2 holds the nodes
   // of one contiguous eighth of them
@@ -644,7 +634,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
       y1 = py - o.y;
     }
   };
-  w64g_sync<NW>();
+  __syncthreads();
   for (;;) {
     if (NW >= 8 && whole && sp >= W64G_SHARE * parts && sp <= 64 * NW) {
       // every part keeps each parts-th entry (neighbours on the stack are
@@ -754,17 +744,14 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
       push = false;
     }
     const uint64_t pm = __ballot(push);
-    int at = sp - k, all = (int)__popcll(pm);
-    if (NW > 1) {
-      if (lane == 0) s_push[w] = (uint32_t)all;
-      __syncthreads();  // every wave has read its entries; counts known
-      all = 0;
+    if (lane == 0) s_push[w] = (uint32_t)__popcll(pm);
+    __syncthreads();  // every wave has read its entries; counts known
+    int at = sp - k, all = 0;
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        const int t = (int)s_push[q];
-        if (q < (int)w) at += t;
-        all += t;
-      }
+    for (int q = 0; q < NW; ++q) {
+      const int t = (int)s_push[q];
+      if (q < (int)w) at += t;
+      all += t;
     }
     sp = sp - k + all;
     if (sp > CAP) {  // cannot happen with the reserve above
@@ -832,20 +819,18 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(8, 8)))
         }
       }
     }
-    w64g_sync<NW>();  // entries written before the next round reads them
+    __syncthreads();  // entries written before the next round reads them
   }
   double *a = acc + (size_t)(im0 + part) * 3 * cap;
-  if (NW > 1) {
-    // the waves' sums, added in wave order
-    double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(&stk[0]);
-    red[w][0][lane] = ax; red[w][1][lane] = ay; red[w][2][lane] = az;
-    __syncthreads();
-    ax = ay = az = 0.0;
-    if (w == 0) {
+  // the waves' sums, added in wave order
+  double(*red)[3][64] = reinterpret_cast<double(*)[3][64]>(&stk[0]);
+  red[w][0][lane] = ax; red[w][1][lane] = ay; red[w][2][lane] = az;
+  __syncthreads();
+  ax = ay = az = 0.0;
+  if (w == 0) {
 #pragma unroll
-      for (int q = 0; q < NW; ++q) {
-        ax += red[q][0][lane]; ay += red[q][1][lane]; az += red[q][2][lane];
-      }
+    for (int q = 0; q < NW; ++q) {
+      ax += red[q][0][lane]; ay += red[q][1][lane]; az += red[q][2][lane];
     }
   }
   if (w == 0 && s < it.end) {

@@ -305,7 +305,10 @@ int rb_step(rb_ctx *ctx, rb_particles *p, int64_t n, int64_t n_active, double t,
             double dt, int32_t nsteps);
 
 /* Batch forms: every patch steps / gets forces independently, one launch
- * per kernel for all patches (work items ordered by patch cost). */
+ * per kernel for all patches (work items ordered by patch cost).  A patch's
+ * tree and the nodes that its particles accept are those it has alone; the
+ * waves and workgroups that add up a particle's sum depend on the size of
+ * the whole launch, so its rounding can differ from a context of its own. */
 int rb_batch_step(rb_ctx *ctx, rb_particles *p, double t, double dt, int32_t nsteps);
 int rb_batch_gravity(rb_ctx *ctx, const rb_particles *p, double t, double *ax,
                      double *ay, double *az);

@@ -433,13 +433,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(8, 8))) void
 // corners y bounds every lane's value from below (above), rounding included.
 // So every particle sees exactly the nodes its own stackless walk sees.
 //
-// Bound by FP64 issue: VALU busy 96% of the time, half of its lanes at work
-// (the lanes of a mask; 64 particles of a thin sheet need 1.9 times the nodes
-// that one needs).  A cell costs 36 FP64 operations and one FP32 reciprocal
-// root, its record arriving by scalar loads.  Against the node-by-node walk
-// of k_walk64_parts, opened nodes cost one lane of a round instead of a visit
-// of the whole wave, accepted cells need no test, and the 88 scalar
-// instructions of a visit fall to 11 per cell.  Whole calls, parts -> rounds:
+// Bound by FP64 issue: on 256 sheets of 2,000 to 64,000 particles (four
+// waves) the vector units are busy 91% of the time and issue 0.85 of a vector
+// instruction per SIMD and quad-cycle, with 53% of their lanes at work (the
+// lanes of a mask; 64 particles of a thin sheet need 1.9 times the nodes that
+// one needs); on 1,048,583 particles of a sphere 93%, 0.87 and 64%; on one
+// sheet of 50,000 (eight waves, 782 items) 58%, 0.55 and 53%.  A cell costs 36
+// FP64 operations and one FP32 reciprocal root, its record arriving by scalar
+// loads; with the opening tests and the particles' pairs, 60 vector and 26
+// scalar instructions are issued for a wave's cell.  Against the node-by-node
+// walk of k_walk64_parts, opened nodes cost one lane of a round instead of a
+// visit of the whole wave, accepted cells need no test, and the scalar
+// instructions of the launch are half (256 sheets 9.2e9; the parts' rate of
+// 0.60 per CU and cycle over their 50 ms is 1.8e10).  Whole calls, parts -> rounds:
 // 1,024-particle sphere 155 -> 143 us; four steps of the 50,000-particle
 // sheet 2.57 -> 2.15 ms (64 accumulator sets per particle become one; 1.84 with
 // shared ends, below); a step

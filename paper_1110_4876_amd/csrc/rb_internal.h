@@ -358,8 +358,12 @@ inline int rb_n_acc(const rb_ctx *c) { return (c->img_split ? c->n_img : 1) * c-
 // Below RB_WALK64_FULL items (the sixteen-wave workgroups that the chip holds
 // at once; one fills its CU's FP64 units) several workgroups share each item
 // of a small patch: RB_WALK64_SHARES for a patch of up to RB_WALK64_SHARED4
-// items, two up to RB_WALK64_SHARED2.  (By the patch's size, so that a patch
-// of a batch gets the sums that it gets alone.)  Us with 1 / 2 / 4 per item:
+// items, two up to RB_WALK64_SHARED2: by the patch's size, but only where the
+// launch's items, those of all patches, are few; like the waves per item, so
+// that a patch's sums can be added in another order in a batch than alone.
+// Larger patches get none here: sheets of 8,200 to 16,400 particles alone
+// would gain up to 12% by two, patches of them side by side and spheres lose.
+// Us with 1 / 2 / 4 per item:
 // two steps of sheets of 1,000 particles (16 items) 312 / 244 / 215, 3,000 370
 // / 278 / 248, 6,000 406 / 307 / 310, 12,000 433 / 381 / 418, 25,000 586 / 586
 // / 636; forces of spheres of 3,000 187 / 168 / 169, 6,000 221 / 207 / 224,

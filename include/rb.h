@@ -208,7 +208,11 @@ void rb_params_default(rb_params *p);
 /*
  * Create a context for one system of up to `capacity` particles on the
  * current HIP device, issuing work on `hip_stream` (a hipStream_t; NULL =
- * the null stream).  Allocates all workspace (about 0.6 kB per particle).
+ * the null stream).  Allocates all workspace: about 0.9 kB per particle, and
+ * 24 bytes per particle for every set of sums that walk64_schedule 3 can use
+ * within 2 GiB (in all 2.5 kB per particle of up to 1.4 million, 1.1 kB above;
+ * with 3x3 ghost boxes 15 kB of up to 157,000).  The first collision search
+ * adds 0.32 kB per particle.
  * Errors: RB_EINVAL for invalid parameters (see rb_params), RB_ENOMEM,
  * RB_EUNSUPPORTED (n_ghost > 2).
  */
